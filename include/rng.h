@@ -173,14 +173,16 @@ int rng_calibrate_store(uint32_t *d_state, uint64_t n_streams, uint64_t n, void 
 int rng_skip(int g, uint32_t *d_state, uint64_t n_streams, uint64_t k, void *stream);
 
 /* Sequence splitting (Sec. II.A.4): one logical stream, d_state_one
- * ([words] uint32, device, read only), produces `total` samples divided
- * across n_threads GPU threads, thread t writing samples
- * [t*C, min((t+1)*C, total)) with C = ceil(total / n_threads), each thread
- * starting from the jumped-ahead state, so that d_out[0 .. total) equals the
- * serial sequence.  The advanced state is written to d_final_state ([words],
- * device; may alias d_state_one).  d_workspace of at least
- * rng_split_workspace_bytes(g, n_threads) bytes, 256-byte aligned, caller
- * owned, holds the per-thread states. */
+ * ([words] uint32, device, read only), produces `total` samples divided over
+ * the device's threads, each starting from the jumped-ahead state, so that
+ * d_out[0 .. total) equals the serial sequence.  The advanced state is written
+ * to d_final_state ([words], device; may alias d_state_one).  d_workspace of
+ * at least rng_split_workspace_bytes(g, n_threads) bytes, 256-byte aligned,
+ * caller owned, holds the start states of up to n_threads threads.  XS256
+ * takes thread t's samples as [t*C, min((t+1)*C, total)) with
+ * C = ceil(total / n_threads); the other generators, whose jump is a few
+ * instructions, cut the sequence into blocks that suit the device and leap
+ * from block to block, whatever n_threads is. */
 int rng_split_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes);
 int rng_generate_split(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                        int t, void *d_out, uint32_t *d_final_state, void *d_workspace,
@@ -204,19 +206,19 @@ int rng_generate_split_noalloc(int g, const uint32_t *d_state_one, uint64_t tota
                                int t, void *d_out, uint32_t *d_final_state, void *stream);
 
 /* Leapfrogging (Sec. II.A.4): the same sequence and output as
- * rng_generate_split, computed the other way round.  With T = min(n_threads,
- * total) threads, thread j emits numbers j, j + T, j + 2T, ... of the serial
- * sequence, so d_out[i] is number i and every wave stores 64 consecutive
- * numbers.  Thread j starts at the state after j steps (a radix-16 tree of
- * jumps), steps once, and then advances T steps per number with the
- * generator's T-step map: one modular multiply per MWC word, a 32x32 GF(2)
- * product for xorshift32, a 256x256 one for XS256 (through a 4-bit table of
- * M^T in LDS), an affine map for the LCG.  d_out[0 .. total) equals the
- * serial sequence; the advanced state goes to d_final_state ([words], device;
- * may alias d_state_one).  d_workspace of at least
- * rng_leapfrog_workspace_bytes(g, T) bytes, 256-byte aligned, caller owned,
- * holds the thread states and the T-step constants.  Errors as
- * rng_generate_split. */
+ * rng_generate_split, interleaved over the threads.  XS256, with
+ * T = min(n_threads, total) threads: thread j emits numbers j, j + T,
+ * j + 2T, ... of the serial sequence, starting at the state after j steps (a
+ * radix-16 tree of jumps) and advancing T steps per number by the T-step map,
+ * a 256x256 GF(2) product through a 4-bit table of M^T in LDS.  The other
+ * generators interleave blocks of 32 to 128 numbers instead of single ones, so
+ * that the leap (one modular multiply per MWC word, a 32x32 GF(2) product for
+ * xorshift32, an affine map for the LCG) is paid once per block, whatever
+ * n_threads is.  d_out[0 .. total) equals the serial sequence; the advanced
+ * state goes to d_final_state ([words], device; may alias d_state_one).
+ * d_workspace of at least rng_leapfrog_workspace_bytes(g, T) bytes, 256-byte
+ * aligned, caller owned, holds the thread states and the T-step constants.
+ * Errors as rng_generate_split. */
 int rng_leapfrog_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes);
 int rng_generate_leapfrog(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                           int t, void *d_out, uint32_t *d_final_state, void *d_workspace,

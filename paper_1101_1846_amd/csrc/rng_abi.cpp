@@ -341,6 +341,22 @@ static void rot_constants(int g, uint64_t N, GenArgs &a)
     std::memcpy(a.rot_lcg, hit->lcg, sizeof(hit->lcg));
 }
 
+// Streams that run as long sequences, windows of consecutive numbers across a
+// wave (seq.hip), instead of a row or chunk per lane: up to one stream per
+// wave of the device from the shortest rows that fill a window of 32-number
+// blocks on (KISS, us, rows against windows: 64 x 4096 24.3 / 13.8, 1000 x
+// 10^5 112 / 100, 100 x 1000001 232 / 98; MWC32 equal to within 1 us where the
+// call is launch-bound), and more streams if their rows start inside 128-byte
+// lines and are long enough to pay for a wave's start (KISS 10^4 x 25001
+// 643 / 324, 1500 x 100001 345 / 173; but 10^4 x 10^4 125 / 203, and with
+// whole lines 10^4 x 16384 193 / 192).
+static bool seq_streams(int g, uint64_t S, uint64_t N, const void *out)
+{
+    if (!seq_gen(g)) return false;
+    if (S <= kSeqWaves) return N >= 2048;
+    return N >= 16384 && S <= ((uint64_t)1 << 24) && (N % 32 != 0 || ((uintptr_t)out & 127));
+}
+
 // Shared by rng_generate and the split path: one generate launch over
 // S streams whose states live at stride ld.
 int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint64_t N, void *d_out,
@@ -359,6 +375,10 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
     a.vec4 = (N % 4 == 0) && (((uintptr_t)d_out & 15) == 0);
     a.nt = 0;  // plain stores: the streaming hint measured slower for these writes
     a.tab = tab;
+    if (staged && seq_streams(g, S, N, d_out)) {
+        if (int e = check_launch(launch_seq(g, dt, d_state, ld, S, N, d_out, nullptr, tab, st), "rng_generate")) return e;
+        return check_launch(dispatch_skip(g, d_state, ld, S, N, tab, st), "rng_generate: state");
+    }
     if (staged && S < 64) {
         uint64_t c;
         uint32_t P;
@@ -432,6 +452,7 @@ int split_run(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_thr
     if (int rc = split_scratch_bytes(g, total, n_threads, &need)) return rc;
     if (ws_bytes < need)
         return fail(RNG_ENOMEM, "workspace %llu bytes < %llu", (unsigned long long)ws_bytes, (unsigned long long)need);
+    if (seq_gen(g)) return seq_run(g, d_state_one, total, t, d_out, d_final_state, ws, tab, st);
     // radix-16 tree: level l starts threads [16^l, 16^(l+1)) from threads below 16^l;
     // the start state's copy and levels 0 .. 2 in one launch
     uint64_t far;

@@ -53,6 +53,20 @@ int dispatch_state_copy(int g, const uint32_t *src, uint64_t ss, uint64_t si, ui
 int generate_few(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint64_t N, uint64_t C, uint64_t P,
                  void *d_out, const DevTables &tab, hipStream_t st);
 
+// Long sequences of few streams without tables of start states (seq.hip; every
+// generator but XS256): S streams of N numbers from states at word stride ld
+// into out [S][N].  With S = 1 the state after the last number goes to
+// final_state if that is not null (it must not overlap the start state); the
+// start states are not written.
+constexpr uint64_t kSeqWaves = 1024;  // 4 per CU
+inline bool seq_gen(int g) { return g != RNG_XS256; }
+int launch_seq(int g, int dt, const uint32_t *state, uint64_t ld, uint64_t S, uint64_t N, void *out,
+               uint32_t *final_state, const DevTables &tab, hipStream_t st);
+// One sequence of `total` numbers through launch_seq; a final state that
+// overlaps the start state goes by a copy of it in ws (one state).
+int seq_run(int g, const uint32_t *state_one, uint64_t total, int t, void *out, uint32_t *final_state, uint32_t *ws,
+            const DevTables &tab, hipStream_t st);
+
 // Tables of the current device only if they exist already (never allocates).
 int device_tables_if_ready(DevTables *out);
 // Looks up, once per device, the address of the allocation-free entry

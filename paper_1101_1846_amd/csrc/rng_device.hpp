@@ -112,6 +112,16 @@ __device__ __forceinline__ uint32_t gf2_apply32(const uint32_t *__restrict__ col
     return r;
 }
 
+// The XOR of r over lanes 0 .. 31, in every lane (uniform); all lanes active.
+__device__ __forceinline__ uint32_t xor_over_32(uint32_t r)
+{
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x141, 0xF, 0xF, false);  // row_half_mirror
+    r ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x140, 0xF, 0xF, false);  // row_mirror
+    return (uint32_t)__builtin_amdgcn_readlane((int)r, 0) ^ (uint32_t)__builtin_amdgcn_readlane((int)r, 16);
+}
+
 // x <- M x for a 256x256 GF(2) matrix M given by its 4-bit lookup table T
 // (2048 quads, 32 KiB): quads (2p + h) * 16 + v hold words 4h .. 4h+3 of the
 // XOR of columns 4p + k over the set bits k of v.  The product is the XOR of

@@ -188,9 +188,67 @@ __global__ __launch_bounds__(kSkipWG) void k_skip_each(SkipArgs a)
     g.store(a.st, a.ld, s);
 }
 
+// A wave per state, for few states: the k-step map is built from the step's own
+// constants in registers, so that nothing is prepared in LDS or on the host (a
+// table of 392 MWC16 constants per workgroup took the launch to 15 us for one
+// KISS state).  Lanes below 32 carry the first MWC16 word, the others the
+// second; lane c of 32 holds column c of each xorshift32 power, read 16 powers
+// ahead, and a product is an XOR over those lanes.
+constexpr uint64_t kSkipWaveMax = 4096;
+
+template <class G>
+__global__ __launch_bounds__(64) void k_skip_wave(SkipArgs a)
+{
+    constexpr bool kMwc16 = G::kId == G_MWC1616 || G::kId == G_KISS;
+    constexpr bool kXs32 = G::kId == G_XS32 || G::kId == G_KISS;
+    const int lane = threadIdx.x;
+    G g;
+    g.load(a.st, a.ld, blockIdx.x, a.tab);
+    const int nb = 64 - __builtin_clzll(a.k);  // k > 0
+    uint32_t y = 0;
+    if constexpr (G::kId == G_XS32) y = g.y;
+    if constexpr (G::kId == G_KISS) y = g.jsr;
+    if constexpr (kXs32) {
+        y = (uint32_t)__builtin_amdgcn_readfirstlane((int)y);
+        for (int b0 = 0; b0 < nb; b0 += 16) {
+            uint32_t col[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) col[i] = a.tab.xs32_pow[(b0 + i) * 32 + (lane & 31)];  // 64 powers
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if ((a.k >> (b0 + i)) & 1) y = xor_over_32(col[i] & (0u - ((y >> (lane & 31)) & 1u)));
+        }
+    }
+    if constexpr (G::kId == G_XS32) g.y = y;
+    if constexpr (kMwc16) {
+        const uint32_t ai = lane < 32 ? g.a1 : g.a2, m = ai * 65536u - 1u;
+        uint32_t z = lane < 32 ? g.z : g.w, c = (0u - m) % m;  // one step is a; a 2^48 = 2^32 (mod m)
+        uint32_t la = 69069u, lc = 1234567u;
+        for (int b = 0; b < nb; ++b) {
+            if ((a.k >> b) & 1) {
+                z = mwc16_mulmod(z, c, ai);
+                if constexpr (G::kId == G_KISS) g.jcong = la * g.jcong + lc;
+            }
+            c = mwc16_mulmod(c, c, ai);
+            lc = la * lc + lc;
+            la *= la;
+        }
+        g.z = (uint32_t)__builtin_amdgcn_readlane((int)z, 0);
+        g.w = (uint32_t)__builtin_amdgcn_readlane((int)z, 32);
+        if constexpr (G::kId == G_KISS) g.jsr = y;
+    }
+    if (lane == 0) g.store(a.st, a.ld, blockIdx.x);
+}
+
 template <class G>
 int launch_skip_by(const SkipArgs &a, hipStream_t stream)
 {
+    if constexpr (G::kId == G_XS32 || G::kId == G_KISS || G::kId == G_MWC1616) {
+        if (a.S <= kSkipWaveMax) {
+            hipLaunchKernelGGL(k_skip_wave<G>, dim3((unsigned)a.S), dim3(64), 0, stream, a);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        }
+    }
     if (G::kId == G_XS256 && a.S < kXs256TableMin) {  // see the file comment
         hipLaunchKernelGGL(k_skip_each<G>, dim3((unsigned)((a.S + kSkipWG - 1) / kSkipWG)), dim3(kSkipWG), 0, stream,
                            a);
@@ -219,7 +277,7 @@ int dispatch_skip(int g, uint32_t *st, uint64_t ld, uint64_t S, uint64_t k, cons
     a.k = k;
     a.tab = tab;
     if (g == RNG_MWC32) a.mwc32_f = mwc32_fold_const(k);
-    if (g == RNG_XS32 || g == RNG_KISS) xs32_lcg_jump(k, a.xs32, &a.lcg_a, &a.lcg_c);
+    if ((g == RNG_XS32 || g == RNG_KISS) && S > kSkipWaveMax) xs32_lcg_jump(k, a.xs32, &a.lcg_a, &a.lcg_c);
     switch (g) {
     case RNG_MWC32: return launch_skip_by<GenMWC32>(a, s);
     case RNG_XS256: return launch_skip_by<GenXS256>(a, s);
