@@ -409,6 +409,9 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
         a.rot = 1;
         rot_constants(g, N, a);
     }
+    if (staged && a.P == 1 && shape.wg <= 256 && N >= kRowMin && N <= kRowMax &&
+        (!a.vec4 || S % 64 != 0 || N % kGenTile != 0))
+        return check_launch(launch_rows(g, dt, d_state, ld, S, N, N, d_out, true, nullptr, tab, st), "rng_generate");
     rc = dispatch_generate(g, dt, a, (int)shape.wg, (int)shape.unroll, staged, st);
     if (rc != kStatesNotWritten) return check_launch(rc, "rng_generate");
     // chunks of one stream in several workgroups: the states advance after

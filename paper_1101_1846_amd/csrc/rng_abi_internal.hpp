@@ -67,6 +67,13 @@ int launch_seq(int g, int dt, const uint32_t *state, uint64_t ld, uint64_t S, ui
 int seq_run(int g, const uint32_t *state_one, uint64_t total, int t, void *out, uint32_t *final_state, uint32_t *ws,
             const DevTables &tab, hipStream_t st);
 
+// Rows of any length (32 <= C < 2^24), count and alignment, one per lane
+// (rows.hip): R rows of C numbers one after the other in out, the last one of
+// `last`, from states at word stride ld, which are rewritten if write_back.
+constexpr uint64_t kRowMin = 32, kRowMax = ((uint64_t)1 << 24) - 1;
+int launch_rows(int g, int dt, uint32_t *state, uint64_t ld, uint64_t R, uint64_t C, uint64_t last, void *out,
+                bool write_back, uint32_t *final_state, const DevTables &tab, hipStream_t st);
+
 // Tables of the current device only if they exist already (never allocates).
 int device_tables_if_ready(DevTables *out);
 // Looks up, once per device, the address of the allocation-free entry
