@@ -174,15 +174,13 @@ int rng_skip(int g, uint32_t *d_state, uint64_t n_streams, uint64_t k, void *str
 
 /* Sequence splitting (Sec. II.A.4): one logical stream, d_state_one
  * ([words] uint32, device, read only), produces `total` samples divided over
- * the device's threads, each starting from the jumped-ahead state, so that
+ * the device's threads, each starting from jumped-ahead states, so that
  * d_out[0 .. total) equals the serial sequence.  The advanced state is written
- * to d_final_state ([words], device; may alias d_state_one).  d_workspace of
- * at least rng_split_workspace_bytes(g, n_threads) bytes, 256-byte aligned,
- * caller owned, holds the start states of up to n_threads threads.  XS256
- * takes thread t's samples as [t*C, min((t+1)*C, total)) with
- * C = ceil(total / n_threads); the other generators, whose jump is a few
- * instructions, cut the sequence into blocks that suit the device and leap
- * from block to block, whatever n_threads is. */
+ * to d_final_state ([words], device; may alias d_state_one).  The sequence is
+ * cut into blocks of consecutive samples that suit the device; n_threads only
+ * sizes the workspace.  d_workspace of at least
+ * rng_split_workspace_bytes(g, n_threads) bytes, 256-byte aligned, caller
+ * owned, holds a copy of the start state when the final one overlaps it. */
 int rng_split_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes);
 int rng_generate_split(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                        int t, void *d_out, uint32_t *d_final_state, void *d_workspace,
@@ -190,35 +188,31 @@ int rng_generate_split(int g, const uint32_t *d_state_one, uint64_t total, uint6
 
 /* For callers that cannot allocate (code under HIP graph capture, serving
  * loops, harnesses that forbid hipMalloc): rng_generate_split without a
- * workspace argument.  The thread states live in a device array of
- * RNG_SPLIT_NOALLOC_SCRATCH_BYTES that the library holds on every device it
- * runs on until the process ends; the call itself makes no hipMalloc, hipFree
- * or other allocating call.  rng_init() must have run on the current device
- * (it builds the tables and looks up the array's address), else RNG_EINVAL.
- * A split needs 4 * W * T bytes (W state words, T = ceil(total / C) threads
- * with work, C = ceil(total / n_threads)); larger splits return RNG_ERANGE
- * (32 MiB holds 2^20 threads of every generator).  Every call on one device
- * shares the array and leaves it holding its thread states, so calls that
- * overlap on one device (other streams, other host threads) race: serialise
- * them.  Arguments, output and errors otherwise as rng_generate_split. */
+ * workspace argument.  A start state that the final one overlaps is copied to
+ * a small device array that the library holds on every device it runs on until
+ * the process ends; the call itself makes no hipMalloc, hipFree or other
+ * allocating call.  rng_init() must have run on the current device (it builds
+ * the tables and looks up the array's address), else RNG_EINVAL.  Splits whose
+ * workspace (4 * W * T bytes: W state words, T = ceil(total / C) threads with
+ * work, C = ceil(total / n_threads)) exceeds RNG_SPLIT_NOALLOC_SCRATCH_BYTES
+ * return RNG_ERANGE (32 MiB is 2^20 threads of every generator).  Every call
+ * on one device shares the array, so calls that overlap in time on one device
+ * (other streams, other host threads) race: serialise them.  Arguments, output
+ * and errors otherwise as rng_generate_split. */
 #define RNG_SPLIT_NOALLOC_SCRATCH_BYTES (32u << 20)
 int rng_generate_split_noalloc(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                                int t, void *d_out, uint32_t *d_final_state, void *stream);
 
 /* Leapfrogging (Sec. II.A.4): the same sequence and output as
- * rng_generate_split, interleaved over the threads.  XS256, with
- * T = min(n_threads, total) threads: thread j emits numbers j, j + T,
- * j + 2T, ... of the serial sequence, starting at the state after j steps (a
- * radix-16 tree of jumps) and advancing T steps per number by the T-step map,
- * a 256x256 GF(2) product through a 4-bit table of M^T in LDS.  The other
- * generators interleave blocks of 32 to 128 numbers instead of single ones, so
- * that the leap (one modular multiply per MWC word, a 32x32 GF(2) product for
- * xorshift32, an affine map for the LCG) is paid once per block, whatever
- * n_threads is.  d_out[0 .. total) equals the serial sequence; the advanced
- * state goes to d_final_state ([words], device; may alias d_state_one).
- * d_workspace of at least rng_leapfrog_workspace_bytes(g, T) bytes, 256-byte
- * aligned, caller owned, holds the thread states and the T-step constants.
- * Errors as rng_generate_split. */
+ * rng_generate_split, interleaved over the threads.  Blocks of consecutive
+ * numbers are interleaved, not single ones, so that the leap (one modular
+ * multiply per MWC word, a GF(2) product for the XorShifts, an affine map for
+ * the LCG) is paid once per block; n_threads only sizes the workspace.
+ * d_out[0 .. total) equals the serial sequence; the advanced state goes to
+ * d_final_state ([words], device; may alias d_state_one).  d_workspace of at
+ * least rng_leapfrog_workspace_bytes(g, T) bytes, T = min(n_threads, total),
+ * 256-byte aligned, caller owned, holds a copy of the start state when the
+ * final one overlaps it.  Errors as rng_generate_split. */
 int rng_leapfrog_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes);
 int rng_generate_leapfrog(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                           int t, void *d_out, uint32_t *d_final_state, void *d_workspace,

@@ -6,7 +6,9 @@
 // the wave's LDS tile, and the tile goes out row by row through per-row
 // destination pointers, consecutive lanes on consecutive 16-byte quads.  No
 // chunk writes the state back (the others read it at unordered times): the
-// host advances the states by N with a skip launch afterwards.
+// host advances the states by N with a skip launch afterwards.  Only rows too
+// short for windows of consecutive numbers (seq.hip) come here, so never XS256,
+// whose chunks are longer.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -153,7 +155,6 @@ int generate_few(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint
     int rc = -2;
     switch (g) {
     case RNG_MWC32: rc = launch_lanes_t<GenMWC32>(dt, a, st); break;
-    case RNG_XS256: rc = launch_lanes_t<GenXS256>(dt, a, st); break;
     case RNG_XS32: rc = launch_lanes_t<GenXS32>(dt, a, st); break;
     case RNG_KISS: rc = launch_lanes_t<GenKISS>(dt, a, st); break;
     case RNG_MWC1616: rc = launch_lanes_t<GenMWC1616>(dt, a, st); break;

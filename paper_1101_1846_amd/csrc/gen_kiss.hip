@@ -3,5 +3,4 @@
 
 namespace rngx {
 RNGX_INSTANTIATE(GenKISS)
-RNGX_INSTANTIATE_TREE_HEAD(GenKISS)
 }  // namespace rngx

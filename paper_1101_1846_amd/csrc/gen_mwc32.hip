@@ -3,5 +3,4 @@
 
 namespace rngx {
 RNGX_INSTANTIATE(GenMWC32)
-RNGX_INSTANTIATE_TREE_HEAD(GenMWC32)
 }  // namespace rngx

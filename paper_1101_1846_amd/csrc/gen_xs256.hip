@@ -3,5 +3,4 @@
 
 namespace rngx {
 RNGX_INSTANTIATE(GenXS256)
-RNGX_INSTANTIATE_TREE_HEAD(GenXS256)
 }  // namespace rngx

@@ -3,5 +3,4 @@
 
 namespace rngx {
 RNGX_INSTANTIATE(GenXS32)
-RNGX_INSTANTIATE_TREE_HEAD(GenXS32)
 }  // namespace rngx

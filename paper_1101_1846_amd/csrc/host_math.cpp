@@ -169,6 +169,59 @@ Gf2Mat<8> xs256_step_matrix()
 Gf2Mat<1> xs32_step_matrix() { return I_plus_L(5) * I_plus_R(17) * I_plus_L(13); }
 
 // ---------------------------------------------------------------- tables
+// Polynomials over GF(2) of degree below 256, bit i the coefficient of x^i.
+struct Gf2Poly {
+    uint64_t w[4];
+};
+
+// a b mod (x^256 + f).
+static Gf2Poly poly_mulmod(const Gf2Poly &a, const Gf2Poly &b, const Gf2Poly &f)
+{
+    Gf2Poly r{{0, 0, 0, 0}};
+    for (int i = 255; i >= 0; --i) {
+        const uint64_t top = 0 - (r.w[3] >> 63), on = 0 - ((b.w[i / 64] >> (i % 64)) & 1);
+        for (int k = 3; k > 0; --k) r.w[k] = (r.w[k] << 1) | (r.w[k - 1] >> 63);
+        r.w[0] <<= 1;
+        for (int k = 0; k < 4; ++k) r.w[k] ^= (f.w[k] & top) ^ (a.w[k] & on);
+    }
+    return r;
+}
+
+// The characteristic polynomial x^256 + f of the XS256 step, as the shortest
+// recurrence of one bit of its output (Berlekamp-Massey, Massey 1969); the step
+// has the full period, so the recurrence has degree 256.
+static Gf2Poly xs256_char_poly()
+{
+    constexpr int n = 640;
+    const Gf2Mat<8> M = xs256_step_matrix();
+    std::vector<int> bit(n);
+    uint32_t v[8] = {1, 0, 0, 0, 0, 0, 0, 0}, u[8];
+    for (int i = 0; i < n; ++i) {
+        M.apply(v, u);
+        std::memcpy(v, u, sizeof(v));
+        bit[i] = v[7] & 1;
+    }
+    std::vector<int> C(n + 1), B(n + 1), t;
+    C[0] = B[0] = 1;
+    int L = 0, m = 1;
+    for (int i = 0; i < n; ++i, ++m) {
+        int d = bit[i];
+        for (int k = 1; k <= L; ++k) d ^= C[k] & bit[i - k];
+        if (!d) continue;
+        t = C;
+        for (int k = 0; k + m <= n; ++k) C[k + m] ^= B[k];
+        if (2 * L <= i) {
+            L = i + 1 - L;
+            B = t;
+            m = 0;
+        }
+    }
+    Gf2Poly f{{0, 0, 0, 0}};  // x^256 C(1/x)
+    for (int k = 1; k <= 256; ++k)
+        if (C[k]) f.w[(256 - k) / 64] |= (uint64_t)1 << ((256 - k) % 64);
+    return f;
+}
+
 static HostTables *build_tables()
 {
     auto *T = new HostTables();
@@ -232,6 +285,19 @@ static HostTables *build_tables()
     }
     delete base;
     delete P;
+    const Gf2Poly f = xs256_char_poly();
+    Gf2Poly xp{{2, 0, 0, 0}};  // x^(2^j)
+    T->xs256_poly.resize((size_t)8 * 64 * 8);
+    for (int j = 0; j <= 12; ++j) {
+        if (j >= 5) {
+            Gf2Poly c{{1, 0, 0, 0}};
+            for (int l = 0; l < 64; ++l) {
+                std::memcpy(&T->xs256_poly[((size_t)(j - 5) * 64 + l) * 8], c.w, sizeof(c.w));
+                c = poly_mulmod(c, xp, f);
+            }
+        }
+        xp = poly_mulmod(xp, xp, f);
+    }
     return T;
 }
 

@@ -50,6 +50,7 @@ struct HostTables {
     std::vector<uint32_t> xs256_pow;           // [64][256][8]: M^(2^b)
     std::vector<uint32_t> xs256_t4;            // [64][64][2][16][4]: 4-bit lookup tables of M^(2^b)
     std::vector<uint32_t> xs256_t4w;           // [16][15][8192]: 4-bit lookup tables of M^(d 16^j), d = 1..15
+    std::vector<uint32_t> xs256_poly;          // [8][64][8]: x^(l 2^j) mod the step's characteristic polynomial, j = 5..12
 };
 
 // 4-bit lookup table of a 256x256 GF(2) matrix given by its 256 columns of 8

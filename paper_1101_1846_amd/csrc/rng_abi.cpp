@@ -68,7 +68,8 @@ int device_tables(DevTables *out)
         const size_t o_x256 = (o_m16 + n_m16 + 255) & ~(size_t)255;
         const size_t n_x256 = H.xs256_t4.size() * sizeof(uint32_t);
         const size_t o_x256w = o_x256 + n_x256, n_x256w = H.xs256_t4w.size() * sizeof(uint32_t);
-        const size_t total = o_x256w + n_x256w;
+        const size_t o_poly = o_x256w + n_x256w, n_poly = H.xs256_poly.size() * sizeof(uint32_t);
+        const size_t total = o_poly + n_poly;
         std::string host(total, '\0');
         std::memcpy(&host[o_t392], H.t392, n_t392);
         std::memcpy(&host[o_m32], H.mwc32_pow_fold, n_m32);
@@ -77,6 +78,7 @@ int device_tables(DevTables *out)
         std::memcpy(&host[o_m16], H.mwc16_pow_fold, n_m16);
         std::memcpy(&host[o_x256], H.xs256_t4.data(), n_x256);
         std::memcpy(&host[o_x256w], H.xs256_t4w.data(), n_x256w);
+        std::memcpy(&host[o_poly], H.xs256_poly.data(), n_poly);
         void *blob = nullptr;
         if ((e = hipMalloc(&blob, total)) != hipSuccess) return hip_fail(e, "hipMalloc(tables)");
         if ((e = hipMemcpy(blob, host.data(), total, hipMemcpyHostToDevice)) != hipSuccess) {
@@ -91,6 +93,7 @@ int device_tables(DevTables *out)
         d.tab.mwc16_pow = (const uint32_t *)(b + o_m16);
         d.tab.xs256_t4 = (const uint4 *)(b + o_x256);
         d.tab.xs256_t4w = (const uint4 *)(b + o_x256w);
+        d.tab.xs256_poly = (const uint4 *)(b + o_poly);
         d.tab.mwc32_a = H.mwc32_a;
         d.tab.mwc32_m = H.mwc32_m;
         d.blob = blob;
@@ -272,18 +275,6 @@ int dispatch_seed(int g, uint64_t seed, uint64_t first, uint64_t S, uint32_t *st
     RNGX_GEN_SWITCH(g, launch_seed_t<G>(seed, first, S, st, tab, s))
 }
 
-int dispatch_tree_head(int g, const uint32_t *st0, uint32_t *ws, uint64_t T, uint64_t unit, const DevTables &tab,
-                       hipStream_t s)
-{
-    RNGX_GEN_SWITCH(g, launch_tree_head_t<G>(st0, ws, T, unit, tab, s))
-}
-
-int dispatch_tree_level(int g, uint32_t *ws, uint64_t T, uint32_t shift, uint64_t unit, const DevTables &tab,
-                        hipStream_t s)
-{
-    RNGX_GEN_SWITCH(g, launch_tree_level_t<G>(ws, T, shift, unit, tab, s))
-}
-
 int dispatch_state_copy(int g, const uint32_t *src, uint64_t ss, uint64_t si, uint32_t *dst, uint64_t ds,
                         uint64_t di, hipStream_t s)
 {
@@ -342,19 +333,24 @@ static void rot_constants(int g, uint64_t N, GenArgs &a)
 }
 
 // Streams that run as long sequences, windows of consecutive numbers across a
-// wave (seq.hip), instead of a row or chunk per lane: up to one stream per
-// wave of the device from the shortest rows that fill a window of 32-number
-// blocks on (KISS, us, rows against windows: 64 x 4096 24.3 / 13.8, 1000 x
-// 10^5 112 / 100, 100 x 1000001 232 / 98; MWC32 equal to within 1 us where the
-// call is launch-bound), and more streams if their rows start inside 128-byte
-// lines and are long enough to pay for a wave's start (KISS 10^4 x 25001
-// 643 / 324, 1500 x 100001 345 / 173; but 10^4 x 10^4 125 / 203, and with
-// whole lines 10^4 x 16384 193 / 192).
+// wave (seq.hip, seq_xs256.hip), instead of a row or chunk per lane: up to one
+// stream per wave of the device from the shortest rows that fill a window of
+// 32-number blocks on (us, rows against windows: KISS 64 x 4096 24.3 / 13.8,
+// 1000 x 10^5 112 / 100, 100 x 1000001 232 / 98; MWC32 equal to within 1 us
+// where the call is launch-bound; XS256 64 x 4096 144 / 13, 1000 x 10^5 322 /
+// 131), and more streams if their rows start inside 128-byte lines and are
+// long enough to pay for a wave's start (KISS 10^4 x 25001 643 / 324, 1500 x
+// 100001 345 / 173; but 10^4 x 10^4 125 / 203, and with whole lines 10^4 x
+// 16384 193 / 192).  XS256, whose chunks start by a chain of table products
+// per lane, takes four streams per wave, and shorter rows (4096 x 4096 152 /
+// 71, 4096 x 10^4 188 / 106; but 4096 x 65536 235 / 266, 10^4 x 10^4 222 /
+// 255, 20000 x 10001 421 / 518).
 static bool seq_streams(int g, uint64_t S, uint64_t N, const void *out)
 {
-    if (!seq_gen(g)) return false;
-    if (S <= kSeqWaves) return N >= 2048;
-    return N >= 16384 && S <= ((uint64_t)1 << 24) && (N % 32 != 0 || ((uintptr_t)out & 127));
+    const bool lines = N % 32 == 0 && !((uintptr_t)out & 127);
+    if (S <= kSeqWaves) return N >= (g == RNG_XS256 ? 512 : 2048);
+    if (g == RNG_XS256 && S <= 4 * kSeqWaves && N >= 2048 && N < 16384) return true;
+    return N >= 16384 && S <= ((uint64_t)1 << 24) && !lines;
 }
 
 // Shared by rng_generate and the split path: one generate launch over
@@ -433,9 +429,9 @@ int check_sizes(uint64_t S, uint64_t N, uint64_t words)
     return RNG_OK;
 }
 
-// Sequence splitting after the argument checks of the entry points: thread
-// states in ws ([W][T] words, ws_bytes available), a radix-16 tree of jumps,
-// then the generation launch(es) and the final state.  Launches only.
+// Sequence splitting after the argument checks of the entry points: the
+// workspace (ws_bytes available) holds a copy of the start state if the final
+// state overlaps it.  Launches only.
 int split_args_check(uint64_t total, uint64_t n_threads, const void *d_out, const uint32_t *d_state_one,
                      const uint32_t *d_final_state)
 {
@@ -455,36 +451,7 @@ int split_run(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_thr
     if (int rc = split_scratch_bytes(g, total, n_threads, &need)) return rc;
     if (ws_bytes < need)
         return fail(RNG_ENOMEM, "workspace %llu bytes < %llu", (unsigned long long)ws_bytes, (unsigned long long)need);
-    if (seq_gen(g)) return seq_run(g, d_state_one, total, t, d_out, d_final_state, ws, tab, st);
-    // radix-16 tree: level l starts threads [16^l, 16^(l+1)) from threads below 16^l;
-    // the start state's copy and levels 0 .. 2 in one launch
-    uint64_t far;
-    if (mul_overflows(C, T, &far)) return fail(RNG_ERANGE, "jump distance overflows");
-    int rc = check_launch(dispatch_tree_head(g, d_state_one, ws, T, C, tab, st), "split: tree head");
-    if (rc) return rc;
-    for (uint32_t shift = kTreeHeadShift; ((uint64_t)1 << shift) < T; shift += 4) {
-        rc = check_launch(dispatch_tree_level(g, ws, T, shift, C, tab, st), "split: tree level");
-        if (rc) return rc;
-    }
-    const uint64_t rem = total - (T - 1) * C;  // samples of the last thread
-    const uint64_t full = rem == C ? T : T - 1;
-    Shape shape = row_shape(g, t, full / 64 * 64, C);
-    // whole 64-thread groups in one launch (the resident schedule needs them),
-    // the rest of the full threads in a second
-    const uint64_t full64 = full / 64 * 64;
-    if (full64) {
-        rc = generate_impl(g, t, ws, T, full64, C, d_out, shape, true, st);
-        if (rc) return rc;
-    }
-    if (full > full64) {
-        rc = generate_impl(g, t, ws + full64, T, full - full64, C, (uint32_t *)d_out + full64 * C, shape, true, st);
-        if (rc) return rc;
-    }
-    if (full < T) {
-        rc = generate_impl(g, t, ws + (T - 1), T, 1, rem, (uint32_t *)d_out + (T - 1) * C, shape, true, st);
-        if (rc) return rc;
-    }
-    return check_launch(dispatch_state_copy(g, ws, T, T - 1, d_final_state, 1, 0, st), "split: final");
+    return seq_run(g, d_state_one, total, t, d_out, d_final_state, ws, tab, st);
 }
 
 // Workspace bytes a split of `total` samples over n_threads threads uses:

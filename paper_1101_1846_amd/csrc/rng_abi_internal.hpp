@@ -33,18 +33,6 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
                   Shape shape, bool staged, hipStream_t st);
 int dispatch_generate(int g, int dt, const GenArgs &a, int wg, int unroll, bool staged, hipStream_t st);
 int dispatch_skip(int g, uint32_t *st, uint64_t ld, uint64_t S, uint64_t k, const DevTables &tab, hipStream_t s);
-// One radix-16 level of a thread-start tree: threads [2^shift, min(2^(shift+4), T))
-// of ws ([W][T]) from the threads below 2^shift, unit samples per thread index.
-int dispatch_tree_level(int g, uint32_t *ws, uint64_t T, uint32_t shift, uint64_t unit, const DevTables &tab,
-                        hipStream_t s);
-// Thread starts 0 .. min(T, 4096) - 1 of a split or leapfrogged sequence
-// from one state (k_tree_head); the further tree levels start at shift 12.
-template <class G>
-int launch_tree_head_t(const uint32_t *st0, uint32_t *ws, uint64_t T, uint64_t unit, const DevTables &tab,
-                       hipStream_t stream);
-int dispatch_tree_head(int g, const uint32_t *st0, uint32_t *ws, uint64_t T, uint64_t unit, const DevTables &tab,
-                       hipStream_t s);
-constexpr uint32_t kTreeHeadShift = 12;
 int dispatch_state_copy(int g, const uint32_t *src, uint64_t ss, uint64_t si, uint32_t *dst, uint64_t ds,
                         uint64_t di, hipStream_t s);
 
@@ -53,15 +41,16 @@ int dispatch_state_copy(int g, const uint32_t *src, uint64_t ss, uint64_t si, ui
 int generate_few(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint64_t N, uint64_t C, uint64_t P,
                  void *d_out, const DevTables &tab, hipStream_t st);
 
-// Long sequences of few streams without tables of start states (seq.hip; every
-// generator but XS256): S streams of N numbers from states at word stride ld
-// into out [S][N].  With S = 1 the state after the last number goes to
+// Long sequences of few streams without start states in memory (seq.hip, and
+// seq_xs256.hip for XS256): S streams of N numbers from states at word stride
+// ld into out [S][N].  With S = 1 the state after the last number goes to
 // final_state if that is not null (it must not overlap the start state); the
 // start states are not written.
 constexpr uint64_t kSeqWaves = 1024;  // 4 per CU
-inline bool seq_gen(int g) { return g != RNG_XS256; }
 int launch_seq(int g, int dt, const uint32_t *state, uint64_t ld, uint64_t S, uint64_t N, void *out,
                uint32_t *final_state, const DevTables &tab, hipStream_t st);
+int launch_seq_xs256(int dt, const uint32_t *state, uint64_t ld, uint64_t S, uint64_t N, void *out,
+                     uint32_t *final_state, const DevTables &tab, hipStream_t st);
 // One sequence of `total` numbers through launch_seq; a final state that
 // overlaps the start state goes by a copy of it in ws (one state).
 int seq_run(int g, const uint32_t *state_one, uint64_t total, int t, void *out, uint32_t *final_state, uint32_t *ws,

@@ -83,9 +83,6 @@ template <class G>
 int launch_seed_t(uint64_t seed, uint64_t first, uint64_t S, uint32_t *st, const DevTables &tab,
                   hipStream_t stream);
 template <class G>
-int launch_tree_level_t(uint32_t *ws, uint64_t T, uint32_t shift, uint64_t unit, const DevTables &tab,
-                        hipStream_t stream);
-template <class G>
 int launch_state_copy_t(const uint32_t *src, uint64_t ss, uint64_t si, uint32_t *dst, uint64_t ds,
                         uint64_t di, hipStream_t stream);
 template <class G>

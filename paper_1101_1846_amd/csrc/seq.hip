@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64) void k_seq(SeqArgs a)
     const uint64_t body = a.N - head, nwin = (body + 64 * K - 1) / (64 * K);
     if (p >= nwin && p) return;
     G g;
-    g.load(a.state, a.ld, s, a.tab);
+    load_uniform(g, a.state, a.ld, s);
     for (uint32_t k = 0; k < head; ++k) {
         const uint32_t u = seq_bits<DT>(g.next());
         if (p == 0 && lane == 0) out[k] = u;
@@ -347,6 +347,7 @@ int launch_seq(int g, int dt, const uint32_t *state, uint64_t ld, uint64_t S, ui
     seq_shape(S, N, &k, &a.wp);
     switch (g) {
     case RNG_MWC32: return launch_seq_t<GenMWC32>(dt, a, k, st);
+    case RNG_XS256: return launch_seq_xs256(dt, state, ld, S, N, out, final_state, tab, st);
     case RNG_XS32: return launch_seq_t<GenXS32>(dt, a, k, st);
     case RNG_KISS: return launch_seq_t<GenKISS>(dt, a, k, st);
     case RNG_MWC1616: return launch_seq_t<GenMWC1616>(dt, a, k, st);

@@ -22,6 +22,7 @@
 #include "host_math.hpp"
 #include "rng.h"
 #include "rng_abi_internal.hpp"
+#include "xs256_jump.hpp"
 
 namespace rngx {
 
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(64) void k_skip_wave(SkipArgs a)
     constexpr bool kXs32 = G::kId == G_XS32 || G::kId == G_KISS;
     const int lane = threadIdx.x;
     G g;
-    g.load(a.st, a.ld, blockIdx.x, a.tab);
+    load_uniform(g, a.st, a.ld, blockIdx.x);
     const int nb = 64 - __builtin_clzll(a.k);  // k > 0
     uint32_t y = 0;
     if constexpr (G::kId == G_XS32) y = g.y;
@@ -219,6 +220,7 @@ __global__ __launch_bounds__(64) void k_skip_wave(SkipArgs a)
                 if ((a.k >> (b0 + i)) & 1) y = xor_over_32(col[i] & (0u - ((y >> (lane & 31)) & 1u)));
         }
     }
+    if constexpr (G::kId == G_XS256) xs256_wave_jump(g.v, a.k, lane, a.tab);
     if constexpr (G::kId == G_XS32) g.y = y;
     if constexpr (kMwc16) {
         const uint32_t ai = lane < 32 ? g.a1 : g.a2, m = ai * 65536u - 1u;
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(64) void k_skip_wave(SkipArgs a)
 template <class G>
 int launch_skip_by(const SkipArgs &a, hipStream_t stream)
 {
-    if constexpr (G::kId == G_XS32 || G::kId == G_KISS || G::kId == G_MWC1616) {
+    if constexpr (G::kId != G_MWC32) {
         if (a.S <= kSkipWaveMax) {
             hipLaunchKernelGGL(k_skip_wave<G>, dim3((unsigned)a.S), dim3(64), 0, stream, a);
             return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -1,9 +1,9 @@
 // split_noalloc.hip -- sequence splitting (Sec. II.A.4) for callers that cannot
-// allocate: the per-thread start states live in a file-scope device array
-// instead of a caller workspace, so the entry point makes no hipMalloc,
-// hipFree or other allocating call.  Each device that loads the library holds
-// its own copy of the array until the process ends; its address on a device
-// is looked up once, by rng_init() with that device current.
+// allocate: a start state that the final one overlaps is copied to a
+// file-scope device array instead of a caller workspace, so the entry point
+// makes no hipMalloc, hipFree or other allocating call.  Each device that loads
+// the library holds its own copy of the array until the process ends; its
+// address on a device is looked up once, by rng_init() with that device current.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -17,12 +17,10 @@ namespace rngx {
 namespace {
 
 constexpr uint64_t kScratchBytes = RNG_SPLIT_NOALLOC_SCRATCH_BYTES;
-static_assert(kScratchBytes % 256 == 0, "scratch size");
 
-// Thread start states of rng_generate_split_noalloc ([W][T] words).  In host
-// code this name is a stand-in, not a device address: kernels get the
-// address from hipGetSymbolAddress (g_scratch below).
-static __device__ __align__(256) uint32_t scratch[kScratchBytes / 4];
+// Copy of a start state.  In host code this name is a stand-in, not a device
+// address: kernels get the address from hipGetSymbolAddress (g_scratch below).
+static __device__ __align__(256) uint32_t scratch[64];
 
 std::mutex g_mu;
 void *g_scratch[kMaxDevices];  // the array's address on each device, once looked up
