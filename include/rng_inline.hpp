@@ -43,15 +43,22 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 }
 
 // One base-2^16 MWC word z = c * 2^16 + x: z <- a * (z & 0xFFFF) + (z >> 16)
-// (eq. (2)-(3) with the mask and shift of Sec. II.A.1).  v_mad_u32_u16 reads
-// only the low 16 bits of both factors, so the mask costs no instruction: a
-// shift and one multiply-add per word (for the same expression in C the
-// compiler emits an AND and a 24-bit multiply-add).
+// (eq. (2)-(3) with the mask and shift of Sec. II.A.1), as one two-element dot
+// product of z's halves with (a, 1).  The factor pair is loop-invariant.
 __device__ __forceinline__ uint32_t mwc16_step(uint32_t z, uint32_t a)
 {
-    uint32_t r;
-    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(z), "v"(z >> 16));
-    return r;
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, z), __builtin_bit_cast(u16x2, (a & 0xFFFFu) | 0x10000u), 0u,
+                                  false);
+}
+
+// The low word of a x + c as one v_mad_u64_u32, which takes as long as a
+// v_mul_lo_u32 alone.
+__device__ __forceinline__ uint32_t mad_lo(uint32_t a, uint32_t x, uint32_t c)
+{
+    uint64_t r, carry;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(x), "v"(a), "s"((uint64_t)c));
+    return (uint32_t)r;
 }
 }  // namespace detail
 
@@ -197,7 +204,7 @@ struct KISS {
     {
         z = detail::mwc16_step(z, a1);
         w = detail::mwc16_step(w, a2);
-        jcong = 69069u * jcong + 1234567u;
+        jcong = detail::mad_lo(69069u, jcong, 1234567u);
         jsr ^= jsr << 13;
         jsr ^= jsr >> 17;
         jsr ^= jsr << 5;

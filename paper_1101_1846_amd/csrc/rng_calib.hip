@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void k_valu_fused(uint32_t *out, uint32_t iter
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const uint32_t x = g[s].next() >> 8, y = g[s].next() >> 8;
-                cnt += in_quarter_circle(x, y);
+                cnt += outside_quarter_circle<true>(x, y);
             }
         }
     }
