@@ -293,35 +293,35 @@ typedef struct {
 typedef struct rng_batch rng_batch_t;
 
 /* A batch handle for up to max_requests requests of at most max_samples
- * samples in total; it owns its device workspace (chunk states, plan) and
- * pinned staging buffers, and its graphs.  Created on the current device. */
+ * samples in total; it owns its device workspace (start states, tile map,
+ * plan) and pinned staging buffers, and its graphs.  Created on the current device. */
 int rng_batch_create(uint32_t max_requests, uint64_t max_samples, rng_batch_t **h);
 /* Plan a batch from a host table of n requests (copied; the caller may reuse
  * its table).  No two requests may share a stream state (the same d_state
  * twice is RNG_EINVAL; overlapping strided states are not detected).  Blocks
  * until the previous launch's plan upload has left the staging buffers. */
 int rng_batch_set(rng_batch_t *h, const rng_request_t *h_reqs, uint32_t n);
-/* Queue the planned batch on stream: one plan upload, then the root jumps
- * (with tree level 0), the further tree levels and the persistent
- * generation kernel. */
+/* Queue the planned batch on stream: the plan (in the first kernel's
+ * arguments if it is small, else one upload), a kernel that copies the start
+ * states, and the persistent generation kernel, whose waves start their lanes
+ * from a request's state by jump-ahead. */
 int rng_batch_launch(rng_batch_t *h, void *stream);
 /* use_graph = 1: rng_batch_launch replays a HIP graph of those kernels,
- * captured once per (tree depth, shape) on the handle's own stream;
- * 0 (the default): it launches them directly.  Both give the same results.
- * On MI355X with ROCm 7 a graph replay of 2-6 kernels costs about 21 us of
+ * captured once per shape on the handle's own stream; 0 (the default): it
+ * launches them directly.  Both give the same results.  On MI355X with ROCm 7 a
+ * graph replay of a few kernels costs about 21 us of
  * host time against 2.6 us per direct launch, so the direct launches give
  * the lower latency. */
 int rng_batch_set_graph(rng_batch_t *h, int use_graph);
 /* Persistent-kernel shape: wg lanes per workgroup in {64, 128, 256, 512,
  * 1024} and unroll (samples per generation step) in {1, 2, 4, 8, 16}, every
  * pair built (others RNG_EINVAL; 1024-lane workgroups stage 32-sample LDS
- * tiles, the others 64); and chunk length C (a multiple of 64).  0 keeps the current value.  chunk = RNG_BATCH_CHUNK_AUTO lets every plan
- * choose C: the power of two in [64, 4096] that cuts the batch into about
- * 2^17 chunks (as many 64-chunk tiles as the device holds waves), so that
- * small batches still spread over the device; the workspace is sized for
- * 256-sample chunks (more for handles of more than 2^36 samples), and a plan
- * goes below that only while its chunks fit.  A changed C applies to the
- * last planned table at once (it is planned again). */
+ * tiles, the others 64); and chunk length C (a multiple of 64).  0 keeps the
+ * current value.  A lane produces consecutive samples of one request, at most
+ * the power of two below C or 4096; a plan takes fewer where the batch is too
+ * small to fill the device with rows that long.  chunk = RNG_BATCH_CHUNK_AUTO
+ * allows 4096.  A changed C applies to the last planned table at once (it is
+ * planned again). */
 #define RNG_BATCH_CHUNK_AUTO 0xFFFFFFFFu
 int rng_batch_set_shape(rng_batch_t *h, uint32_t wg, uint32_t unroll, uint32_t chunk);
 /* The current shape; chunk reads RNG_BATCH_CHUNK_AUTO in automatic mode. */

@@ -445,8 +445,6 @@ int split_args_check(uint64_t total, uint64_t n_threads, const void *d_out, cons
 int split_run(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads, int t, void *d_out,
               uint32_t *d_final_state, uint32_t *ws, uint64_t ws_bytes, const DevTables &tab, hipStream_t st)
 {
-    const uint64_t C = (total + n_threads - 1) / n_threads;
-    const uint64_t T = (total + C - 1) / C;  // threads with work
     uint64_t need;
     if (int rc = split_scratch_bytes(g, total, n_threads, &need)) return rc;
     if (ws_bytes < need)

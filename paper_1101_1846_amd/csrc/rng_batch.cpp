@@ -1,8 +1,8 @@
 // rng_batch.cpp -- the batched path of the C ABI: plans a batch of
-// independent requests (chunking, grouping by generator and dtype, the
-// radix-16 tree work lists), ships the plan through pinned host memory, and
-// replays one captured HIP graph per batch shape: root jumps (which also
-// reset the tile counter), tree levels, persistent generation kernel.
+// independent requests (row lengths, grouping by generator and dtype), ships
+// the plan through pinned host memory or in the first kernel's arguments, and
+// launches two kernels, directly or as one captured HIP graph per shape: root
+// (start states, tile map, tile counter) and persistent generation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -15,9 +15,7 @@
 #include "rng_batch_internal.hpp"
 
 namespace rngx {
-int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t max_requests, hipStream_t s);
-int launch_batch_level(const BatchArgs &a, uint32_t level, unsigned grid, hipStream_t s);
-int launch_batch_tree_small(const BatchArgs &a, const PlanInline &pin, uint32_t n, hipStream_t s);
+int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t requests, hipStream_t s);
 int launch_batch_gen(const BatchArgs &a, int wg, int unroll, unsigned grid, hipStream_t s);
 int batch_gen_occupancy(int wg, int unroll, int *blocks_per_cu);
 }  // namespace rngx
@@ -32,16 +30,15 @@ struct rng_batch {
     uint64_t C = 1024;
     bool chunk_auto = false;  // C chosen per plan (RNG_BATCH_CHUNK_AUTO)
     uint32_t wg = 256, unroll = 8;
-    uint64_t ws_words = 0;
+    uint64_t map_cap = 0;  // tiles the map holds
     char *d_plan = nullptr, *h_plan = nullptr;  // packed plan (BatchHeader first), device and pinned staging
-    uint64_t plan_cap = 0;                      // bytes of each
     uint32_t *d_ws = nullptr, *d_counter = nullptr, *d_map = nullptr;
     hipEvent_t copied = nullptr;
     hipStream_t capture = nullptr;  // private stream the graphs are recorded on
     bool copy_pending = false;
     bool planned = false;
     struct Graph {
-        uint32_t levels, wg, unroll;
+        uint32_t wg, unroll;
         hipGraph_t graph;
         hipGraphExec_t exec;
     };
@@ -54,81 +51,84 @@ struct rng_batch {
     BatchHeader &hdr() { return *(BatchHeader *)h_plan; }
 };
 
-// Automatic chunk length: a power of two in [64, 4096] that cuts the batch
-// into about 2^17 chunks (2048 tiles of 64: the waves the device holds at
-// once), so that a small batch still spreads over the device.  The workspace
-// is sized for chunks of auto_chunk_min (256, more for huge handles); shorter
-// chunks are taken only while the plan's chunks fit it.
-constexpr uint64_t kAutoChunkMax = 4096;
-constexpr uint64_t kAutoChunkFloor = kBatchTile;
-constexpr uint64_t kSmallBatch = (uint64_t)1 << 19;  // samples
-constexpr uint64_t kAutoChunks = (uint64_t)1 << 17;
-static uint64_t auto_chunk_min(uint64_t max_samples)
+// Rows are at most as long as the chunk length allows, the power of two at most
+// C (in automatic mode 4096); a request of up to 64 rows takes the shortest that
+// fit it in one tile.
+static uint64_t longest_row(const rng_batch *h)
 {
-    uint64_t c = 256;  // keeps the chunk capacity below 2^28
-    while (c < kAutoChunkMax && max_samples / c > ((uint64_t)1 << 28)) c *= 2;
+    uint64_t c = (uint64_t)1 << kBatchLgMax;
+    while (!h->chunk_auto && c > h->C) c /= 2;
     return c;
 }
 
-static uint64_t chunk_capacity(const rng_batch *h, uint64_t C)
+// log2 of the row length of a batch of n requests, `total` samples, by what it
+// costs, in ns: a tile's start 16000, a sample of each row 94 with all waves
+// writing (5.6 TB/s over 2048), 70 in the last tiles, which run out alone.
+// (16 requests, 10^6 samples: rows of 32, 19 us against 70 with rows of 1024;
+// 100, 10^7: 36 with 128, 80 with 32; 890, 8.4 10^7: 108 with 512, 132 with
+// 1024, 162 with 128; from about 3 10^8 samples on the longest.)
+static uint32_t row_bits(uint64_t n, uint64_t total, uint32_t longest)
 {
-    return (h->max_samples + C - 1) / C + h->max_requests + (uint64_t)kBatchMaxGroups * 64;
+    uint32_t best = longest;
+    double least = 1e300;
+    for (uint32_t lg = longest; lg >= (uint32_t)kBatchLgMin; --lg) {
+        const double tiles = (double)n + (double)(total >> (lg + 6));
+        const double t = (tiles * 16000 + (double)(total >> 6) * 94) / 2048 + 16000 + 70.0 * (double)(1u << lg);
+        if (t < least) {
+            least = t;
+            best = lg;
+        }
+    }
+    return best;
 }
 
-// Segments of all levels: at most one per request and level.
-static uint64_t seg_capacity(const rng_batch *h) { return (uint64_t)kBatchMaxLevels * h->max_requests; }
-
-// Block starts of all levels: the levels' work items sum to fewer than the
-// chunks, so sum(ceil(items / kLevelWG)) <= chunks / kLevelWG + levels.
-static uint64_t blk_capacity(const rng_batch *h, uint64_t C)
+// Tiles of any plan: rows below the longest are chosen only while they make
+// fewer than 18 tiles per sample of a row, 18 2^11, beside one per request.
+static uint64_t tile_capacity(const rng_batch *h)
 {
-    return chunk_capacity(h, C) / kLevelWG + kBatchMaxLevels + 1;
+    const uint64_t per = 64 * longest_row(h);
+    return std::max((h->max_samples + per - 1) / per, (uint64_t)1 << 16) + h->max_requests;
 }
 
 static uint64_t align16(uint64_t x) { return (x + 15) & ~(uint64_t)15; }
 
-// Packed plan: header, requests, segments, block starts (16-byte aligned each).
-static uint64_t plan_capacity(const rng_batch *h, uint64_t C)
+// Packed plan: header, requests (16-byte aligned each).
+static uint64_t plan_capacity(const rng_batch *h)
 {
-    return align16(sizeof(BatchHeader)) + align16(sizeof(BatchReq) * (uint64_t)h->max_requests) +
-           align16(8 * seg_capacity(h)) + 4 * blk_capacity(h, C);
+    return align16(sizeof(BatchHeader)) + align16(sizeof(BatchReq) * (uint64_t)h->max_requests);
 }
 
-// Sizes the chunk workspace, the chunk-to-request map and the level work
-// lists for chunk length C.  Growing any of them drops the captured graphs,
-// which hold the old addresses.
-static int alloc_ws(rng_batch *h, uint64_t C)
+// Sizes the tile map, and at first the plan and the start states.  Growing the
+// map drops the captured graphs, which hold the old address.
+static int alloc_ws(rng_batch *h)
 {
-    const uint64_t chunks = chunk_capacity(h, C);
-    const uint64_t words = chunks * 8;  // widest state: 8 words
-    const uint64_t plan_bytes = plan_capacity(h, C);
-    if (words <= h->ws_words && plan_bytes <= h->plan_cap) return RNG_OK;
+    const uint64_t tiles = tile_capacity(h), plan_bytes = plan_capacity(h);
     if (plan_bytes >= ((uint64_t)1 << 32)) return fail(RNG_ENOMEM, "batch plan above 4 GiB");
-    if (chunks >= ((uint64_t)1 << 32)) return fail(RNG_ENOMEM, "more than 2^32 chunks of %llu samples",
-                                                   (unsigned long long)C);
+    if (tiles >= ((uint64_t)1 << 32) || (!h->chunk_auto && h->max_samples / h->C >= ((uint64_t)1 << 32)))
+        return fail(RNG_ENOMEM, "more than 2^32 chunks of %llu samples", (unsigned long long)h->C);
+    if (tiles <= h->map_cap) return RNG_OK;
     for (auto &g : h->graphs) {
         (void)hipGraphExecDestroy(g.exec);
         (void)hipGraphDestroy(g.graph);
     }
     h->graphs.clear();
     (void)hipDeviceSynchronize();  // no launch may still use the old buffers
-    if (h->d_ws) (void)hipFree(h->d_ws);
     if (h->d_map) (void)hipFree(h->d_map);
-    if (h->d_plan) (void)hipFree(h->d_plan);
-    if (h->h_plan) (void)hipHostFree(h->h_plan);
-    h->d_ws = h->d_map = nullptr;
-    h->d_plan = h->h_plan = nullptr;
-    h->ws_words = h->plan_cap = 0;
-    h->planned = false;  // the plan lived in the old staging buffer
+    h->d_map = nullptr;
+    h->map_cap = 0;
+    h->planned = false;
     hipError_t e;
-    if ((e = hipMalloc((void **)&h->d_ws, words * 4)) != hipSuccess) return hip_fail(e, "hipMalloc(batch workspace)");
-    if ((e = hipMalloc((void **)&h->d_map, chunks * 4)) != hipSuccess) return hip_fail(e, "hipMalloc(chunk map)");
-    if ((e = hipMalloc((void **)&h->d_plan, plan_bytes)) != hipSuccess) return hip_fail(e, "hipMalloc(batch plan)");
-    if ((e = hipHostMalloc((void **)&h->h_plan, plan_bytes, hipHostMallocDefault)) != hipSuccess)
-        return hip_fail(e, "hipHostMalloc(batch plan)");
-    std::memset(h->h_plan, 0, sizeof(BatchHeader));
-    h->ws_words = words;
-    h->plan_cap = plan_bytes;
+    if (!h->d_ws && (e = hipMalloc((void **)&h->d_ws, (uint64_t)h->max_requests * 32)) != hipSuccess)
+        return hip_fail(e, "hipMalloc(batch states)");
+    if (!h->d_plan && (e = hipMalloc((void **)&h->d_plan, plan_bytes)) != hipSuccess)
+        return hip_fail(e, "hipMalloc(batch plan)");
+    if (!h->h_plan) {
+        if ((e = hipHostMalloc((void **)&h->h_plan, plan_bytes, hipHostMallocDefault)) != hipSuccess)
+            return hip_fail(e, "hipHostMalloc(batch plan)");
+        std::memset(h->h_plan, 0, sizeof(BatchHeader));
+    }
+    if ((e = hipMalloc((void **)&h->d_map, tiles * 4)) != hipSuccess) return hip_fail(e, "hipMalloc(tile map)");
+    h->map_cap = tiles;
     return RNG_OK;
 }
 
@@ -158,7 +158,7 @@ static BatchArgs make_args(rng_batch *h, const DevTables &tab)
 {
     BatchArgs a{};
     a.hdr = (const BatchHeader *)h->d_plan;
-    a.chunk_req = h->d_map;
+    a.tile_req = h->d_map;
     a.ws = h->d_ws;
     a.counter = h->d_counter;
     a.tab = tab;
@@ -188,7 +188,7 @@ int rng_batch_create(uint32_t max_requests, uint64_t max_samples, rng_batch_t **
         (e = hipEventCreateWithFlags(&h->copied, hipEventDisableTiming)) != hipSuccess ||
         (e = hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking)) != hipSuccess)
         rc = hip_fail(e, "rng_batch_create");
-    if (!rc) rc = alloc_ws(h, h->C);
+    if (!rc) rc = alloc_ws(h);
     if (rc) {
         free_batch(h);
         return rc;
@@ -219,10 +219,15 @@ int rng_batch_set_shape(rng_batch_t *h, uint32_t wg, uint32_t unroll, uint32_t c
         if (!autoc && chunk % kBatchTile)
             return fail(RNG_EINVAL, "chunk %u is not a multiple of %d", chunk, kBatchTile);
         if (h->copy_pending) (void)hipEventSynchronize(h->copied);
-        const uint64_t cmin = autoc ? auto_chunk_min(h->max_samples) : chunk;
-        if (int rc = alloc_ws(h, cmin)) return rc;
+        const uint64_t old_c = h->C;
+        const bool old_auto = h->chunk_auto;
         h->chunk_auto = autoc;
-        h->C = autoc ? cmin : chunk;
+        if (!autoc) h->C = chunk;
+        if (int rc = alloc_ws(h)) {
+            h->C = old_c;
+            h->chunk_auto = old_auto;
+            return rc;
+        }
         h->planned = false;  // the plan depends on the chunk length
         if (!h->last.empty()) {
             std::vector<rng_request_t> t = h->last;
@@ -259,12 +264,19 @@ int rng_batch_set(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     if (n && !reqs) return fail(RNG_EINVAL, "NULL request table");
     if (n > h->max_requests) return fail(RNG_ENOMEM, "%u requests > capacity %u", n, h->max_requests);
     if (n > 1) {
-        // two requests on one state would race on its write-back
-        std::vector<uintptr_t> p(n);
-        for (uint32_t i = 0; i < n; ++i) p[i] = (uintptr_t)reqs[i].d_state;
-        std::sort(p.begin(), p.end());
-        if (std::adjacent_find(p.begin(), p.end()) != p.end())
-            return fail(RNG_EINVAL, "two requests share one d_state");
+        // two requests on one state would race on its write-back: an open
+        // hash table of at least twice the pointers (null ones fail the plan)
+        uint32_t bits = 4;
+        while (((uint64_t)1 << bits) < 2 * (uint64_t)n) ++bits;
+        std::vector<uintptr_t> seen((uint64_t)1 << bits, 0);
+        const uint64_t mask = seen.size() - 1;
+        for (uint32_t i = 0; i < n; ++i) {
+            const uintptr_t p = (uintptr_t)reqs[i].d_state;
+            uint64_t at = (p * 0x9E3779B97F4A7C15ull) >> (64 - bits);
+            while (seen[at] && seen[at] != p) at = (at + 1) & mask;
+            if (p && seen[at] == p) return fail(RNG_EINVAL, "two requests share one d_state");
+            seen[at] = p;
+        }
     }
     return batch_set_distinct(h, reqs, n);
 }
@@ -302,17 +314,6 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     if (total_samples > h->max_samples)
         return fail(RNG_ENOMEM, "batch of %llu samples > capacity %llu", (unsigned long long)total_samples,
                     (unsigned long long)h->max_samples);
-    if (h->chunk_auto) {
-        // The workspace holds max_samples in chunks of auto_chunk_min.  A
-        // small batch (its time is the serial work per lane) takes shorter
-        // chunks, down to one 64-sample tile, while they fit; larger ones keep
-        // the longer minimum, since more chunks mean more tree work.
-        const uint64_t cmin = auto_chunk_min(h->max_samples), fit = (h->max_samples + cmin - 1) / cmin;
-        uint64_t c = total_samples <= kSmallBatch ? kAutoChunkFloor : cmin;
-        while (c < kAutoChunkMax && (total_samples / (2 * c) >= kAutoChunks || (total_samples + c - 1) / c > fit))
-            c *= 2;
-        h->C = c;
-    }
     // The pinned staging buffers are about to be rewritten: wait for the
     // previous launch's copies to leave them.
     if (h->copy_pending) {
@@ -320,104 +321,48 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
         h->copy_pending = false;
     }
-    // group requests by (generator, dtype), stable
-    std::vector<uint32_t> order(n);
-    for (uint32_t i = 0; i < n; ++i) order[i] = i;
-    auto key = [&](uint32_t i) { return reqs[i].gen * 2 + reqs[i].dtype; };
-    std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return key(x) < key(y); });
-    const uint64_t C = h->C;
-
     h->planned = false;  // until this plan is complete: a failure below leaves nothing to launch
+    const uint32_t cap = row_bits(n, total_samples, (uint32_t)__builtin_ctzll(longest_row(h)));
+    auto tile_bits = [cap](uint64_t length) {
+        uint32_t lg = kBatchLgMin;
+        while (lg < cap && ((uint64_t)64 << lg) < length) ++lg;
+        return lg;
+    };
+    auto tiles_of = [](uint64_t length, uint32_t lg) { return (length + ((uint64_t)64 << lg) - 1) >> (lg + 6); };
+    uint64_t tiles = 0;
+    for (uint32_t i = 0; i < n; ++i) tiles += tiles_of(reqs[i].length, tile_bits(reqs[i].length));
+    if (tiles > h->map_cap)
+        return fail(RNG_ENOMEM, "batch needs %llu tiles > %llu", (unsigned long long)tiles, (unsigned long long)h->map_cap);
+    // requests by (generator, dtype), in table order within each
     BatchHeader &H = h->hdr();
     std::memset(&H, 0, sizeof(H));
-    H.C = C;
     H.n = n;
     H.off_reqs = (uint32_t)align16(sizeof(BatchHeader));
     BatchReq *Q = plan_at<BatchReq>(&H, H.off_reqs);
-    uint64_t ws_off = 0, tiles = 0, max_chunks = 0;
-    uint32_t i = 0;
-    while (i < n) {
-        const int k = key(order[i]);
-        BatchGroup &G = H.groups[H.ngroups];
-        G.gen = (uint32_t)reqs[order[i]].gen;
-        G.dtype = (uint32_t)reqs[order[i]].dtype;
-        G.words = (uint32_t)gen_words(reqs[order[i]].gen);
-        G.req_begin = i;
-        uint64_t chunks = 0;
-        for (; i < n && key(order[i]) == k; ++i) {
-            const rng_request_t &r = reqs[order[i]];
-            BatchReq &q = Q[i];
-            q.state = r.d_state;
-            q.stride = r.state_stride;
-            q.offset = r.offset;
-            q.length = r.length;
-            q.out = (uint32_t *)r.d_out;
-            q.chunk_base = (uint32_t)chunks;
-            q.nchunks = (uint32_t)((r.length + C - 1) / C);
-            q.group = H.ngroups;
-            q.pad = 0;
-            chunks += q.nchunks;
-            max_chunks = std::max<uint64_t>(max_chunks, q.nchunks);
-        }
-        G.req_end = i;
-        G.nchunks = (uint32_t)chunks;
-        G.nchunks_pad = (uint32_t)((chunks + 63) / 64 * 64);
-        G.tile_begin = (uint32_t)tiles;
-        tiles += G.nchunks_pad / 64;
-        G.tile_end = (uint32_t)tiles;
-        G.ws_off = ws_off;
-        ws_off += (uint64_t)G.words * G.nchunks_pad;
-        H.ngroups++;
+    uint32_t count[16] = {0}, group[16] = {0}, begin[16] = {0};  // by key = 2 generator + dtype
+    auto key = [&](uint32_t i) { return (uint32_t)reqs[i].gen * 2 + (uint32_t)reqs[i].dtype; };
+    for (uint32_t i = 0; i < n; ++i) ++count[key(i)];
+    uint32_t at = 0;
+    for (uint32_t k = 0; k < 16; ++k) {
+        begin[k] = at;
+        at += count[k];
+        if (!count[k]) continue;
+        group[k] = H.ngroups;
+        H.groups[H.ngroups++] = BatchGroup{k / 2, k % 2};
     }
-    if (ws_off > h->ws_words) return fail(RNG_ENOMEM, "batch needs %llu workspace words > %llu",
-                                          (unsigned long long)ws_off, (unsigned long long)h->ws_words);
-    H.n_tiles = (uint32_t)tiles;
-    // radix-16 levels: 16^levels >= the largest request's chunk count
-    uint32_t levels = 0;
-    while (((uint64_t)1 << (kRadixBits * levels)) < max_chunks) ++levels;
-    if (levels > (uint32_t)kBatchMaxLevels) return fail(RNG_ERANGE, "a request needs more than 2^40 chunks");
-    H.levels = levels;
-    for (uint32_t g = 0; g < H.ngroups; ++g) H.has_xs256 |= H.groups[g].gen == (uint32_t)RNG_XS256;
-    H.off_seg = (uint32_t)align16(H.off_reqs + sizeof(BatchReq) * (uint64_t)n);
-    uint2 *segs = plan_at<uint2>(&H, H.off_seg);
-    const bool pow2 = (C & (C - 1)) == 0;
-    const uint32_t lc = (uint32_t)__builtin_ctzll(C);
-    uint32_t S = 0, B = 0;
-    H.lvl[0] = LevelInfo{};  // level 0 is done by the root kernel: only its table power (small-batch tree)
-    H.lvl[0].pow = pow2 && lc + kRadixBits <= 64 ? lc : 0xFFFFFFFFu;
-    for (uint32_t l = 1; l < levels; ++l) {
-        LevelInfo &L = H.lvl[l];
-        L.seg_off = S;
-        L.shift = kRadixBits * l;
-        L.pow = pow2 && lc + L.shift + kRadixBits <= 64 ? lc + L.shift : 0xFFFFFFFFu;
-        L.pad = 0;
-        const uint64_t lo = (uint64_t)1 << L.shift, hi = lo << kRadixBits;
-        uint64_t acc = 0;
-        for (uint32_t r = 0; r < n; ++r) {
-            const uint64_t nc = Q[r].nchunks;
-            if (nc <= lo) continue;
-            segs[S++] = make_uint2(r, (uint32_t)acc);
-            acc += std::min(nc, hi) - lo;
-        }
-        L.seg_n = S - L.seg_off;
-        H.level_total[l] = (uint32_t)acc;
+    for (uint32_t i = 0; i < n; ++i) {
+        const rng_request_t &r = reqs[i];
+        const uint32_t k = key(i), lg = tile_bits(r.length);
+        Q[begin[k]++] = BatchReq{r.d_state, r.state_stride, r.offset, r.length, (uint32_t *)r.d_out,
+                                 0, (uint32_t)tiles_of(r.length, lg), group[k], lg};
     }
-    // block starts after all segments: the segment of each level's block's first item
-    H.off_blk = (uint32_t)align16(H.off_seg + 8ull * S);
-    uint64_t nblk = 0;
-    for (uint32_t l = 1; l < levels; ++l) nblk += (H.level_total[l] + kLevelWG - 1) / kLevelWG;
-    if (H.off_blk + 4 * nblk > h->plan_cap) return fail(RNG_ENOMEM, "batch plan exceeds its buffer");
-    uint32_t *blks = plan_at<uint32_t>(&H, H.off_blk);
-    for (uint32_t l = 1; l < levels; ++l) {
-        LevelInfo &L = H.lvl[l];
-        L.blk_off = B;
-        uint32_t k = 0;
-        for (uint64_t t0 = 0; t0 < H.level_total[l]; t0 += kLevelWG) {
-            while (k + 1 < L.seg_n && segs[L.seg_off + k + 1].y <= t0) ++k;
-            blks[B++] = k;
-        }
+    uint32_t base = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        Q[i].tile_base = base;
+        base += Q[i].ntiles;
     }
-    H.plan_bytes = H.off_blk + 4 * B;
+    H.n_tiles = base;
+    H.plan_bytes = (uint32_t)align16(H.off_reqs + sizeof(BatchReq) * (uint64_t)n);
     h->planned = true;
     return RNG_OK;
 }
@@ -457,28 +402,21 @@ int rng_batch_launch(rng_batch_t *h, void *stream)
         h->occ_unroll = h->unroll;
     }
     const unsigned gen_grid = h->gen_full;
-    const unsigned level_grid =
-        (unsigned)std::min<uint64_t>((chunk_capacity(h, h->C) + kLevelWG - 1) / kLevelWG, 256);
     if (!h->use_graph) {
-        // root (and tree level 0), the further tree levels, persistent generation
         const BatchArgs a = make_args(h, tab);
-        int rc;
-        if (pin.bytes && H.levels <= kSmallTreeLevels && H.n <= kSmallTreeRequests) {
-            // the whole tree of each request in one launch instead of 1 + levels - 1
-            rc = launch_batch_tree_small(a, pin, H.n, st);
-        } else {
-            rc = launch_batch_root(a, pin, h->max_requests, st);
-            for (uint32_t l = 1; !rc && l < H.levels; ++l) rc = launch_batch_level(a, l, level_grid, st);
+        int rc = launch_batch_root(a, pin, H.n, st);
+        if (!rc && H.n_tiles) {
+            const unsigned need = (unsigned)std::min<uint64_t>(gen_grid, (H.n_tiles + h->wg / 64 - 1) / (h->wg / 64));
+            rc = launch_batch_gen(a, (int)h->wg, (int)h->unroll, need, st);
         }
-        if (!rc) rc = launch_batch_gen(a, (int)h->wg, (int)h->unroll, gen_grid, st);
         return check_launch(rc, "rng_batch_launch");
     }
     rng_batch::Graph *gp = nullptr;
     for (auto &g : h->graphs)
-        if (g.levels == H.levels && g.wg == h->wg && g.unroll == h->unroll) gp = &g;
+        if (g.wg == h->wg && g.unroll == h->unroll) gp = &g;
     if (!gp) {
         const BatchArgs a = make_args(h, tab);
-        rng_batch::Graph g{H.levels, h->wg, h->unroll, nullptr, nullptr};
+        rng_batch::Graph g{h->wg, h->unroll, nullptr, nullptr};
         // Recorded on the handle's own stream (the caller's may be the null
         // stream, which cannot capture); nothing runs while recording.
         hipStream_t cs = h->capture;
@@ -486,8 +424,6 @@ int rng_batch_launch(rng_batch_t *h, void *stream)
             return hip_fail(e, "hipStreamBeginCapture");
         pin.bytes = 0;  // the graph's root kernel reads the uploaded plan
         int rc = launch_batch_root(a, pin, h->max_requests, cs);
-        // level 0 (chunks 1..15 of every request) is done by the root kernel
-        for (uint32_t l = 1; !rc && l < H.levels; ++l) rc = launch_batch_level(a, l, level_grid, cs);
         if (!rc) rc = launch_batch_gen(a, (int)h->wg, (int)h->unroll, gen_grid, cs);
         e = hipStreamEndCapture(cs, &g.graph);
         if (rc) {

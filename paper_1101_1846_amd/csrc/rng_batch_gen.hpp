@@ -8,6 +8,7 @@
 #include "rng_batch_internal.hpp"
 #include "rng_device.hpp"
 #include "rng_internal.hpp"
+#include "wave_starts.hpp"
 
 namespace rngx {
 
@@ -25,7 +26,7 @@ __device__ __forceinline__ gu32 *global_ptr(uint32_t *p) { return (gu32 *)p; }
 
 // LDS tile depth of the generation kernel: kBatchTile samples per row, or 32
 // for 1024-lane workgroups, whose 16 tiles of 64 rows would not fit in the
-// 160 KiB of LDS at 64 (chunk lengths are multiples of kBatchTile, so of both).
+// 160 KiB of LDS at 64.
 constexpr int batch_tile_depth(int wg) { return wg >= 1024 ? 32 : kBatchTile; }
 
 template <int DT>
@@ -35,89 +36,86 @@ __device__ __forceinline__ uint32_t bits_of(uint32_t u)
     else return u;
 }
 
-// One 64-chunk tile: lane l generates chunk chunk0 + l of the group into its
-// LDS row, K samples at a time; rows are then stored with consecutive lanes on
-// consecutive words of one chunk's output.
+// The rows of one tile, lane l's states in g: c = 2^lgc samples of lane l from
+// l c on, up to `left` (the samples from the tile's start to the request's end,
+// at most 64 c).  K samples at a time go through the LDS tile and are stored
+// with consecutive lanes on consecutive quads of a row.
 template <class G, int DT, int U, int K>
-__device__ void batch_tile(const BatchArgs &a, const BatchGroup &gr, uint32_t tile, uint32_t *lds_tile,
-                           uint32_t **row_ptr, uint32_t *row_len)
+__device__ __forceinline__ void batch_rows(G &g, gu32 *out, uint32_t left, uint32_t lgc, uint32_t *tile, int lane)
 {
-    static_assert(K % U == 0 && K % 4 == 0 && kBatchTile % K == 0, "tile depth");
-    constexpr int LD = K + 4;
-    const BatchHeader &h = *a.hdr;
-    const int lane = threadIdx.x & 63;
-    const uint32_t c0 = (tile - gr.tile_begin) * 64;
-    const bool active = c0 + lane < gr.nchunks;
-    const uint32_t c = active ? c0 + lane : c0;
-    // the chunk's request (the root and tree kernels wrote the map)
-    const BatchReq q = plan_at<const BatchReq>(a.hdr, h.off_reqs)[a.chunk_req[gr.tile_begin * 64 + c]];
-    const uint64_t j = c - q.chunk_base;
-    const uint64_t start = j * h.C;
-    const uint32_t len = active ? (uint32_t)min<uint64_t>(h.C, q.length - start) : 0;
-    uint32_t *dst = q.out + start;
-
-    G g;
-    g.load(a.ws + gr.ws_off, gr.nchunks_pad, c, a.tab);
-
-    row_ptr[lane] = dst;
-    row_len[lane] = len;
-    uint32_t maxlen = len;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) maxlen = max(maxlen, (uint32_t)__shfl_xor((int)maxlen, off, 64));
-    const bool aligned = __all(((uintptr_t)dst & 15) == 0);
-    uint32_t *row = lds_tile + lane * LD;
-
-    for (uint32_t k0 = 0; k0 < maxlen; k0 += K) {
-        // Lanes with a whole block left take the unrolled path together; only
-        // the lanes in the final partial block of their chunk (the last chunk
-        // of a request) step one sample at a time, so that they stop exactly
-        // at the chunk's end.
-        if (k0 + K <= len) {
+    static_assert(K % U == 0 && K % 4 == 0, "tile depth");
+    constexpr int LD = K + 4, QPR = K / 4, RPI = 64 / QPR;
+    const uint32_t c = 1u << lgc, at = (uint32_t)lane << lgc;
+    const uint32_t len = left > at ? min(left - at, c) : 0, longest = min(left, c);
+    const bool aligned = ((uintptr_t)out & 15) == 0;
+    uint32_t *row = tile + lane * LD;
+    for (uint32_t k0 = 0; k0 < longest; k0 += K) {
+        // Lanes with a whole block left take the unrolled path together; the
+        // lane whose row ends inside it stops exactly at the request's end.
+        const uint32_t cnt = len > k0 ? min(len - k0, (uint32_t)K) : 0;
+        uint32_t k = 0;
 #pragma unroll 1
-            for (int k = 0; k < K; k += U) {
-                uint32_t v[U];
+        for (; k + U <= cnt; k += U) {
+            uint32_t v[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = bits_of<DT>(g.next());
-                if constexpr (U % 4 == 0) {
+            for (int u = 0; u < U; ++u) v[u] = bits_of<DT>(g.next());
+            if constexpr (U % 4 == 0) {
 #pragma unroll
-                    for (int u = 0; u < U; u += 4) *(uint4 *)&row[k + u] = make_uint4(v[u], v[u + 1], v[u + 2], v[u + 3]);
-                } else {
+                for (int u = 0; u < U; u += 4) *(uint4 *)&row[k + u] = make_uint4(v[u], v[u + 1], v[u + 2], v[u + 3]);
+            } else {
 #pragma unroll
-                    for (int u = 0; u < U; ++u) row[k + u] = v[u];
-                }
+                for (int u = 0; u < U; ++u) row[k + u] = v[u];
             }
-        } else if (k0 < len) {
-            for (uint32_t k = 0; k < len - k0; ++k) row[k] = bits_of<DT>(g.next());
         }
+        for (; k < cnt; ++k) row[k] = bits_of<DT>(g.next());
         RNGX_COMPILER_FENCE();
-        if (aligned) {
-            constexpr int QPR = K / 4, RPI = 64 / QPR;
-            const int rr = lane / QPR, qq = lane % QPR;
+        if (aligned && k0 + K <= c && left == 64u << lgc) {  // uniform: every quad is whole
+            const int r0 = lane / QPR, q = lane % QPR;
+            u32x4 P[QPR];
+#pragma unroll
+            for (int i = 0; i < QPR; ++i) P[i] = *(const u32x4 *)(tile + (r0 + i * RPI) * LD + 4 * q);
+#pragma unroll
+            for (int i = 0; i < QPR; ++i) *(gu32x4 *)(out + (((uint32_t)(r0 + i * RPI) << lgc) + k0 + 4 * q)) = P[i];
+        } else if (aligned) {
+            const int r0 = lane / QPR, q = lane % QPR;
 #pragma unroll 4
             for (int i = 0; i < QPR; ++i) {
-                const int r = i * RPI + rr;
-                const uint32_t col = k0 + 4 * qq, n = row_len[r];
-                gu32 *p = global_ptr(row_ptr[r]) + col;
-                const uint32_t *s = lds_tile + r * LD + 4 * qq;
-                if (col + 4 <= n) {
-                    *(gu32x4 *)p = *(const u32x4 *)s;
-                } else if (col < n) {
-                    for (uint32_t e = 0; e < n - col; ++e) p[e] = s[e];
+                const uint32_t col = k0 + 4 * q, pos = ((uint32_t)(r0 + i * RPI) << lgc) + col;
+                const uint32_t *s = tile + (r0 + i * RPI) * LD + 4 * q;
+                if (col < c && pos + 4 <= left) {
+                    *(gu32x4 *)(out + pos) = *(const u32x4 *)s;
+                } else if (col < c && pos < left) {
+                    for (uint32_t e = 0; e < left - pos; ++e) out[pos + e] = s[e];
                 }
             }
         } else {
-            constexpr int RPI = 64 / K;
-            const int rr = lane / K, cc = lane % K;
+            constexpr int RPW = 64 / K;
+            const int r0 = lane / K, w = lane % K;
 #pragma unroll 4
             for (int i = 0; i < K; ++i) {
-                const int r = i * RPI + rr;
-                const uint32_t col = k0 + cc;
-                if (col < row_len[r]) global_ptr(row_ptr[r])[col] = lds_tile[r * LD + cc];
+                const uint32_t col = k0 + w, pos = ((uint32_t)(r0 + i * RPW) << lgc) + col;
+                if (col < c && pos < left) out[pos] = tile[(r0 + i * RPW) * LD + w];
             }
         }
         RNGX_COMPILER_FENCE();
     }
-    if (active && j + 1 == q.nchunks) g.store(q.state, q.stride, 0);
+}
+
+// One tile: the wave starts its lanes from the request's state, and the lane
+// that produces the request's last sample writes the state back.
+template <class G, int U, int K>
+__device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchReq &q, uint32_t r, uint32_t i, uint32_t dtype,
+                                           uint32_t *tile, int lane)
+{
+    const uint64_t first = (uint64_t)i << (q.lgc + 6), rest = q.length - first;
+    const uint32_t left = (uint32_t)min(rest, (uint64_t)64 << q.lgc);
+    G g;
+    load_uniform(g, a.ws + (uint64_t)8 * r, 1, 0);
+    wave_starts(g, q.offset + first, q.lgc, tile, lane, a.tab);
+    gu32 *out = global_ptr(q.out) + first;
+    if (dtype == RNG_DT_F32) batch_rows<G, RNG_DT_F32, U, K>(g, out, left, q.lgc, tile, lane);
+    else batch_rows<G, RNG_DT_U32, U, K>(g, out, left, q.lgc, tile, lane);
+    if (i + 1 == q.ntiles && (uint32_t)lane == (left - 1) >> q.lgc) g.store(q.state, q.stride, 0);
 }
 
 // Persistent generation.  Wave w of the grid's W waves takes tile w first;
@@ -128,39 +126,33 @@ template <int WG, int U>
 __global__ __launch_bounds__(WG) void k_batch_gen(BatchArgs a)
 {
     constexpr int K = batch_tile_depth(WG), NW = WG / 64, LD = K + 4;
-    __shared__ __attribute__((aligned(16))) uint32_t lds[NW * 64 * LD];
-    __shared__ uint32_t *rptr[NW * 64];
-    __shared__ uint32_t rlen[NW * 64];
+    constexpr int kTileWords = 64 * LD > kWaveStartLds ? 64 * LD : kWaveStartLds;
+    static_assert(kTileWords % 4 == 0, "16-byte aligned tiles");
+    __shared__ __attribute__((aligned(16))) uint32_t lds[NW * kTileWords];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const BatchHeader &h = *a.hdr;
-    const uint32_t nwaves = gridDim.x * NW;
+    const uint32_t nwaves = gridDim.x * NW, n_tiles = uniform_read(&a.hdr->n_tiles);
+    const BatchReq *reqs = plan_at<const BatchReq>(a.hdr, uniform_read(&a.hdr->off_reqs));
+    uint32_t *tile = &lds[wv * kTileWords];
     uint32_t t = blockIdx.x * NW + wv;
-    for (;; ) {
-        if (t >= h.n_tiles) break;
-        uint32_t gi = 0;
-        while (gi + 1 < h.ngroups && t >= h.groups[gi].tile_end) ++gi;
-        const BatchGroup &gr = h.groups[gi];
-        const uint32_t key = gr.gen * 2 + gr.dtype;
-        uint32_t *tile = &lds[wv * 64 * LD];
-        switch (key) {
-#define RNGX_BATCH_CASE(GEN, ID)                                                                   \
-    case ID * 2 + RNG_DT_U32: batch_tile<GEN, RNG_DT_U32, U, K>(a, gr, t, tile, &rptr[wv * 64], &rlen[wv * 64]); break; \
-    case ID * 2 + RNG_DT_F32: batch_tile<GEN, RNG_DT_F32, U, K>(a, gr, t, tile, &rptr[wv * 64], &rlen[wv * 64]); break;
-            RNGX_BATCH_CASE(GenMWC32, G_MWC32)
-            RNGX_BATCH_CASE(GenXS256, G_XS256)
-            RNGX_BATCH_CASE(GenXS32, G_XS32)
-            RNGX_BATCH_CASE(GenKISS, G_KISS)
-            RNGX_BATCH_CASE(GenMWC1616, G_MWC1616)
-#undef RNGX_BATCH_CASE
+    while (t < n_tiles) {
+        const uint32_t r = uniform_read(a.tile_req + t);
+        const BatchReq q = uniform_read(reqs + r);
+        const BatchGroup gr = uniform_read(a.hdr->groups + q.group);
+        const uint32_t i = t - q.tile_base;
+        switch (gr.gen) {
+        case G_MWC32: batch_tile<GenMWC32, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+        case G_XS256: batch_tile<GenXS256, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+        case G_XS32: batch_tile<GenXS32, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+        case G_KISS: batch_tile<GenKISS, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+        case G_MWC1616: batch_tile<GenMWC1616, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
         }
-        if (nwaves >= h.n_tiles) break;  // every tile was handed out statically
+        if (nwaves >= n_tiles) break;  // every tile was handed out statically
         uint32_t next = 0;
         if (lane == 0) next = atomicAdd(a.counter, 1u);
-        t = nwaves + __builtin_amdgcn_readfirstlane(__shfl(next, 0, 64));
+        t = nwaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
     }
 }
-
 
 template <int WG, int U>
 static int gen_t(const BatchArgs &a, unsigned grid, hipStream_t s)

@@ -151,36 +151,6 @@ __device__ __forceinline__ void gf2_apply256_t4(const uint4 *T, uint32_t (&x)[8]
     for (int i = 0; i < 8; ++i) x[i] = r[i];
 }
 
-// The same with a loop over the words of x: a tenth of the code, for kernels
-// that take one product at their start, where fetching straight-line code for
-// the first time costs more than the loop (9000 against 4000 clocks).
-__device__ __forceinline__ void gf2_apply256_t4_loop(const uint4 *T, uint32_t (&x)[8])
-{
-    uint32_t r[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll 1
-    for (int i = 0; i < 8; ++i, T += 8 * 32) {
-        uint32_t w = x[0];
-#pragma unroll
-        for (int k = 0; k < 7; ++k) x[k] = x[k + 1];
-#pragma unroll
-        for (int p = 0; p < 8; p += 2) {
-            const uint32_t n0 = (w >> (4 * p)) & 15u, n1 = (w >> (4 * p + 4)) & 15u;
-            const uint4 a0 = T[(2 * p) * 16 + n0], a1 = T[(2 * p + 1) * 16 + n0];
-            const uint4 b0 = T[(2 * p + 2) * 16 + n1], b1 = T[(2 * p + 3) * 16 + n1];
-            r[0] = xor3(r[0], a0.x, b0.x);
-            r[1] = xor3(r[1], a0.y, b0.y);
-            r[2] = xor3(r[2], a0.z, b0.z);
-            r[3] = xor3(r[3], a0.w, b0.w);
-            r[4] = xor3(r[4], a1.x, b1.x);
-            r[5] = xor3(r[5], a1.y, b1.y);
-            r[6] = xor3(r[6], a1.z, b1.z);
-            r[7] = xor3(r[7], a1.w, b1.w);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = r[i];
-}
-
 // Copies NQ consecutive 16-byte quads (whole lookup tables of 2048 quads,
 // 32 KiB) into LDS with a workgroup of WG lanes, every global load issued
 // before the first LDS write: one memory round trip, where a loop strided by
@@ -338,6 +308,21 @@ struct GenKISS : rng_inline::KISS {
         jcong = (uint32_t)(d[2] >> 32);
     }
 };
+
+// *p for a whole wave (p uniform) through the scalar cache, so that the result
+// is uniform to the compiler too; nothing in the launch may write it.
+template <class T>
+__device__ __forceinline__ T uniform_read(const T *p)
+{
+    static_assert(sizeof(T) % 4 == 0);
+    struct Words {
+        uint32_t w[sizeof(T) / 4];
+    } x;
+    const auto *c = (const __attribute__((address_space(4))) uint32_t *)p;
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) x.w[i] = c[i];
+    return __builtin_bit_cast(T, x);
+}
 
 // Stream s's state for a whole wave (s uniform) through the scalar cache: with
 // vector loads every wave of a launch that starts from one state asks the same

@@ -47,9 +47,7 @@ template <int DT, int K>
 __global__ __launch_bounds__(64) void k_seq_xs256(SeqXsArgs a)
 {
     constexpr int U = 8, LD = K + 4, QPR = K / 4, RPI = 64 / QPR;
-    constexpr int kWords = 64 * LD > 8192 ? 64 * LD : 8192;  // the tile, or a 4-bit table
-    __shared__ __attribute__((aligned(16))) uint32_t tile[kWords];
-    __shared__ uint32_t s_w[kXs256Window];
+    __shared__ __attribute__((aligned(16))) uint32_t tile[64 * LD > kXs256Lds ? 64 * LD : kXs256Lds];
     const int lane = threadIdx.x;
     const uint32_t s = blockIdx.x / a.wp, p = blockIdx.x - s * a.wp;
     gu32 *out = (gu32 *)a.out + (uint64_t)s * a.N;
@@ -100,7 +98,7 @@ __global__ __launch_bounds__(64) void k_seq_xs256(SeqXsArgs a)
         if (t != p) xs256_wave_jump(base.v, (uint64_t)a.wp << lgwin, lane, a.tab);
         g = base;
         asm volatile("" ::: "memory");  // the last tile is in registers
-        xs256_lane_starts(g.v, a.lgc, (uint4 *)tile, s_w, lane, a.tab);
+        xs256_lane_starts(g.v, a.lgc, tile, lane, a.tab);
         gchar *dst = (gchar *)(out + (t << lgwin));
         if (t < full) {
 #pragma unroll

@@ -1,0 +1,90 @@
+// wave_starts.hpp -- start states of a wave's 64 lanes from one state that they
+// share: lane l moves k + l 2^lgc steps on, k any distance.  Latency bounds it,
+// so what the lanes share is done once for the wave: powers are squared up in
+// registers or read in one load, and a product of the shared state with a GF(2)
+// matrix is an XOR across the lanes (about 3 us for KISS, 8 for XS256).
+#pragma once
+#include "xs256_jump.hpp"
+
+namespace rngx {
+
+constexpr int kWaveStartLds = kXs256Lds;  // words of LDS of the wave's own
+
+template <class G>
+__device__ __forceinline__ void wave_starts(G &g, uint64_t k, uint32_t lgc, uint32_t *lds, int lane,
+                                            const DevTables &tab)
+{
+    constexpr bool kMwc16 = G::kId == G_MWC1616 || G::kId == G_KISS;
+    constexpr bool kXs32 = G::kId == G_XS32 || G::kId == G_KISS;
+    if constexpr (G::kId == G_XS256) {
+        xs256_wave_jump(g.v, k, lane, tab);
+        xs256_lane_starts(g.v, lgc, lds, lane, tab);
+    }
+    if constexpr (G::kId == G_MWC32) {
+        const uint64_t mine = tab.mwc32_pow[lane];
+        auto power = [&](int b) {
+            return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), b) << 32 |
+                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, b);
+        };
+        uint64_t z = (uint64_t)g.c << 32 | g.x;
+        for (int b = 0; b < 64 && (k >> b); ++b)
+            if ((k >> b) & 1) z = mwc32_mulmod(z, power(b), tab.mwc32_a, tab.mwc32_m);
+        for (int b = 0; b < 6; ++b) {
+            const uint64_t r = mwc32_mulmod(z, power((int)lgc + b), tab.mwc32_a, tab.mwc32_m);
+            z = (lane >> b) & 1 ? r : z;
+        }
+        g.x = (uint32_t)z;
+        g.c = (uint32_t)(z >> 32);
+    }
+    if constexpr (kXs32) {
+        uint32_t *word;
+        if constexpr (G::kId == G_KISS) word = &g.jsr;
+        else word = &g.y;
+        uint32_t y = (uint32_t)__builtin_amdgcn_readfirstlane((int)*word);
+        for (int b0 = 0; b0 < 64 && (k >> b0); b0 += 16) {
+            uint32_t col[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) col[i] = tab.xs32_pow[(b0 + i) * 32 + (lane & 31)];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if ((k >> (b0 + i)) & 1) y = xor_over_32(col[i] & (0u - ((y >> (lane & 31)) & 1u)));
+        }
+#pragma unroll 2
+        for (int b = 0; b < 6; ++b) {
+            const uint32_t r = gf2_apply32(tab.xs32_pow + (lgc + b) * 32, y);
+            y = (lane >> b) & 1 ? r : y;
+        }
+        *word = y;
+    }
+    if constexpr (kMwc16) {
+        // lanes below 32 carry the powers of the first word, the others of the second
+        const uint32_t ai = lane < 32 ? g.a1 : g.a2, m = ai * 65536u - 1u;
+        uint32_t c = (0u - m) % m, u = 0;  // one step is a; a 2^48 = 2^32 (mod a 2^16 - 1)
+        uint32_t a = 69069u, d = 1234567u, ua = 1, ud = 0;
+        for (uint32_t b = 0; b < lgc + 6 || (b < 64 && (k >> b)); ++b) {
+            if ((k >> b) & 1) {
+                u = u ? mwc16_mulmod(u, c, ai) : c;
+                ud = a * ud + d;
+                ua *= a;
+            }
+            if (b >= lgc && b < lgc + 6) {
+                const bool on = (lane >> (b - lgc)) & 1;
+                const uint32_t z = mwc16_mulmod(g.z, (uint32_t)__builtin_amdgcn_readlane((int)c, 0), g.a1);
+                const uint32_t w = mwc16_mulmod(g.w, (uint32_t)__builtin_amdgcn_readlane((int)c, 32), g.a2);
+                g.z = on ? z : g.z;
+                g.w = on ? w : g.w;
+                if constexpr (G::kId == G_KISS) g.jcong = on ? a * g.jcong + d : g.jcong;
+            }
+            c = mwc16_mulmod(c, c, ai);
+            d = a * d + d;
+            a *= a;
+        }
+        if (k) {
+            g.z = mwc16_mulmod(g.z, (uint32_t)__builtin_amdgcn_readlane((int)u, 0), g.a1);
+            g.w = mwc16_mulmod(g.w, (uint32_t)__builtin_amdgcn_readlane((int)u, 32), g.a2);
+            if constexpr (G::kId == G_KISS) g.jcong = ua * g.jcong + ud;
+        }
+    }
+}
+
+}  // namespace rngx

@@ -68,13 +68,17 @@ __device__ __forceinline__ void xs256_wave_jump(uint32_t (&x)[8], uint64_t k, in
 }
 
 constexpr int kXs256PolyMin = 5, kXs256PolyMax = 12;  // log2 of the distances with a coefficient table
-constexpr int kXs256Window = 264;                     // words of s_w below
+constexpr int kXs256Window = 264;                     // words of the expansion below
+constexpr int kXs256Lds = 2048 + kXs256Window;        // words of LDS for xs256_lane_starts
 
-// The state of lane l: x (uniform, v_0 .. v_7) moved l 2^lgc steps on.
-// t4: 2048 quads of LDS, s_w: kXs256Window words, both the wave's own.
-__device__ __forceinline__ void xs256_lane_starts(uint32_t (&x)[8], uint32_t lgc, uint4 *t4, uint32_t *s_w, int lane,
+// The state of lane l: x (uniform, v_0 .. v_7) moved l 2^lgc steps on.  lds:
+// kXs256Lds words of the wave's own, 16-byte aligned.  The 4-bit table is built
+// and used a quarter at a time (16 of the 64 nibbles, 8 KiB).
+__device__ __forceinline__ void xs256_lane_starts(uint32_t (&x)[8], uint32_t lgc, uint32_t *lds, int lane,
                                                   const DevTables &tab)
 {
+    uint4 *t4 = (uint4 *)lds;
+    uint32_t *s_w = lds + 2048;
     // numbers 0 .. 262 from v_0 on: 16 lanes each from every 64th state (with 8
     // from every 32nd the gathers took more than the steps saved)
     const uint32_t n = lane_nibble(x, lane);
@@ -108,35 +112,52 @@ __device__ __forceinline__ void xs256_lane_starts(uint32_t (&x)[8], uint32_t lgc
 #pragma unroll
         for (int k = 0; k < 8; ++k) w[8 + i + k] = g.next();  // up to word 263
     asm volatile("" ::: "memory");
-    // quad (2p + h) * 16 + v, p = lane: words 4h .. 4h+3 of the XOR of the
-    // states after 4p + k steps over the set bits k of v, in Gray-code order
-    uint32_t m[11], e[8];
+    // Quarter i: quad (2p + h) * 16 + v holds words 4h .. 4h+3 of the XOR of the
+    // states after 4 (16 i + p) + k steps over the set bits k of v; lane 4p + j
+    // writes entries 4j .. 4j+3 of nibble p.  Then 16 nibbles of the
+    // coefficients look theirs up.  (A loop: straight-line code costs its first
+    // fetch, 9000 against 4000 clocks for the look-ups.)
+    uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w}, r[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    const uint32_t on2 = 0u - (uint32_t)(lane & 1), on3 = 0u - (uint32_t)((lane >> 1) & 1);
+    uint4 *const mine = t4 + (lane >> 2) * 32 + 4 * (lane & 3);
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i) {
+        uint32_t m[11], e[8];
 #pragma unroll
-    for (int i = 0; i < 11; ++i) m[i] = s_w[4 * lane + i];
+        for (int k = 0; k < 11; ++k) m[k] = s_w[64 * i + 4 * (lane >> 2) + k];
+        asm volatile("" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = 0;
+        for (int k = 0; k < 8; ++k) e[k] = (m[2 + k] & on2) ^ (m[3 + k] & on3);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int v = i ^ (i >> 1);
-        if (i) {
-            const int k = __builtin_ctz(i);
+        for (int n = 0; n < 4; ++n) {  // entries 0, 1, 3, 2
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] ^= m[k + j];
+            for (int k = 0; k < 8; ++k)
+                if (n) e[k] ^= m[(n & 1 ? 0 : 1) + k];
+            mine[n ^ (n >> 1)] = make_uint4(e[0], e[1], e[2], e[3]);
+            mine[16 + (n ^ (n >> 1))] = make_uint4(e[4], e[5], e[6], e[7]);
         }
-        t4[2 * lane * 16 + v] = make_uint4(e[0], e[1], e[2], e[3]);
-        t4[(2 * lane + 1) * 16 + v] = make_uint4(e[4], e[5], e[6], e[7]);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int p = 0; p < 16; p += 2) {
+            const uint32_t w = p < 8 ? c[0] : c[1];
+            const uint32_t n0 = (w >> (4 * (p & 7))) & 15u, n1 = (w >> (4 * (p & 7) + 4)) & 15u;
+            const uint4 a0 = t4[(2 * p) * 16 + n0], a1 = t4[(2 * p + 1) * 16 + n0];
+            const uint4 b0 = t4[(2 * p + 2) * 16 + n1], b1 = t4[(2 * p + 3) * 16 + n1];
+            r[0] = xor3(r[0], a0.x, b0.x);
+            r[1] = xor3(r[1], a0.y, b0.y);
+            r[2] = xor3(r[2], a0.z, b0.z);
+            r[3] = xor3(r[3], a0.w, b0.w);
+            r[4] = xor3(r[4], a1.x, b1.x);
+            r[5] = xor3(r[5], a1.y, b1.y);
+            r[6] = xor3(r[6], a1.z, b1.z);
+            r[7] = xor3(r[7], a1.w, b1.w);
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < 6; ++k) c[k] = c[k + 2];
     }
-    asm volatile("" ::: "memory");
-    x[0] = c0.x;
-    x[1] = c0.y;
-    x[2] = c0.z;
-    x[3] = c0.w;
-    x[4] = c1.x;
-    x[5] = c1.y;
-    x[6] = c1.z;
-    x[7] = c1.w;
-    gf2_apply256_t4_loop(t4, x);
-    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = r[i];
 }
 
 }  // namespace rngx
