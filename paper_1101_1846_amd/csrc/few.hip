@@ -7,7 +7,8 @@
 // destination pointers, consecutive lanes on consecutive 16-byte quads.  No
 // chunk writes the state back (the others read it at unordered times): the
 // host advances the states by N with a skip launch afterwards.  Only rows too
-// short for windows of consecutive numbers (seq.hip) come here, so never XS256,
+// short for windows of consecutive numbers (seq.hip) come here, with launch
+// shapes of more than 256 lanes (rows.hip takes the others), so never XS256,
 // whose chunks are longer.
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -333,24 +333,22 @@ static void rot_constants(int g, uint64_t N, GenArgs &a)
 }
 
 // Streams that run as long sequences, windows of consecutive numbers across a
-// wave (seq.hip, seq_xs256.hip), instead of a row or chunk per lane: up to one
-// stream per wave of the device from the shortest rows that fill a window of
-// 32-number blocks on (us, rows against windows: KISS 64 x 4096 24.3 / 13.8,
-// 1000 x 10^5 112 / 100, 100 x 1000001 232 / 98; MWC32 equal to within 1 us
-// where the call is launch-bound; XS256 64 x 4096 144 / 13, 1000 x 10^5 322 /
-// 131), and more streams if their rows start inside 128-byte lines and are
-// long enough to pay for a wave's start (KISS 10^4 x 25001 643 / 324, 1500 x
-// 100001 345 / 173; but 10^4 x 10^4 125 / 203, and with whole lines 10^4 x
-// 16384 193 / 192).  XS256, whose chunks start by a chain of table products
-// per lane, takes four streams per wave, and shorter rows (4096 x 4096 152 /
-// 71, 4096 x 10^4 188 / 106; but 4096 x 65536 235 / 266, 10^4 x 10^4 222 /
-// 255, 20000 x 10001 421 / 518).
+// wave (seq.hip, seq_xs256.hip), instead of rows or chunks of a row per lane: up
+// to one stream per wave of the device, from the lengths on at which a stream's
+// windows outnumber its 64 chunks' worth of waves (KISS, us, chunks / windows:
+// 64 x 2048 10.9 / 14.0, 1000 x 4096 14.3 / 16.9, 256 x 10^4 22 / 17, 512 x 10^5
+// 78 / 51, 64 x 10^5 71 / 23; 1500 x 100001 146 / 163).  XS256, whose chunks
+// start by a chain of table products per lane, from shorter rows on (64 x 512
+// 18.3 / 12.6, 1000 x 1000 42 / 20), with four streams per wave (4096 x 4096
+// 151 / 67, 4096 x 10^4 188 / 95; but 4096 x 65536 231 / 227, 2 10^4 x 10^4 421
+// either way), and with more where rows that long start inside 128-byte lines
+// (10^4 x 25001 525 / 358).
 static bool seq_streams(int g, uint64_t S, uint64_t N, const void *out)
 {
-    const bool lines = N % 32 == 0 && !((uintptr_t)out & 127);
-    if (S <= kSeqWaves) return N >= (g == RNG_XS256 ? 512 : 2048);
-    if (g == RNG_XS256 && S <= 4 * kSeqWaves && N >= 2048 && N < 16384) return true;
-    return N >= 16384 && S <= ((uint64_t)1 << 24) && !lines;
+    if (g != RNG_XS256) return S <= kSeqWaves && N >= 8192;
+    if (S <= kSeqWaves) return N >= 512;
+    if (S <= 4 * kSeqWaves && N >= 2048 && N < 16384) return true;
+    return N >= 16384 && S <= ((uint64_t)1 << 24) && (N % 32 != 0 || ((uintptr_t)out & 127));
 }
 
 // Shared by rng_generate and the split path: one generate launch over
@@ -375,6 +373,9 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
         if (int e = check_launch(launch_seq(g, dt, d_state, ld, S, N, d_out, nullptr, tab, st), "rng_generate")) return e;
         return check_launch(dispatch_skip(g, d_state, ld, S, N, tab, st), "rng_generate: state");
     }
+    uint32_t lgp, c;
+    if (staged && shape.wg <= 256 && N <= kRowMax && row_chunks(g, S, N, &lgp, &c))
+        return check_launch(launch_rows(g, dt, d_state, ld, S, N, lgp, c, d_out, tab, st), "rng_generate");
     if (staged && S < 64) {
         uint64_t c;
         uint32_t P;
@@ -407,7 +408,7 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
     }
     if (staged && a.P == 1 && shape.wg <= 256 && N >= kRowMin && N <= kRowMax &&
         (!a.vec4 || S % 64 != 0 || N % kGenTile != 0))
-        return check_launch(launch_rows(g, dt, d_state, ld, S, N, N, d_out, true, nullptr, tab, st), "rng_generate");
+        return check_launch(launch_rows(g, dt, d_state, ld, S, N, 0, (uint32_t)N, d_out, tab, st), "rng_generate");
     rc = dispatch_generate(g, dt, a, (int)shape.wg, (int)shape.unroll, staged, st);
     if (rc != kStatesNotWritten) return check_launch(rc, "rng_generate");
     // chunks of one stream in several workgroups: the states advance after

@@ -56,12 +56,13 @@ int launch_seq_xs256(int dt, const uint32_t *state, uint64_t ld, uint64_t S, uin
 int seq_run(int g, const uint32_t *state_one, uint64_t total, int t, void *out, uint32_t *final_state, uint32_t *ws,
             const DevTables &tab, hipStream_t st);
 
-// Rows of any length (32 <= C < 2^24), count and alignment, one per lane
-// (rows.hip): R rows of C numbers one after the other in out, the last one of
-// `last`, from states at word stride ld, which are rewritten if write_back.
+// Rows of any length (32 <= N < 2^24), count and alignment, one per lane, or
+// 2^lgp chunks of C numbers per stream, one per lane (rows.hip; row_chunks gives
+// them, false if there is none to gain).  The states are rewritten.
 constexpr uint64_t kRowMin = 32, kRowMax = ((uint64_t)1 << 24) - 1;
-int launch_rows(int g, int dt, uint32_t *state, uint64_t ld, uint64_t R, uint64_t C, uint64_t last, void *out,
-                bool write_back, uint32_t *final_state, const DevTables &tab, hipStream_t st);
+bool row_chunks(int g, uint64_t S, uint64_t N, uint32_t *lgp, uint32_t *C);
+int launch_rows(int g, int dt, uint32_t *state, uint64_t ld, uint64_t S, uint64_t N, uint32_t lgp, uint32_t C, void *out,
+                const DevTables &tab, hipStream_t st);
 
 // Tables of the current device only if they exist already (never allocates).
 int device_tables_if_ready(DevTables *out);

@@ -9,6 +9,12 @@
 // number it writes the first ones of the next lane's row, which complete the
 // line that the two rows share.  Only a group of 64 rows begins and ends with
 // a partial line.
+//
+// Too few streams for that are cut into P chunks each, P a power of two up to
+// 64, and a lane's row is a chunk: chunk v mod P of stream v / P, which follows
+// the row before it in memory like any other.  All chunks of a stream are lanes
+// of one wave, so every lane has read its start state before the last chunk's
+// writes the stream's back, and one launch does it.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -16,18 +22,18 @@
 
 #include "rng.h"
 #include "rng_abi_internal.hpp"
+#include "wave_starts.hpp"
 
 namespace rngx {
 
 namespace {
 
 struct RowArgs {
-    uint32_t *state;        // [W][ld]; rewritten if wb
-    uint64_t ld, R, C;      // word stride, rows, numbers per row
-    uint64_t last;          // numbers of the last row (1 .. C)
-    uint32_t *out;          // rows one after the other
-    uint32_t *final_state;  // [W][1]: state after the last row, or null
-    uint32_t wb;
+    uint32_t *state;  // [W][ld]
+    uint64_t ld, S;   // word stride, streams
+    uint64_t N;       // numbers per stream
+    uint32_t lgp, C;  // log2 of the chunks per stream, numbers per chunk (the last one N - (P - 1) C)
+    uint32_t *out;    // [S][N]
     DevTables tab;
 };
 
@@ -55,16 +61,19 @@ constexpr int row_groups(int K)
 // its head and its last tile, which do not overlap their own stores.
 constexpr uint64_t kRowShort = 512;
 
-template <class G, int DT, int K>
+// kChunks: more than one chunk per stream.
+template <class G, int DT, int K, bool kChunks>
 __global__ __launch_bounds__(64) void k_rows(RowArgs a)
 {
     constexpr int U = 8, LD = K + 4, QPR = K / 4, RPI = 64 / QPR, MG = row_groups<G>(K);
     __shared__ __attribute__((aligned(16))) uint32_t tile[64 * LD];
     __shared__ uint32_t s_ext[64];  // numbers from a row's first whole line to the next row's
     const int lane = threadIdx.x;
-    const uint64_t wave = blockIdx.x, nwaves = gridDim.x, groups = (a.R + 63) / 64;
+    const uint64_t wave = blockIdx.x, nwaves = gridDim.x, R = kChunks ? a.S << a.lgp : a.S, groups = (R + 63) / 64;
     const uint32_t ng = (uint32_t)((groups - wave + nwaves - 1) / nwaves);  // the launcher keeps it within MG
-    const uint32_t C = (uint32_t)a.C;
+    const uint32_t N = (uint32_t)a.N, lgp = kChunks ? a.lgp : 0, lastj = (1u << lgp) - 1, tail = N - lastj * a.C;
+    // row r of a group from the group's first number on
+    auto begin = [&](uint32_t r) { return kChunks ? (r >> lgp) * N + (r & lastj) * a.C : r * N; };
     uint32_t *row = tile + lane * LD;
     const int r0 = lane / QPR, q = lane % QPR;
     const uint32_t *src = tile + r0 * LD + 4 * q;
@@ -72,7 +81,7 @@ __global__ __launch_bounds__(64) void k_rows(RowArgs a)
 #pragma unroll
     for (int i = 0; i < MG; ++i)
         if ((uint32_t)i < ng)
-            gs[i].load(a.state, a.ld, min((wave + (uint64_t)i * nwaves) * 64 + lane, a.R - 1), a.tab);
+            gs[i].load(a.state, a.ld, min((wave + (uint64_t)i * nwaves) * 64 + lane, R - 1) >> lgp, a.tab);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): every state is in before the first store
     G g;
     u32x4 P[QPR];
@@ -95,15 +104,16 @@ __global__ __launch_bounds__(64) void k_rows(RowArgs a)
         g = gs[0];
 #pragma unroll
         for (int i = 0; i + 1 < MG; ++i) gs[i] = gs[i + 1];
-        const uint32_t rows = (uint32_t)min<uint64_t>(64, a.R - s0);
+        const uint32_t rows = (uint32_t)min<uint64_t>(64, R - s0);
         // words relative to the line in which the group starts
-        gu32 *base = (gu32 *)a.out + s0 * a.C;
+        gu32 *base = (gu32 *)a.out + (s0 >> lgp) * a.N;
         const uint32_t e = (uint32_t)((uintptr_t)base >> 2) & 31;
         base -= e;
         // lanes past the last row repeat it, numbers and stores alike
-        const uint32_t rl = min((uint32_t)lane, rows - 1), rel = e + rl * C;
-        const bool mine = (uint32_t)lane < rows, last = s0 + rl == a.R - 1;
-        const uint32_t len = last ? (uint32_t)a.last : C;
+        const uint32_t rl = min((uint32_t)lane, rows - 1), j = rl & lastj, rel = e + begin(rl);
+        const bool mine = (uint32_t)lane < rows;
+        const uint32_t len = !kChunks ? N : j == lastj ? tail : a.C;
+        if constexpr (kChunks) lane_jump(g, j * a.C, 32 - __builtin_clz(lastj * a.C), a.tab);
         const uint32_t h = min((0u - rel) & 31u, len);
         uint32_t maxh = 0;
 #pragma unroll
@@ -138,7 +148,7 @@ __global__ __launch_bounds__(64) void k_rows(RowArgs a)
         s_ext[lane] = ext;
         uint32_t off[QPR];  // bytes: this lane's quad of the rows that it stores
 #pragma unroll
-        for (int i = 0; i < QPR; ++i) off[i] = ((e + min((uint32_t)(r0 + i * RPI), rows - 1) * C + 31) & ~31u) * 4 + 16 * q;
+        for (int i = 0; i < QPR; ++i) off[i] = ((e + begin(min((uint32_t)(r0 + i * RPI), rows - 1)) + 31) & ~31u) * 4 + 16 * q;
         uint32_t minL = L, maxE = ext;
 #pragma unroll
         for (int o = 32; o; o >>= 1) {
@@ -186,7 +196,7 @@ __global__ __launch_bounds__(64) void k_rows(RowArgs a)
                 const uint32_t n = s_ext[r0 + i * RPI], c = k0 + 4 * q;
                 const uint32_t *from = src + i * RPI * LD;
                 const uint32_t r = min((uint32_t)(r0 + i * RPI), rows - 1);
-                gu32 *to = (gu32 *)(dst + (((e + r * C + 31) & ~31u) * 4 + 16 * q));
+                gu32 *to = (gu32 *)(dst + (((e + begin(r) + 31) & ~31u) * 4 + 16 * q));
                 if (c + 4 <= n) {
                     *(gu32x4 *)to = *(const u32x4 *)from;
                 } else if (c < n) {
@@ -195,20 +205,23 @@ __global__ __launch_bounds__(64) void k_rows(RowArgs a)
             }
             fence();
         }
-        if (mine) {
-            if (a.wb) g.store(a.state, a.ld, s0 + lane);
-            if (last && a.final_state) g.store(a.final_state, 1, 0);
-        }
+        if (mine && j == lastj) g.store(a.state, a.ld, (s0 + lane) >> lgp);
     }
 }
 
 template <class G, int DT, int K>
 int launch_rows_k(const RowArgs &a, hipStream_t st)
 {
-    const uint64_t groups = (a.R + 63) / 64, waves = 1024 * (128 / K);
+    const uint64_t groups = ((a.S << a.lgp) + 63) / 64, waves = 1024 * (128 / K);
     const uint64_t per = std::min<uint64_t>((groups + waves - 1) / waves, row_groups<G>(K));
     const dim3 grid((unsigned)((groups + per - 1) / per)), block(64);
-    hipLaunchKernelGGL((k_rows<G, DT, K>), grid, block, 0, st, a);
+    if constexpr (G::kId != G_XS256) {
+        if (a.lgp) {
+            hipLaunchKernelGGL((k_rows<G, DT, K, true>), grid, block, 0, st, a);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        }
+    }
+    hipLaunchKernelGGL((k_rows<G, DT, K, false>), grid, block, 0, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -222,18 +235,32 @@ int launch_rows_t(int dt, const RowArgs &a, hipStream_t st)
 
 }  // namespace
 
-int launch_rows(int g, int dt, uint32_t *state, uint64_t ld, uint64_t R, uint64_t C, uint64_t last, void *out,
-                bool write_back, uint32_t *final_state, const DevTables &tab, hipStream_t st)
+// Chunks of S streams of N numbers: as many as give every wave slot a group of
+// 64 (four waves per CU with chunks of at least kRowShort, eight with shorter
+// ones), of 64 numbers or more.  They are whole lines if that makes the last
+// one, which takes the rest, at most an eighth longer.
+bool row_chunks(int g, uint64_t S, uint64_t N, uint32_t *lgp, uint32_t *C)
+{
+    uint32_t lg = 0;
+    while (lg < 6 && N >> (lg + 1) >= 64 && S << (lg + 1) <= (N >> (lg + 1) < kRowShort ? 2 : 1) * (uint64_t)65536) ++lg;
+    if (g == RNG_XS256 || lg == 0) return false;
+    const uint64_t c = N >> lg, whole = c & ~(uint64_t)31;
+    *lgp = lg;
+    *C = (uint32_t)(8 * (N - (whole << lg)) <= whole ? whole : c);
+    return true;
+}
+
+int launch_rows(int g, int dt, uint32_t *state, uint64_t ld, uint64_t S, uint64_t N, uint32_t lgp, uint32_t C, void *out,
+                const DevTables &tab, hipStream_t st)
 {
     RowArgs a{};
     a.state = state;
     a.ld = ld;
-    a.R = R;
+    a.S = S;
+    a.N = N;
+    a.lgp = lgp;
     a.C = C;
-    a.last = last;
     a.out = (uint32_t *)out;
-    a.final_state = final_state;
-    a.wb = write_back;
     a.tab = tab;
     switch (g) {
     case RNG_MWC32: return launch_rows_t<GenMWC32>(dt, a, st);
