@@ -50,11 +50,12 @@ __device__ __forceinline__ uint32_t row_bits(uint32_t u)
 
 // Groups whose states a wave reads before its first store (a wait for a load
 // waits for the stores before it too), as far as the registers go: 512 for 4
-// waves per CU with tiles of 128, 256 for 8 with tiles of 64.
+// waves per CU with tiles of 128, 256 for 8 with tiles of 64.  Chunks make one
+// group per wave.
 template <class G>
-constexpr int row_groups(int K)
+constexpr int row_groups(int K, bool chunks)
 {
-    return K >= 128 ? 16 : G::W > 6 ? 4 : 8;
+    return chunks ? 1 : K >= 128 ? 16 : G::W > 6 ? 4 : 8;
 }
 
 // Rows below this take 64-number tiles, 8 waves per CU: most of a short row is
@@ -65,7 +66,7 @@ constexpr uint64_t kRowShort = 512;
 template <class G, int DT, int K, bool kChunks>
 __global__ __launch_bounds__(64) void k_rows(RowArgs a)
 {
-    constexpr int U = 8, LD = K + 4, QPR = K / 4, RPI = 64 / QPR, MG = row_groups<G>(K);
+    constexpr int U = 8, LD = K + 4, QPR = K / 4, RPI = 64 / QPR, MG = row_groups<G>(K, kChunks);
     __shared__ __attribute__((aligned(16))) uint32_t tile[64 * LD];
     __shared__ uint32_t s_ext[64];  // numbers from a row's first whole line to the next row's
     const int lane = threadIdx.x;
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(64) void k_rows(RowArgs a)
         const uint32_t rl = min((uint32_t)lane, rows - 1), j = rl & lastj, rel = e + begin(rl);
         const bool mine = (uint32_t)lane < rows;
         const uint32_t len = !kChunks ? N : j == lastj ? tail : a.C;
-        if constexpr (kChunks) lane_jump(g, j * a.C, 32 - __builtin_clz(lastj * a.C), a.tab);
+        if constexpr (kChunks) lane_jump(g, j * a.C, 32 - __builtin_clz(lastj * a.C), tile, lane, a.tab);
         const uint32_t h = min((0u - rel) & 31u, len);
         uint32_t maxh = 0;
 #pragma unroll
@@ -213,7 +214,7 @@ template <class G, int DT, int K>
 int launch_rows_k(const RowArgs &a, hipStream_t st)
 {
     const uint64_t groups = ((a.S << a.lgp) + 63) / 64, waves = 1024 * (128 / K);
-    const uint64_t per = std::min<uint64_t>((groups + waves - 1) / waves, row_groups<G>(K));
+    const uint64_t per = std::min<uint64_t>((groups + waves - 1) / waves, row_groups<G>(K, a.lgp > 0));
     const dim3 grid((unsigned)((groups + per - 1) / per)), block(64);
     if constexpr (G::kId != G_XS256) {
         if (a.lgp) {
@@ -238,7 +239,8 @@ int launch_rows_t(int dt, const RowArgs &a, hipStream_t st)
 // Chunks of S streams of N numbers: as many as give every wave slot a group of
 // 64 (four waves per CU with chunks of at least kRowShort, eight with shorter
 // ones), of 64 numbers or more.  They are whole lines if that makes the last
-// one, which takes the rest, at most an eighth longer.
+// one, which takes the rest, at most an eighth longer.  (A last chunk that is
+// shorter would take its whole group off the overlapped tiles.)
 bool row_chunks(int g, uint64_t S, uint64_t N, uint32_t *lgp, uint32_t *C)
 {
     uint32_t lg = 0;

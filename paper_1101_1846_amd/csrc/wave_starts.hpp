@@ -87,46 +87,71 @@ __device__ __forceinline__ void wave_starts(G &g, uint64_t k, uint32_t lgc, uint
     }
 }
 
-// Each lane's own state moved its own k steps on (k below 2^nb, nb uniform);
-// not for XS256.  The powers are squared up in registers (MWC16, whose table
-// takes a search for the multiplier and a load per bit, one after the other) or
-// are the same for all lanes and read through the scalar cache.
+// Each lane's own state moved its own k steps on (k below 2^nb, nb <= 24,
+// uniform); not for XS256.  A chain of nb products, so no load is in it: the
+// MWC16 powers are squared up in registers (their table would take a search for
+// the multiplier too), the MWC32 ones lie one per lane, and the xorshift32
+// columns are copied to lds (kLaneJumpLds words of the wave's own) at once.
+constexpr int kLaneJumpLds = 24 * 32;
+
 template <class G>
-__device__ __forceinline__ void lane_jump(G &g, uint32_t k, int nb, const DevTables &tab)
+__device__ __forceinline__ void lane_jump(G &g, uint32_t k, int nb, uint32_t *lds, int lane, const DevTables &tab)
 {
     static_assert(G::kId != G_XS256);
     constexpr bool kMwc16 = G::kId == G_MWC1616 || G::kId == G_KISS;
+    constexpr bool kXs32 = G::kId == G_XS32 || G::kId == G_KISS;
     uint32_t cz = 0, cw = 0, a = 69069u, d = 1234567u;
+    uint64_t power = 0;
+    if constexpr (G::kId == G_MWC32) power = tab.mwc32_pow[lane];
+    if constexpr (kXs32) {
+        asm volatile("" ::: "memory");
+        uint32_t v[kLaneJumpLds / 64];
+#pragma unroll
+        for (int i = 0; i < kLaneJumpLds / 64; ++i) v[i] = tab.xs32_pow[64 * i + lane];
+#pragma unroll
+        for (int i = 0; i < kLaneJumpLds / 64; ++i) lds[64 * i + lane] = v[i];
+        asm volatile("" ::: "memory");
+    }
     if constexpr (kMwc16) {  // one step is a; a 2^48 = 2^32 (mod a 2^16 - 1)
         const uint32_t m1 = g.a1 * 65536u - 1u, m2 = g.a2 * 65536u - 1u;
         cz = (0u - m1) % m1;
         cw = (0u - m2) % m2;
     }
-#pragma unroll 2
+#pragma unroll 1
     for (int b = 0; b < nb; ++b) {
         const bool on = (k >> b) & 1;
-        const bool any = __ballot(on) != 0;  // uniform
-        if (any) {
+        if (__ballot(on)) {  // uniform
             if constexpr (G::kId == G_MWC32) {
-                const uint64_t z = (uint64_t)g.c << 32 | g.x;
-                const uint64_t r = mwc32_mulmod(z, uniform_read(tab.mwc32_pow + b), tab.mwc32_a, tab.mwc32_m);
+                const uint64_t c = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(power >> 32), b) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)power, b);
+                const uint64_t r = mwc32_mulmod((uint64_t)g.c << 32 | g.x, c, tab.mwc32_a, tab.mwc32_m);
                 g.x = on ? (uint32_t)r : g.x;
                 g.c = on ? (uint32_t)(r >> 32) : g.c;
             }
-            if constexpr (G::kId == G_XS32) {
-                const uint32_t r = gf2_apply32(tab.xs32_pow + b * 32, g.y);
-                g.y = on ? r : g.y;
+            if constexpr (kXs32) {
+                uint32_t y;
+                if constexpr (G::kId == G_KISS) y = g.jsr;
+                else y = g.y;
+                const uint4 *m = (const uint4 *)(lds + 32 * b);
+                uint32_t r = 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint4 c = m[i];
+                    r ^= c.x & (uint32_t)__builtin_amdgcn_sbfe((int)y, 4 * i, 1);
+                    r ^= c.y & (uint32_t)__builtin_amdgcn_sbfe((int)y, 4 * i + 1, 1);
+                    r ^= c.z & (uint32_t)__builtin_amdgcn_sbfe((int)y, 4 * i + 2, 1);
+                    r ^= c.w & (uint32_t)__builtin_amdgcn_sbfe((int)y, 4 * i + 3, 1);
+                }
+                y = on ? r : y;
+                if constexpr (G::kId == G_KISS) g.jsr = y;
+                else g.y = y;
             }
             if constexpr (kMwc16) {
                 const uint32_t z = mwc16_mulmod(g.z, cz, g.a1), w = mwc16_mulmod(g.w, cw, g.a2);
                 g.z = on ? z : g.z;
                 g.w = on ? w : g.w;
             }
-            if constexpr (G::kId == G_KISS) {
-                const uint32_t r = gf2_apply32(tab.xs32_pow + b * 32, g.jsr);
-                g.jsr = on ? r : g.jsr;
-                g.jcong = on ? a * g.jcong + d : g.jcong;
-            }
+            if constexpr (G::kId == G_KISS) g.jcong = on ? a * g.jcong + d : g.jcong;
         }
         if constexpr (kMwc16) {
             cz = mwc16_mulmod(cz, cz, g.a1);
@@ -135,6 +160,7 @@ __device__ __forceinline__ void lane_jump(G &g, uint32_t k, int nb, const DevTab
         d = a * d + d;
         a *= a;
     }
+    asm volatile("" ::: "memory");
 }
 
 }  // namespace rngx
