@@ -464,6 +464,25 @@ int split_scratch_bytes(int g, uint64_t total, uint64_t n_threads, uint64_t *byt
     return RNG_OK;
 }
 
+// Windows of the fused consumer: blocks as long as leave a window for each of
+// 2048 waves and two for each stream (a start costs 3 to 8 us, a number of each
+// lane about 25 ns, and the last window is part empty), none shorter than 64
+// numbers; none at all for streams too short for lanes.  XS256 up to 8192 streams
+// (us, chunks / windows: 1 x 4 10^6 195 / 20, 1000 x 10^4 227 / 29, 10^4 x 10^4
+// 191 / 182, 2 10^4 x 5000 165 / 285).
+static void fused_windows(uint64_t S, uint64_t N, FusedArgs &a)
+{
+    if (N < 256) return;
+    uint32_t lg = 12;
+    while (lg > 6 && (S * ((N + ((uint64_t)64 << lg) - 1) >> (lg + 6)) < 2048 || ((uint64_t)128 << lg) > N)) --lg;
+    const uint64_t nwin = (N + ((uint64_t)64 << lg) - 1) >> (lg + 6);
+    uint64_t p = 4096 / S ? 4096 / S : 1;
+    if (p > nwin) p = nwin;
+    a.windows = 1;
+    a.lgc = lg;
+    a.P = (uint32_t)p;
+}
+
 }  // namespace rngx
 
 using namespace rngx;
@@ -630,15 +649,11 @@ int rng_fused_pi(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, uint6
     a.N = n;
     a.count = d_count;
     a.tab = tab;
-    if (n_streams < 64) {
-        lane_chunks(g, n_streams, n, &a.C, &a.P);
-        a.lanes = a.P > 1;
-    } else {
-        choose_chunks(g, n_streams, n, 8, &a.C, &a.P, (uint64_t)1 << 17);
-    }
-    if (a.P == 1) a.C = n;
+    choose_chunks(g, n_streams, n, 8, &a.C, &a.P, (uint64_t)1 << 17);
+    if (n_streams < 64 || (g == RNG_XS256 && n_streams <= 8192)) fused_windows(n_streams, n, a);
+    if (!a.windows && a.P == 1) a.C = n;
     if (int rc = check_launch(dispatch_fused(g, a, (hipStream_t)stream), "rng_fused_pi")) return rc;
-    if (a.P == 1) return RNG_OK;
+    if (!a.windows && a.P == 1) return RNG_OK;
     return check_launch(dispatch_skip(g, d_state, n_streams, n_streams, n, tab, (hipStream_t)stream),
                         "rng_fused_pi: state");
 }

@@ -72,9 +72,10 @@ struct FusedArgs {
     uint32_t *state;
     uint64_t ld;
     uint64_t S, N;
-    uint64_t C;  // even chunk length
-    uint32_t P;
-    uint32_t lanes;  // fewer streams than lanes: lane v takes chunk v mod P of stream v / P
+    uint64_t C;        // even chunk length
+    uint32_t P;        // chunks per stream, or waves per stream
+    uint32_t windows;  // windows of 64 blocks of 2^lgc numbers, a block per lane
+    uint32_t lgc;
     uint64_t *count;
     DevTables tab;
 };

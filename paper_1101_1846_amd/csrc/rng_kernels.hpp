@@ -10,6 +10,7 @@
 #include "rng_device.hpp"
 #include "rng_internal.hpp"
 #include "rng_aux_kernels.hpp"
+#include "wave_starts.hpp"
 
 namespace rngx {
 
@@ -580,44 +581,13 @@ __device__ __forceinline__ uint32_t outside_quarter_circle(uint32_t x, uint32_t 
 // Pairs (u_{2k}, u_{2k+1}) -> i = u >> 8, j = u >> 8; count i^2 + j^2 < 2^48,
 // as the pairs less those outside.  Chunk lengths are even so that pairs never
 // straddle chunks.
-template <class G, int WG, int U>
-__global__ __launch_bounds__(WG) void k_fused_pi(FusedArgs a)
+template <class G, int U>
+__device__ __forceinline__ uint64_t count_pairs(G &g, uint64_t n)
 {
     static_assert(U % 2 == 0, "pairs");
-    constexpr int NW = WG / 64;
     constexpr bool kMad = G::kId != G_XS256 && G::kId != G_XS32;
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t wave = (uint64_t)blockIdx.x * NW + wv;
-    uint64_t s, kb, ke;
-    bool valid;
-    if (a.lanes) {
-        // one chunk per lane: its own stream, start and (per-lane) jump
-        const uint64_t total_chunks = a.S * a.P, v = wave * 64 + lane;
-        if (wave * 64 >= total_chunks) return;  // whole waves
-        valid = v < total_chunks;
-        s = valid ? v / a.P : 0;
-        kb = valid ? (v - s * a.P) * a.C : 0;
-        ke = valid ? min(kb + a.C, a.N) : 0;
-    } else {
-        const uint64_t sb = wave / a.P, j = wave - sb * a.P;
-        const uint64_t s0 = sb * 64;
-        if (s0 >= a.S) return;
-        kb = j * a.C;
-        if (kb >= a.N) return;
-        ke = min(kb + a.C, a.N);
-        const uint32_t rows = (uint32_t)min<uint64_t>(64, a.S - s0);
-        valid = (uint32_t)lane < rows;
-        s = valid ? s0 + lane : s0;
-    }
-
-    G g;
-    g.load(a.state, a.ld, s, a.tab);
-    if (kb) g.jump(kb, a.tab);
-
-    const uint64_t n = ke - kb;
     const uint64_t full = n / U;
-    uint64_t total = 0;
+    uint64_t outside = 0;
     uint32_t cnt = 0;
     for (uint64_t it = 0; it < full; ++it) {
 #pragma unroll
@@ -625,20 +595,83 @@ __global__ __launch_bounds__(WG) void k_fused_pi(FusedArgs a)
             const uint32_t x = g.next() >> 8, y = g.next() >> 8;
             cnt += outside_quarter_circle<kMad>(x, y);
         }
-        if ((it & 0xFFFF) == 0xFFFF) { total += cnt; cnt = 0; }
+        if ((it & 0xFFFF) == 0xFFFF) {
+            outside += cnt;
+            cnt = 0;
+        }
     }
     for (uint64_t r = full * U; r + 1 < n; r += 2) {
         const uint32_t x = g.next() >> 8, y = g.next() >> 8;
         cnt += outside_quarter_circle<kMad>(x, y);
     }
     if (n & 1) g.next();
-    total = n / 2 - (total + cnt);
-    if (!valid) total = 0;
-    // wave reduction, one 64-bit atomic per wave
+    return n / 2 - (outside + cnt);
+}
+
+// Adds every lane's count, one 64-bit atomic per workgroup: with one per wave,
+// the atomics of a short call (10^5 streams x 100, 1563 waves) on one address
+// took 20 of its 29 us.  Every lane of the workgroup takes part.
+template <int WG>
+__device__ __forceinline__ void add_counts(uint64_t mine, uint64_t *count)
+{
+    __shared__ uint64_t s_sum[WG / 64];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
-    if (lane == 0 && total) atomicAdd((unsigned long long *)a.count, (unsigned long long)total);
-    if (valid && a.P == 1) g.store(a.state, a.ld, s);  // P > 1: the host skips the states by N
+    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t sum = 0;
+        for (int i = 0; i < WG / 64; ++i) sum += s_sum[i];
+        if (sum) atomicAdd((unsigned long long *)count, (unsigned long long)sum);
+    }
+}
+
+template <class G, int WG, int U>
+__global__ __launch_bounds__(WG) void k_fused_pi(FusedArgs a)
+{
+    constexpr int NW = WG / 64;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t wave = (uint64_t)blockIdx.x * NW + wv;
+    const uint64_t sb = wave / a.P, j = wave - sb * a.P, s = sb * 64 + lane;
+    const uint64_t kb = j * a.C;
+    uint64_t mine = 0;
+    if (s < a.S && kb < a.N) {
+        G g;
+        g.load(a.state, a.ld, s, a.tab);
+        if (kb) g.jump(kb, a.tab);
+        mine = count_pairs<G, U>(g, min(kb + a.C, a.N) - kb);
+        if (a.P == 1) g.store(a.state, a.ld, s);  // P > 1: the host skips the states by N
+    }
+    add_counts<WG>(mine, a.count);
+}
+
+// Few streams, and XS256 in chunks: windows of 64 blocks of 2^lgc numbers, a
+// block per lane, whose starts the wave spreads from the stream's state
+// (wave_starts.hpp); wave p of a stream's wp takes windows p, p + wp, ...  A
+// chunk per lane, each jumped on its own, spent 20 us (KISS) to 240 us (XS256)
+// on constants and tables before its first number.
+template <class G, int WG, int U>
+__global__ __launch_bounds__(WG) void k_fused_pi_windows(FusedArgs a)
+{
+    constexpr int NW = WG / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t s_lds[NW][kWaveStartLds];
+    const int lane = threadIdx.x & 63;
+    const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t wave = (uint64_t)blockIdx.x * NW + wv;
+    const uint64_t s = wave / a.P, p = wave - s * a.P, nwin = (a.N + ((uint64_t)64 << a.lgc) - 1) >> (a.lgc + 6);
+    uint64_t mine = 0;
+    if (s < a.S) {
+#pragma unroll 1
+        for (uint64_t t = p; t < nwin; t += a.P) {
+            G g;
+            load_uniform(g, a.state, a.ld, s);
+            wave_starts(g, t << (a.lgc + 6), a.lgc, s_lds[wv], lane, a.tab);
+            const uint64_t at = (t << (a.lgc + 6)) + ((uint64_t)lane << a.lgc);
+            if (at < a.N) mine += count_pairs<G, U>(g, min(a.N - at, (uint64_t)1 << a.lgc));
+        }
+    }
+    add_counts<WG>(mine, a.count);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -743,11 +776,13 @@ int launch_generate_t(int dt, const GenArgs &a, int wg, int unroll, bool staged,
 template <class G>
 int launch_fused_pi_t(const FusedArgs &a, hipStream_t stream)
 {
-    constexpr int WG = 256;
-    const uint64_t waves = a.lanes ? (a.S * a.P + 63) / 64 : ((a.S + 63) / 64) * a.P;
+    constexpr int WG = 256, U = G::kId != G_XS256 && G::kId != G_XS32 ? 16 : 8;
+    const uint64_t waves = a.windows ? a.S * a.P : ((a.S + 63) / 64) * a.P;
     const uint64_t blocks = (waves + WG / 64 - 1) / (WG / 64);
-    constexpr int U = G::kId != G_XS256 && G::kId != G_XS32 ? 16 : 8;
-    hipLaunchKernelGGL((k_fused_pi<G, WG, U>), dim3((unsigned)blocks), dim3(WG), 0, stream, a);
+    if (a.windows)
+        hipLaunchKernelGGL((k_fused_pi_windows<G, WG, U>), dim3((unsigned)blocks), dim3(WG), 0, stream, a);
+    else
+        hipLaunchKernelGGL((k_fused_pi<G, WG, U>), dim3((unsigned)blocks), dim3(WG), 0, stream, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
