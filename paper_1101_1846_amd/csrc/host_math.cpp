@@ -174,15 +174,39 @@ struct Gf2Poly {
     uint64_t w[4];
 };
 
-// a b mod (x^256 + f).
+// x a mod (x^256 + f).
+static Gf2Poly poly_mulx(Gf2Poly a, const Gf2Poly &f)
+{
+    const uint64_t top = 0 - (a.w[3] >> 63);
+    for (int k = 3; k > 0; --k) a.w[k] = (a.w[k] << 1) | (a.w[k - 1] >> 63);
+    a.w[0] <<= 1;
+    for (int k = 0; k < 4; ++k) a.w[k] ^= f.w[k] & top;
+    return a;
+}
+
+// The 16 products of a by the polynomials of degree below 4.
+static void poly_nibbles(const Gf2Poly &a, const Gf2Poly &f, Gf2Poly (&t)[16])
+{
+    t[0] = Gf2Poly{{0, 0, 0, 0}};
+    t[1] = a;
+    for (int v = 2; v < 16; v *= 2) {
+        t[v] = poly_mulx(t[v / 2], f);
+        for (int u = 1; u < v; ++u)
+            for (int k = 0; k < 4; ++k) t[v + u].w[k] = t[v].w[k] ^ t[u].w[k];
+    }
+}
+
+// a b mod (x^256 + f), four bits of b at a time.
 static Gf2Poly poly_mulmod(const Gf2Poly &a, const Gf2Poly &b, const Gf2Poly &f)
 {
-    Gf2Poly r{{0, 0, 0, 0}};
-    for (int i = 255; i >= 0; --i) {
-        const uint64_t top = 0 - (r.w[3] >> 63), on = 0 - ((b.w[i / 64] >> (i % 64)) & 1);
-        for (int k = 3; k > 0; --k) r.w[k] = (r.w[k] << 1) | (r.w[k - 1] >> 63);
-        r.w[0] <<= 1;
-        for (int k = 0; k < 4; ++k) r.w[k] ^= (f.w[k] & top) ^ (a.w[k] & on);
+    Gf2Poly ta[16], tf[16], r{{0, 0, 0, 0}};
+    poly_nibbles(a, f, ta);
+    poly_nibbles(f, f, tf);  // v x^256
+    for (int i = 63; i >= 0; --i) {
+        const Gf2Poly &over = tf[r.w[3] >> 60], &add = ta[(b.w[i / 16] >> (4 * (i % 16))) & 15];
+        for (int k = 3; k > 0; --k) r.w[k] = (r.w[k] << 4) | (r.w[k - 1] >> 60);
+        r.w[0] <<= 4;
+        for (int k = 0; k < 4; ++k) r.w[k] ^= over.w[k] ^ add.w[k];
     }
     return r;
 }
@@ -298,6 +322,17 @@ static HostTables *build_tables()
         }
         xp = poly_mulmod(xp, xp, f);
     }
+    std::memcpy(T->xs256_char, f.w, sizeof(f.w));
+    T->xs256_digit.resize((size_t)16 * 15 * 8);
+    xp = Gf2Poly{{2, 0, 0, 0}};  // x^(16^j)
+    for (int j = 0; j < 16; ++j) {
+        Gf2Poly c{{1, 0, 0, 0}};
+        for (int d = 1; d <= 15; ++d) {
+            c = poly_mulmod(c, xp, f);
+            std::memcpy(&T->xs256_digit[((size_t)j * 15 + (d - 1)) * 8], c.w, sizeof(c.w));
+        }
+        xp = poly_mulmod(c, xp, f);
+    }
     return T;
 }
 
@@ -318,6 +353,22 @@ const HostTables &host_tables()
 {
     static HostTables *T = build_tables();
     return *T;
+}
+
+void xs256_jump_poly(uint64_t k, uint32_t poly[8])
+{
+    const HostTables &T = host_tables();
+    Gf2Poly f, c{{1, 0, 0, 0}}, x;
+    std::memcpy(f.w, T.xs256_char, sizeof(f.w));
+    bool first = true;
+    for (int j = 0; j < 16; ++j) {
+        const int d = (int)(k >> (4 * j)) & 15;
+        if (!d) continue;
+        std::memcpy(x.w, &T.xs256_digit[((size_t)j * 15 + (d - 1)) * 8], sizeof(x.w));
+        c = first ? x : poly_mulmod(c, x, f);
+        first = false;
+    }
+    std::memcpy(poly, c.w, sizeof(c.w));
 }
 
 uint64_t mwc32_fold_const(uint64_t k)

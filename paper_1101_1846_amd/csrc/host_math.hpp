@@ -51,6 +51,8 @@ struct HostTables {
     std::vector<uint32_t> xs256_t4;            // [64][64][2][16][4]: 4-bit lookup tables of M^(2^b)
     std::vector<uint32_t> xs256_t4w;           // [16][15][8192]: 4-bit lookup tables of M^(d 16^j), d = 1..15
     std::vector<uint32_t> xs256_poly;          // [8][64][8]: x^(l 2^j) mod the step's characteristic polynomial, j = 5..12
+    uint32_t xs256_char[8];                    // that polynomial less x^256
+    std::vector<uint32_t> xs256_digit;         // [16][15][8]: x^(d 16^j) mod it
 };
 
 // 4-bit lookup table of a 256x256 GF(2) matrix given by its 256 columns of 8
@@ -63,6 +65,9 @@ const HostTables &host_tables();
 // Constants of a k-step map, composed from the power tables on the host (for
 // the kernels that move many states, or many threads, by one distance).
 uint64_t mwc32_fold_const(uint64_t k);
+// x^k mod the characteristic polynomial of the XS256 step (one product per
+// nonzero hexadecimal digit of k after the first, 0.3 us each).
+void xs256_jump_poly(uint64_t k, uint32_t poly[8]);
 // Columns of M^k for xorshift32 (eq. (6)) and the (A_k, C_k) of k LCG steps.
 void xs32_lcg_jump(uint64_t k, uint32_t cols[32], uint32_t *lcg_a, uint32_t *lcg_c);
 

@@ -9,13 +9,15 @@
 //   XS32     M^k y by four byte lookups                     (host columns, LDS tables)
 //   XS256    M^k v by 64 nibble lookups                     (LDS table of M^k)
 //   LCG      X <- A_k X + C_k                               (host constants)
-// The XS256 table is built per workgroup: thread c carries column c of the
-// identity through the staged table of M^(d 16^j) for every nonzero
-// hexadecimal digit d at position j of k, and the 256 columns then give the
-// nibble table of M^k.  That costs a few us per nonzero digit of k whatever
-// the number of states, so below kXs256TableMin states every state jumps on
-// its own (one product per nonzero digit, from the global tables), which is
-// as fast there and has a lower latency floor.
+// The XS256 table is built per workgroup from the columns of M^k, each the sum of
+// up to 256 steps of a unit state weighted by x^k mod the step's characteristic
+// polynomial, whose coefficients the host works out (a few hundred ns per
+// nonzero hexadecimal digit of k).  With a chain of table products, one per
+// digit, in its place, the launch took 37 us for 2^20 states and a k of four
+// digits, now 34 (its look-ups take the rest), and 33 for 2^16 states and a k of
+// ten digits, now 16.  Below kXs256TableMin states (10^4: 17 us against 22) each
+// takes its own products, one per nonzero digit, by the lane or, for few,
+// by a whole wave.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -29,20 +31,19 @@ namespace rngx {
 namespace {
 
 constexpr int kSkipWG = 256;
-// XS256 workgroups take 1024 lanes: the first 256 carry one column of M^k
-// each while the table is built, then all of them apply it (16 waves per CU
-// share the LDS reads; with four, each wave's products ran one after the
-// other and the launch took 0.10 ms for 2^20 states).  Splitting each
-// column's products over the four lanes of a quad (nibbles 4m + s on lane s,
-// partial sums combined by DPP) made it slower, 84 against 70 us: the four
-// lanes read four table rows at once, whose entries share LDS banks.
+// XS256 workgroups take 1024 lanes: four to a column of M^k while the table is
+// built, and 16 waves per CU share the LDS reads when they apply it.  (Splitting
+// a product's nibbles over the four lanes of a quad reads four table rows at
+// once, whose entries share LDS banks; products on the matrix cores, as parities
+// of FP4 sums, take longer over packing the bits than the look-ups: 25 against
+// 16 us per 2^20 states.)
 constexpr int kSkipXs256WG = 1024;
 template <class G>
 constexpr int skip_wg()
 {
     return G::kId == G_XS256 ? kSkipXs256WG : kSkipWG;
 }
-constexpr uint64_t kXs256TableMin = (uint64_t)1 << 16;
+constexpr uint64_t kXs256TableMin = (uint64_t)1 << 13;
 
 struct SkipArgs {
     uint32_t *st;           // [W][ld]
@@ -50,6 +51,7 @@ struct SkipArgs {
     uint64_t mwc32_f;       // a^k * 2^64 mod m (fold domain)
     uint32_t lcg_a, lcg_c;  // k steps of the LCG
     uint32_t xs32[32];      // columns of M^k, xorshift32
+    uint64_t poly[4];       // x^k mod the characteristic polynomial of the XS256 step
     DevTables tab;
 };
 
@@ -79,7 +81,7 @@ __global__ __launch_bounds__(skip_wg<G>()) void k_skip_by(SkipArgs a)
     __shared__ uint16_t s_t392[kMwc16 ? kMwc16Count : 1];
     __shared__ uint32_t s_c16[kMwc16 ? kMwc16Count : 1];  // a_i^k * 2^48 mod m_i
     __shared__ uint32_t s_t8[kXs32 ? 1024 : 1];           // byte tables of the xorshift32 M^k
-    __shared__ uint4 s_t4[kXs256 ? 2 * 2048 : 1];          // staged M^(2^b) (two buffers), then M^k
+    __shared__ uint4 s_t4[kXs256 ? 2048 : 1];              // partial columns, then the table of M^k
     __shared__ uint32_t s_col[kXs256 ? 256 * 8 : 1];       // columns of M^k
     const uint32_t tid = threadIdx.x;
     if constexpr (kMwc16) {
@@ -104,43 +106,43 @@ __global__ __launch_bounds__(skip_wg<G>()) void k_skip_by(SkipArgs a)
         }
     }
     if constexpr (kXs256) {
-        const bool colt = tid < 256;  // thread c < 256 carries column c
-        uint32_t col[8];
+        // Column c of M^k is the XOR of M^i e_c over the set bits i of x^k mod
+        // the characteristic polynomial: threads c, 256 + c, ... take 64 of the
+        // 256 steps each, from the columns of M^64, M^128 and M^192 (entries of
+        // single bits in those tables).
+        const uint32_t c = tid & 255, seg = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 8);
+        GenXS256 g;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) col[i] = (uint32_t)(tid / 32 == (uint32_t)i) << (tid % 32);
-        // Nonzero hexadecimal digits of k in increasing position (uniform: k
-        // is the same for every thread).  The table of the next one is loaded
-        // into registers while the current one is applied; buffer b & 1 is
-        // rewritten only after the barrier that follows the previous write,
-        // which every thread reaches after applying what that buffer held.
-        constexpr int Q = 2048 / WG;
-        uint32_t rest = 0;  // non-zero: the host returns before launching for k = 0
-        for (int j = 0; j < 16; ++j)
-            if ((a.k >> (4 * j)) & 15) rest |= 1u << j;
-        auto table = [&](int j) {
-            return a.tab.xs256_t4w + ((size_t)j * 15 + (((a.k >> (4 * j)) & 15) - 1)) * 2048;
-        };
-        uint4 pre[Q];
-        const uint4 *src = table(__builtin_ctz(rest));
-#pragma unroll
-        for (int i = 0; i < Q; ++i) pre[i] = src[tid + i * WG];
-        for (uint32_t buf = 0;; buf ^= 1) {
-            uint4 *t = s_t4 + buf * 2048;
-#pragma unroll
-            for (int i = 0; i < Q; ++i) t[tid + i * WG] = pre[i];
-            __syncthreads();
-            rest &= rest - 1;
-            if (rest) {
-                src = table(__builtin_ctz(rest));
-#pragma unroll
-                for (int i = 0; i < Q; ++i) pre[i] = src[tid + i * WG];
-            }
-            if (colt) gf2_apply256_t4(t, col);
-            if (!rest) break;
+        for (int i = 0; i < 8; ++i) g.v[i] = (uint32_t)(c / 32 == (uint32_t)i) << (c % 32);
+        if (seg) {
+            const uint4 *T = a.tab.xs256_t4w + ((size_t)15 + 4 * seg - 1) * 2048 + (c >> 2) * 32 + (1u << (c & 3));
+            const uint4 lo = T[0], hi = T[16];
+            g.v[0] = lo.x;
+            g.v[1] = lo.y;
+            g.v[2] = lo.z;
+            g.v[3] = lo.w;
+            g.v[4] = hi.x;
+            g.v[5] = hi.y;
+            g.v[6] = hi.z;
+            g.v[7] = hi.w;
         }
-        if (colt)
+        uint32_t col[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        uint64_t bits = a.poly[seg];  // uniform
+#pragma unroll 1
+        for (int i = 0; i < 64; i += 8, bits >>= 8)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s_col[tid * 8 + i] = col[i];
+            for (int b = 0; b < 8; ++b) {
+                if ((bits >> b) & 1)
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) col[k] ^= g.v[k];
+                g.next();
+            }
+        uint32_t *part = (uint32_t *)s_t4;  // [4][8][256]
+#pragma unroll
+        for (int i = 0; i < 8; ++i) part[(seg * 8 + i) * 256 + c] = col[i];
+        __syncthreads();
+        for (uint32_t e = tid; e < 2048; e += WG)  // word e / 256 of column e % 256
+            s_col[(e & 255) * 8 + (e >> 8)] = xor3(part[e], part[2048 + e], part[4096 + e]) ^ part[6144 + e];
         __syncthreads();
         // quad q = (2p + h) * 16 + v: words 4h .. 4h+3 of the XOR of columns 4p + j over the set bits j of v
         for (uint32_t q = tid; q < 2048; q += WG) {
@@ -279,6 +281,7 @@ int dispatch_skip(int g, uint32_t *st, uint64_t ld, uint64_t S, uint64_t k, cons
     a.k = k;
     a.tab = tab;
     if (g == RNG_MWC32) a.mwc32_f = mwc32_fold_const(k);
+    if (g == RNG_XS256 && S >= kXs256TableMin) xs256_jump_poly(k, (uint32_t *)a.poly);
     if ((g == RNG_XS32 || g == RNG_KISS) && S > kSkipWaveMax) xs32_lcg_jump(k, a.xs32, &a.lcg_a, &a.lcg_c);
     switch (g) {
     case RNG_MWC32: return launch_skip_by<GenMWC32>(a, s);
