@@ -293,8 +293,6 @@ static HostTables *build_tables()
         *M = (*M) * (*M);
     }
     delete M;
-    T->xs256_t4.resize((size_t)kPowBits * 8192);
-    for (int b = 0; b < kPowBits; ++b) xs256_nibble_table(&T->xs256_pow[(size_t)b * 2048], &T->xs256_t4[(size_t)b * 8192]);
     // One table per hexadecimal digit d != 0 at position j: a jump by k then
     // takes one product per nonzero digit of k instead of one per set bit.
     T->xs256_t4w.resize((size_t)16 * 15 * 8192);

@@ -48,7 +48,6 @@ struct HostTables {
     uint32_t xs32_pow[kPowBits][32];           // M^(2^b), 32 columns
     uint32_t mwc16_pow_fold[kMwc16Count][kPowBits];  // a_i^(2^b) * 2^48 mod m_i
     std::vector<uint32_t> xs256_pow;           // [64][256][8]: M^(2^b)
-    std::vector<uint32_t> xs256_t4;            // [64][64][2][16][4]: 4-bit lookup tables of M^(2^b)
     std::vector<uint32_t> xs256_t4w;           // [16][15][8192]: 4-bit lookup tables of M^(d 16^j), d = 1..15
     std::vector<uint32_t> xs256_poly;          // [8][64][8]: x^(l 2^j) mod the step's characteristic polynomial, j = 5..12
     uint32_t xs256_char[8];                    // that polynomial less x^256

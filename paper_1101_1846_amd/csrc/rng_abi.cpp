@@ -65,9 +65,7 @@ int device_tables(DevTables *out)
         const size_t o_lcg = o_m32 + 1024, n_lcg = sizeof(H.lcg_pow);
         const size_t o_x32 = o_lcg + 1024, n_x32 = sizeof(H.xs32_pow);
         const size_t o_m16 = o_x32 + n_x32, n_m16 = sizeof(H.mwc16_pow_fold);
-        const size_t o_x256 = (o_m16 + n_m16 + 255) & ~(size_t)255;
-        const size_t n_x256 = H.xs256_t4.size() * sizeof(uint32_t);
-        const size_t o_x256w = o_x256 + n_x256, n_x256w = H.xs256_t4w.size() * sizeof(uint32_t);
+        const size_t o_x256w = (o_m16 + n_m16 + 255) & ~(size_t)255, n_x256w = H.xs256_t4w.size() * sizeof(uint32_t);
         const size_t o_poly = o_x256w + n_x256w, n_poly = H.xs256_poly.size() * sizeof(uint32_t);
         const size_t total = o_poly + n_poly;
         std::string host(total, '\0');
@@ -76,7 +74,6 @@ int device_tables(DevTables *out)
         std::memcpy(&host[o_lcg], H.lcg_pow, n_lcg);
         std::memcpy(&host[o_x32], H.xs32_pow, n_x32);
         std::memcpy(&host[o_m16], H.mwc16_pow_fold, n_m16);
-        std::memcpy(&host[o_x256], H.xs256_t4.data(), n_x256);
         std::memcpy(&host[o_x256w], H.xs256_t4w.data(), n_x256w);
         std::memcpy(&host[o_poly], H.xs256_poly.data(), n_poly);
         void *blob = nullptr;
@@ -91,7 +88,6 @@ int device_tables(DevTables *out)
         d.tab.lcg_pow = (const uint32_t *)(b + o_lcg);
         d.tab.xs32_pow = (const uint32_t *)(b + o_x32);
         d.tab.mwc16_pow = (const uint32_t *)(b + o_m16);
-        d.tab.xs256_t4 = (const uint4 *)(b + o_x256);
         d.tab.xs256_t4w = (const uint4 *)(b + o_x256w);
         d.tab.xs256_poly = (const uint4 *)(b + o_poly);
         d.tab.mwc32_a = H.mwc32_a;

@@ -21,7 +21,6 @@ struct DevTables {
     const uint32_t *lcg_pow;       // [64][2] (A, C) of 2^b LCG steps
     const uint32_t *xs32_pow;      // [64][32] columns of M^(2^b)
     const uint32_t *mwc16_pow;     // [392][64] a_i^(2^b) * 2^48 mod m_i
-    const uint4 *xs256_t4;         // [64][64][2][16] 4-bit lookup tables of M^(2^b)
     const uint4 *xs256_t4w;        // [16][15][64][2][16] 4-bit lookup tables of M^(d 16^j), d = 1..15
     const uint4 *xs256_poly;       // [8][64][2] x^(l 2^j) mod the step's characteristic polynomial, j = 5..12
     uint32_t mwc32_a;              // 65274
@@ -151,23 +150,6 @@ __device__ __forceinline__ void gf2_apply256_t4(const uint4 *T, uint32_t (&x)[8]
     for (int i = 0; i < 8; ++i) x[i] = r[i];
 }
 
-// Copies NQ consecutive 16-byte quads (whole lookup tables of 2048 quads,
-// 32 KiB) into LDS with a workgroup of WG lanes, every global load issued
-// before the first LDS write: one memory round trip, where a loop strided by
-// the runtime workgroup size waits for each quad in turn.  The caller
-// synchronises before use.
-template <int WG, int NQ>
-__device__ __forceinline__ void stage_quads(uint4 *lds, const uint4 *T)
-{
-    static_assert(NQ % WG == 0, "whole rows of the workgroup");
-    constexpr int PER = NQ / WG;
-    uint4 v[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) v[i] = T[i * WG + threadIdx.x];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) lds[i * WG + threadIdx.x] = v[i];
-}
-
 // ---------------------------------------------------------------- generators
 enum { G_MWC32 = 1, G_XS256 = 2, G_XS32 = 3, G_KISS = 4, G_MWC1616 = 5 };
 
@@ -216,8 +198,6 @@ struct GenXS256 : rng_inline::XS256 {
             if (d) gf2_apply256_t4(tab.xs256_t4w + ((size_t)j * 15 + (d - 1)) * 2048, v);
         }
     }
-    // One jump by the power of two whose lookup table T holds (staged in LDS).
-    __device__ __forceinline__ void jump_table(const uint4 *T) { gf2_apply256_t4(T, v); }
     __device__ void seed(const uint64_t *d, const DevTables &)
     {
         uint32_t any = 0;
