@@ -98,11 +98,11 @@ int rng_seed(int g, uint64_t seed, uint64_t first_stream, uint64_t n_streams,
  * d_state [words][n_streams] in/out; d_out [n_streams][n] of dtype t, 4-byte
  * aligned (16-byte alignment with n % 4 == 0 takes 128-bit stores).
  * n = 0 or n_streams = 0 is a no-op.  When n_streams is small the library
- * splits each stream into chunks that start from jumped-ahead states, so the
- * output is still the serial sequence of every stream.  The states are then
- * written back only after every chunk has read them: inside the kernel when
- * one workgroup holds all chunks of its streams, else by a second launch on
- * the same stream that advances them by n. */
+ * splits each stream into chunks or windows of blocks that start from
+ * jumped-ahead states, so the output is still the serial sequence of every
+ * stream.  The states are then written back only after every chunk has read
+ * them: inside the kernel when one wave or workgroup holds all chunks of its
+ * streams, else by a second launch on the same stream that advances them by n. */
 int rng_generate(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, int t,
                  void *d_out, void *stream);
 
@@ -264,15 +264,13 @@ int rng_xs256_placement(int placement, uint32_t *d_state, uint64_t n_streams, ui
 
 /* ---------------------------------------------------------------------- */
 /* Batched generation: thousands of independent requests of uneven length  */
-/* in one persistent generation launch (after the root and tree launches,   */
-/* issued directly or replayed as a captured HIP graph).  Each request is a */
-/* slice [offset, offset + length) of one stream's serial sequence; the     */
-/* stream's state is advanced by offset + length.  Requests are cut into    */
-/* chunks of C samples whose start states come from jump-ahead: one jump    */
-/* per request, then a radix-16 tree (level l starts chunk q 16^l + r from  */
-/* chunk r, q < 16: at most four jumps by powers of two per chunk; level 0  */
-/* in the root's launch, one launch per further level); a persistent kernel */
-/* pulls 64-chunk tiles from an atomic counter.                             */
+/* in one persistent generation launch (after the root launch, issued       */
+/* directly or replayed as a captured HIP graph).  Each request is a slice  */
+/* [offset, offset + length) of one stream's serial sequence; the stream's  */
+/* state is advanced by offset + length.  Requests are cut into chunks of C */
+/* samples, 64 of them to a tile; the persistent kernel's waves pull tiles  */
+/* from an atomic counter, jump the request's state to the tile and start   */
+/* their lanes from it.                                                     */
 /* ---------------------------------------------------------------------- */
 typedef struct {
     int32_t gen;            /* rng_gen_t */

@@ -209,8 +209,6 @@ static uint64_t min_chunk(int g)
     return 1u << 30;
 }
 
-// Split each stream into P chunks when there are too few streams to fill the
-// chip (256 CUs x 4 SIMDs; aim for >= 2 waves per SIMD).
 // Fewer streams than a wave has lanes: one lane per chunk, about 2^17 lanes,
 // chunks a multiple of 64 samples and at least the generator's minimum.
 void lane_chunks(int g, uint64_t S, uint64_t N, uint64_t *C, uint32_t *P)
@@ -222,12 +220,15 @@ void lane_chunks(int g, uint64_t S, uint64_t N, uint64_t *C, uint32_t *P)
     *P = (uint32_t)((N + c - 1) / c);
 }
 
-// Lanes that chunked bulk generation aims for: the waves the device holds at
+// Lanes that chunked bulk generation by k_generate aims for (shapes of more than
+// 256 lanes; XS256 above the sequences' stream counts): the waves the device holds at
 // once with 128-deep LDS tiles (4 per CU, 256 CUs) times 64.  Measured
 // against 2^17 and 2^15 over 64..65536 streams: 2^16 is 15-40 % faster than
 // 2^17 for MWC32 and KISS and equal for XS256; 2^15 slows XS256 and KISS.
 constexpr uint64_t kGenLanes = (uint64_t)1 << 16;
 
+// Split each stream into P chunks when there are too few streams to fill the
+// chip (256 CUs x 4 SIMDs; aim for >= 2 waves per SIMD).
 void choose_chunks(int g, uint64_t S, uint64_t N, uint64_t align, uint64_t *C, uint32_t *P, uint64_t target_lanes)
 {
     uint64_t p = 1;
@@ -341,10 +342,44 @@ static void rot_constants(int g, uint64_t N, GenArgs &a)
 // (10^4 x 25001 525 / 358).
 static bool seq_streams(int g, uint64_t S, uint64_t N, const void *out)
 {
+    // the cheap generators' windows outrun their chunks later (XS32 1000 x 8192
+    // 14.7 / 16.4, 1000 x 16384 19.5 / 19.0)
+    if ((g == RNG_XS32 || g == RNG_MWC32) && S > kSeqWaves / 2 && N < 16384) return false;
     if (g != RNG_XS256) return S <= kSeqWaves && N >= 8192;
     if (S <= kSeqWaves) return N >= 512;
     if (S <= 4 * kSeqWaves && N >= 2048 && N < 16384) return true;
     return N >= 16384 && S <= ((uint64_t)1 << 24) && (N % 32 != 0 || ((uintptr_t)out & 127));
+}
+
+// Rows that k_generate takes although they are no whole tiles: short ones, whose
+// heads and last tiles, which do not overlap their stores, cost more line by line
+// (rows.hip) than the partial lines do while these stay in the caches.
+//   whole lines: XS256 x 96 (us, k_generate / k_rows: 7.1 / 7.8 for 1000 rows), and
+//     short rows that fill the lanes (XS32 65536 x 96 -10 %, 8192 x 512 7.5 / 8.6);
+//   rows that begin inside 16 bytes: below 128 numbers (XS256 1000 x 75 10.9 / 13.4),
+//     as k_generate then stores word by word (XS32 1000 x 203 twice as long);
+//   else by how many numbers a lane's start and a number's steps are worth: XS256
+//     1000 x 340 16.3 / 21.2, 13810 x 776 -7 %, but x 3000 +22 %; KISS 1000 x 168 -17 %,
+//     x 300 +5 %, 40000 x 776 -6 %; MWC1616 1000 x 300 -17 %, x 460 +25 %, 13810 x 776
+//     -6 %; XS32 8192 x 340 8.1 / 14.6, 2000 x 11000 -18 %, but 152 x 11000 +43 %;
+//     MWC32 13810 x 2500 -15 %, 40000 x 1300 -7 %, but 2000 x 50000 +22 %.
+// KISS's rows gain from every lane (1000 x 75 14.2 / 12.1).  More rows than lanes
+// never lose (MWC32 10^5 x 75 +54 %).
+static bool general_rows(int g, uint64_t S, uint64_t N, bool vec4, const void *out)
+{
+    if (S > 65536) return false;
+    const bool cheap = g == RNG_XS32 || g == RNG_MWC32;
+    if (N % 32 == 0 && !((uintptr_t)out & 127)) {
+        if (g == RNG_XS256) return N < 128;
+        return g != RNG_KISS && N <= 512 && (S > 32768 || (cheap && S * N >= (uint64_t)1 << 22));
+    }
+    if (!vec4) return N < 128 && g != RNG_KISS;
+    switch (g) {
+    case RNG_XS256: return N < 512 || (S > kSeqWaves && N < 1536);
+    case RNG_KISS: return N < (S > 16384 ? 1536 : 192);
+    case RNG_MWC1616: return S >= 64 && N < (S > 8192 ? 1536 : 400);
+    }
+    return S >= 64 && S * N < ((uint64_t)1 << 26) && (N < 8192 || S >= kSeqWaves / 2);
 }
 
 // Shared by rng_generate and the split path: one generate launch over
@@ -365,12 +400,13 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
     a.vec4 = (N % 4 == 0) && (((uintptr_t)d_out & 15) == 0);
     a.nt = 0;  // plain stores: the streaming hint measured slower for these writes
     a.tab = tab;
-    if (staged && seq_streams(g, S, N, d_out)) {
+    const bool general = !staged || (N <= kRowMax && general_rows(g, S, N, a.vec4, d_out));
+    if (!general && seq_streams(g, S, N, d_out)) {
         if (int e = check_launch(launch_seq(g, dt, d_state, ld, S, N, d_out, nullptr, tab, st), "rng_generate")) return e;
         return check_launch(dispatch_skip(g, d_state, ld, S, N, tab, st), "rng_generate: state");
     }
     uint32_t lgp, c;
-    if (staged && shape.wg <= 256 && N <= kRowMax && row_chunks(g, S, N, &lgp, &c))
+    if (!general && shape.wg <= 256 && N <= kRowMax && row_chunks(g, S, N, &lgp, &c))
         return check_launch(launch_rows(g, dt, d_state, ld, S, N, lgp, c, d_out, tab, st), "rng_generate");
     if (staged && S < 64) {
         uint64_t c;
@@ -402,7 +438,7 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
         a.rot = 1;
         rot_constants(g, N, a);
     }
-    if (staged && a.P == 1 && shape.wg <= 256 && N >= kRowMin && N <= kRowMax &&
+    if (!general && a.P == 1 && shape.wg <= 256 && N >= kRowMin && N <= kRowMax &&
         (!a.vec4 || S % 64 != 0 || N % kGenTile != 0))
         return check_launch(launch_rows(g, dt, d_state, ld, S, N, 0, (uint32_t)N, d_out, tab, st), "rng_generate");
     rc = dispatch_generate(g, dt, a, (int)shape.wg, (int)shape.unroll, staged, st);
@@ -463,14 +499,21 @@ int split_scratch_bytes(int g, uint64_t total, uint64_t n_threads, uint64_t *byt
 // Windows of the fused consumer: blocks as long as leave a window for each of
 // 2048 waves and two for each stream (a start costs 3 to 8 us, a number of each
 // lane about 25 ns, and the last window is part empty), none shorter than 64
-// numbers; none at all for streams too short for lanes.  XS256 up to 8192 streams
-// (us, chunks / windows: 1 x 4 10^6 195 / 20, 1000 x 10^4 227 / 29, 10^4 x 10^4
-// 191 / 182, 2 10^4 x 5000 165 / 285).
-static void fused_windows(uint64_t S, uint64_t N, FusedArgs &a)
+// numbers; none at all for streams too short for lanes.  Of the lengths that do,
+// the one with the fewest steps, a start counted as the 107 that it takes of a
+// full device.  XS256 up to 8192 streams (us, chunks / windows: 1 x 4 10^6 195 /
+// 20, 1000 x 10^4 227 / 29, 10^4 x 10^4 191 / 182, 2 10^4 x 5000 165 / 285), as
+// long as the last windows' idle lanes and the starts cost less than a chunk's
+// jump per lane, 170 us or 3 10^8 steps (7000 x 530637 2258 / 2882).
+static void fused_windows(int g, uint64_t S, uint64_t N, FusedArgs &a)
 {
     if (N < 256) return;
     uint32_t lg = 12;
     while (lg > 6 && (S * ((N + ((uint64_t)64 << lg) - 1) >> (lg + 6)) < 2048 || ((uint64_t)128 << lg) > N)) --lg;
+    auto steps = [&](uint32_t l) { return ((N + ((uint64_t)64 << l) - 1) >> (l + 6)) * 64 * (((uint64_t)1 << l) + 107); };
+    for (uint32_t l = lg; l >= 6; --l)
+        if (steps(l) < steps(lg)) lg = l;
+    if (g == RNG_XS256 && S >= 64 && S * (steps(lg) - N) > 300000000) return;
     const uint64_t nwin = (N + ((uint64_t)64 << lg) - 1) >> (lg + 6);
     uint64_t p = 4096 / S ? 4096 / S : 1;
     if (p > nwin) p = nwin;
@@ -646,7 +689,7 @@ int rng_fused_pi(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, uint6
     a.count = d_count;
     a.tab = tab;
     choose_chunks(g, n_streams, n, 8, &a.C, &a.P, (uint64_t)1 << 17);
-    if (n_streams < 64 || (g == RNG_XS256 && n_streams <= 8192)) fused_windows(n_streams, n, a);
+    if (n_streams < 64 || (g == RNG_XS256 && n_streams <= 8192)) fused_windows(g, n_streams, n, a);
     if (!a.windows && a.P == 1) a.C = n;
     if (int rc = check_launch(dispatch_fused(g, a, (hipStream_t)stream), "rng_fused_pi")) return rc;
     if (!a.windows && a.P == 1) return RNG_OK;

@@ -237,15 +237,22 @@ int launch_rows_t(int dt, const RowArgs &a, hipStream_t st)
 }  // namespace
 
 // Chunks of S streams of N numbers: as many as give every wave slot a group of
-// 64 (four waves per CU with chunks of at least kRowShort, eight with shorter
-// ones), of 64 numbers or more.  They are whole lines if that makes the last
-// one, which takes the rest, at most an eighth longer.  (A last chunk that is
-// shorter would take its whole group off the overlapped tiles.)
+// 64 (four waves per CU; eight with chunks below kRowShort of the generators whose
+// numbers cost most: MWC1616 13810 x 2500 +21 %, but XS32 -17 %), of 64 numbers or
+// more.  They are whole lines
+// if that makes the last one, which takes the rest, at most an eighth longer.  (A
+// last chunk that is shorter would take its whole group off the overlapped tiles.)
 bool row_chunks(int g, uint64_t S, uint64_t N, uint32_t *lgp, uint32_t *C)
 {
     uint32_t lg = 0;
-    while (lg < 6 && N >> (lg + 1) >= 64 && S << (lg + 1) <= (N >> (lg + 1) < kRowShort ? 2 : 1) * (uint64_t)65536) ++lg;
-    if (g == RNG_XS256 || lg == 0) return false;
+    if (g == RNG_XS256 || S > 65536) return false;
+    while (lg < 6) {
+        const uint64_t c = N >> (lg + 1), lanes = S << (lg + 1);
+        const bool two = (g == RNG_KISS || g == RNG_MWC1616) && c < kRowShort;
+        if (c < 64 || lanes > (two ? 2 : 1) * (uint64_t)65536) break;
+        ++lg;
+    }
+    if (lg == 0) return false;
     const uint64_t c = N >> lg, whole = c & ~(uint64_t)31;
     *lgp = lg;
     *C = (uint32_t)(8 * (N - (whole << lg)) <= whole ? whole : c);
