@@ -356,6 +356,9 @@ static bool seq_streams(int g, uint64_t S, uint64_t N, const void *out)
 // (rows.hip) than the partial lines do while these stay in the caches.
 //   whole lines: XS256 x 96 (us, k_generate / k_rows: 7.1 / 7.8 for 1000 rows), and
 //     short rows that fill the lanes (XS32 65536 x 96 -10 %, 8192 x 512 7.5 / 8.6);
+//   whole tiles: rows of two to four long chunks, which k_generate keeps 64 streams
+//     apart (MWC32 24576 x 8192 144 / 156, XS32 20032 x 8192 -26 %, KISS 28032 x 8192
+//     -23 %, but XS32 16384 x 2048 +11 %, 16384 x 16384 +17 %);
 //   rows that begin inside 16 bytes: below 128 numbers (XS256 1000 x 75 10.9 / 13.4),
 //     as k_generate then stores word by word (XS32 1000 x 203 twice as long);
 //   else by how many numbers a lane's start and a number's steps are worth: XS256
@@ -371,6 +374,7 @@ static bool general_rows(int g, uint64_t S, uint64_t N, bool vec4, const void *o
     const bool cheap = g == RNG_XS32 || g == RNG_MWC32;
     if (N % 32 == 0 && !((uintptr_t)out & 127)) {
         if (g == RNG_XS256) return N < 128;
+        if (N % kGenTile == 0 && N >= (g == RNG_KISS ? 4096 : 3072) && N < 12288 && S >= (cheap ? 8192 : 12289)) return true;
         return g != RNG_KISS && N <= 512 && (S > 32768 || (cheap && S * N >= (uint64_t)1 << 22));
     }
     if (!vec4) return N < 128 && g != RNG_KISS;

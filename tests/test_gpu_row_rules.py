@@ -35,7 +35,7 @@ def run(oracle, name, dt, S, N, off):
     ("u32", 8193, 400, 0), ("f32", 1024, 1532, 0), ("u32", 1025, 1532, 8), ("f32", 1025, 1536, 8), ("u32", 16385, 300, 0),
     ("f32", 70, 127, 1), ("u32", 70, 129, 1), ("f32", 33000, 96, 0), ("u32", 32768, 96, 0), ("f32", 65537, 100, 0),
     ("u32", 8191, 512, 0), ("f32", 8192, 512, 0), ("f32", 511, 8188, 0), ("u32", 513, 8192, 0), ("f32", 600, 16384, 0),
-    ("u32", 513, 16380, 0)])
+    ("u32", 513, 16380, 0), ("u32", 8192, 3072, 0), ("f32", 12289, 4096, 0), ("u32", 8200, 3104, 0)])
 def test_row_rules(oracle, name, dt, S, N, off):
     run(oracle, name, dt, S, N, off)
 
