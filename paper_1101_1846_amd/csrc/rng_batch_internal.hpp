@@ -30,6 +30,11 @@ struct BatchReq {
     uint32_t lgc;        // log2 of the row length
 };
 
+// A slice that ends beyond position 2^64 of its stream: a tile's position, the
+// offset and the samples before the tile, would not fit 64 bits, so the start
+// state is moved by the offset first and the tiles count from there.
+__device__ __forceinline__ bool batch_far(const BatchReq &q) { return q.offset + q.length < q.offset; }
+
 struct BatchGroup {
     uint32_t gen, dtype;
 };
