@@ -355,16 +355,30 @@ int launch_seq(int g, int dt, const uint32_t *state, uint64_t ld, uint64_t S, ui
     return -2;
 }
 
+// The start state is read, and the final one written, by any wave while others
+// store their numbers, so neither may lie in memory that the sequence writes: a
+// start state that the output or the final state overlaps is copied to ws first,
+// and a final state that the output or the start state in use overlaps is worked
+// out in ws (the start state moved by `total`) and copied to its place last.
 int seq_run(int g, const uint32_t *state_one, uint64_t total, int t, void *out, uint32_t *final_state, uint32_t *ws,
             const DevTables &tab, hipStream_t st)
 {
-    const uintptr_t a = (uintptr_t)state_one, b = (uintptr_t)final_state, n = (uintptr_t)gen_words(g) * 4;
-    if (a < b + n && b < a + n) {  // the wave that ends may write before others have read
+    const uint64_t words = (uint64_t)gen_words(g);
+    auto overlap = [](const void *p, uint64_t np, const void *q, uint64_t nq) {
+        return (uintptr_t)p < (uintptr_t)q + 4 * nq && (uintptr_t)q < (uintptr_t)p + 4 * np;
+    };
+    const uint32_t *start = state_one;
+    const bool late = overlap(final_state, words, out, total);
+    if (late || overlap(state_one, words, out, total) || overlap(state_one, words, final_state, words)) start = ws;
+    const bool by_ws = late || (start == ws && overlap(final_state, words, ws, words));
+    if (start != state_one)
         if (int rc = check_launch(dispatch_state_copy(g, state_one, 1, 0, ws, 1, 0, st), "sequence: start state"))
             return rc;
-        state_one = ws;
-    }
-    return check_launch(launch_seq(g, t, state_one, 1, 1, total, out, final_state, tab, st), "sequence");
+    if (int rc = check_launch(launch_seq(g, t, start, 1, 1, total, out, by_ws ? nullptr : final_state, tab, st), "sequence"))
+        return rc;
+    if (!by_ws) return RNG_OK;
+    if (int rc = check_launch(dispatch_skip(g, ws, 1, 1, total, tab, st), "sequence: final state")) return rc;
+    return check_launch(dispatch_state_copy(g, ws, 1, 0, final_state, 1, 0, st), "sequence: final state");
 }
 
 }  // namespace rngx
