@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kLaneWG) void k_generate_lanes(LaneArgs a)
             for (int k = 0; k < K; k += U) {
                 uint32_t w[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) w[u] = lane_bits<DT>(g.next());
+                for (int u = 0; u < U; ++u) w[u] = lane_bits<DT>(next_alone(g));
                 if constexpr (U % 4 == 0) {
 #pragma unroll
                     for (int u = 0; u < U; u += 4) *(uint4 *)&row[k + u] = make_uint4(w[u], w[u + 1], w[u + 2], w[u + 3]);
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kLaneWG) void k_generate_lanes(LaneArgs a)
                 }
             }
         } else if (k0 < len) {
-            for (uint32_t k = 0; k < len - k0; ++k) row[k] = lane_bits<DT>(g.next());
+            for (uint32_t k = 0; k < len - k0; ++k) row[k] = lane_bits<DT>(next_alone(g));
         }
         asm volatile("" ::: "memory");  // LDS writes before the transposed reads (one wavefront: in order)
         if (aligned) {

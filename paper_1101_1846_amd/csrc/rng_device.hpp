@@ -289,6 +289,27 @@ struct GenKISS : rng_inline::KISS {
     }
 };
 
+// g's next number in a loop that stores nothing meanwhile, where a wave waits for
+// its own chain.  KISS with the LCG step in C: after mad_lo, whose 64-bit result
+// leaves a register that the following instruction writes, that chain waits longer
+// than the instruction saves (us, mad_lo / C: 8192 x 96 at 16 bytes into a line,
+// u32 10.9 / 7.8, f32 9.1 / 8.3).
+template <class G>
+__device__ __forceinline__ uint32_t next_alone(G &g)
+{
+    if constexpr (G::kId == G_KISS) {
+        g.z = mwc16_step(g.z, g.a1);
+        g.w = mwc16_step(g.w, g.a2);
+        g.jcong = 69069u * g.jcong + 1234567u;
+        g.jsr ^= g.jsr << 13;
+        g.jsr ^= g.jsr >> 17;
+        g.jsr ^= g.jsr << 5;
+        return g.last();
+    } else {
+        return g.next();
+    }
+}
+
 // *p for a whole wave (p uniform) through the scalar cache, so that the result
 // is uniform to the compiler too; nothing in the launch may write it.
 template <class T>

@@ -110,12 +110,12 @@ __device__ __forceinline__ void store_tile(const uint32_t *tile, uint32_t *out, 
 // are held in VGPRs and their stores are spread evenly through the
 // generation of tile t + 1, so the write stream leaves the CU at a steady
 // rate while the VALU keeps generating.
-template <class G, int DT, int U>
+template <class G, int DT, int U, bool kAlone = false>
 __device__ __forceinline__ void gen_to_row(G &g, uint32_t *row, int k)
 {
     uint32_t v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = out_bits<DT>(g.next());
+    for (int u = 0; u < U; ++u) v[u] = out_bits<DT>(kAlone ? next_alone(g) : g.next());
     if constexpr (U % 4 == 0) {
 #pragma unroll
         for (int u = 0; u < U; u += 4) *(uint4 *)&row[k + u] = make_uint4(v[u], v[u + 1], v[u + 2], v[u + 3]);
@@ -515,9 +515,9 @@ __global__ __launch_bounds__(WG) void k_generate(GenArgs a)
             uint32_t *row = tile + lane * LD;
             if (cnt == K) {
 #pragma unroll 1
-                for (int k = 0; k < K; k += U) gen_to_row<G, DT, U>(g, row, k);
+                for (int k = 0; k < K; k += U) gen_to_row<G, DT, U, true>(g, row, k);
             } else {
-                for (uint32_t k = 0; k < cnt; ++k) row[k] = out_bits<DT>(g.next());
+                for (uint32_t k = 0; k < cnt; ++k) row[k] = out_bits<DT>(next_alone(g));
             }
             RNGX_COMPILER_FENCE();
             store_tile<K>(tile, out, s0, N, k0, rows, cnt, lane, a.vec4, a.nt);
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(WG) void k_generate(GenArgs a)
                 for (int k = 0; k < K; k += U) {
                     uint32_t v[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) v[u] = out_bits<DT>(g.next());
+                    for (int u = 0; u < U; ++u) v[u] = out_bits<DT>(next_alone(g));
                     if (valid) {
                         bool done = false;
                         if constexpr (U % 4 == 0) {
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(WG) void k_generate(GenArgs a)
                 }
             } else {
                 for (uint32_t k = 0; k < cnt; ++k) {
-                    uint32_t v = out_bits<DT>(g.next());
+                    uint32_t v = out_bits<DT>(next_alone(g));
                     if (valid) dst[k] = v;
                 }
             }
