@@ -289,6 +289,29 @@ struct GenKISS : rng_inline::KISS {
     }
 };
 
+// KISS whose MWC16 words step by a shift and a v_mad_u32_u16 (which reads the low
+// halves of both factors), the LCG in C: more instructions per number than
+// rng_inline::KISS's dot products.  For the whole-tile rows that are bound by
+// their stores and lose when these come faster (kiss_words_by_mad).
+struct GenKISSMad : GenKISS {
+    static __device__ __forceinline__ uint32_t word(uint32_t z, uint32_t a)
+    {
+        uint32_t r;
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(z), "v"(z >> 16));
+        return r;
+    }
+    __device__ __forceinline__ uint32_t next()
+    {
+        z = word(z, a1);
+        w = word(w, a2);
+        jcong = 69069u * jcong + 1234567u;
+        jsr ^= jsr << 13;
+        jsr ^= jsr >> 17;
+        jsr ^= jsr << 5;
+        return last();
+    }
+};
+
 // g's next number in a loop that stores nothing meanwhile, where a wave waits for
 // its own chain.  KISS with the LCG step in C: after mad_lo, whose 64-bit result
 // leaves a register that the following instruction writes, that chain waits longer

@@ -675,6 +675,23 @@ __global__ __launch_bounds__(WG) void k_fused_pi_windows(FusedArgs a)
 }
 
 // ------------------------------------------------------------------ launchers
+// Whole-tile KISS rows that take the longer step (GenKISSMad).  Beyond the 256 MiB
+// of the last-level cache the stores are the bound, and the pace that the step sets
+// between them decides by a few percent, either way; most sizes gain from the
+// shorter step (3 % over 340 sizes and both types).  These lose (longer / shorter
+// step's time):
+//   f32 rows of two tiles from 384 MiB to 1 GiB: 0.97-0.98 (2^20 x 256 194.4 / 199.5
+//     us), but 1.07-1.10 on both sides of that range;
+//   u32 rows of 4, 8 or 16 KiB over 2^k streams from 1 GiB on: 0.94-0.96 (2^18 x 1024
+//     169 / 185 us, 65536 x 4096 176 / 191), but 1.05-1.09 at 5/4 and 3/2 of 2^28
+//     numbers and 1.0-1.2 up to 2^27.
+inline bool kiss_words_by_mad(int dt, uint64_t S, uint64_t N)
+{
+    const uint64_t total = S * N;
+    if (dt == RNG_DT_F32) return N == 2 * kGenTile && total >= (uint64_t)3 << 25 && total <= (uint64_t)1 << 28;
+    return (N == 1024 || N == 2048 || N == 4096) && total >= (uint64_t)1 << 28 && (S & (S - 1)) == 0;
+}
+
 template <class G, int DT, int WG, int U, int kMode>
 int launch_generate_shape(const GenArgs &a, hipStream_t stream)
 {
@@ -712,6 +729,7 @@ int launch_generate_shape(const GenArgs &a, hipStream_t stream)
         }
     }
     bool launched = false;
+    [[maybe_unused]] const bool by_mad = G::kId == G_KISS && b.resident && kiss_words_by_mad(DT, a.S, a.N);
     if constexpr (kMode == 2 && K == 128 &&
                   (G::kId == G_MWC32 || G::kId == G_XS32 || G::kId == G_KISS || G::kId == G_MWC1616 ||
                    G::kId == G_XS256)) {
@@ -721,16 +739,37 @@ int launch_generate_shape(const GenArgs &a, hipStream_t stream)
         // the resident one, and smaller when the runs need fewer waves.
         if (b.resident && (a.seg == 2 || a.seg == 4) && a.S % (64 * (uint64_t)a.seg) == 0) {
             const uint64_t sw = a.S / (64 * (uint64_t)a.seg), sblocks = (sw + WG / 64 - 1) / (WG / 64);
-            hipLaunchKernelGGL((k_generate_seg<G, DT, WG, U>), dim3((unsigned)min(sblocks, blocks)), dim3(WG), 0,
-                               stream, b);
+            const dim3 grid((unsigned)min(sblocks, blocks));
+            if constexpr (G::kId == G_KISS && DT == RNG_DT_U32) {
+                if (by_mad) {
+                    hipLaunchKernelGGL((k_generate_seg<GenKISSMad, DT, WG, U>), grid, dim3(WG), 0, stream, b);
+                    launched = true;
+                }
+            }
+            if (!launched) hipLaunchKernelGGL((k_generate_seg<G, DT, WG, U>), grid, dim3(WG), 0, stream, b);
             launched = true;
         }
     }
     if constexpr (kMode == 2 && K == 128 &&
                   (G::kId == G_MWC32 || G::kId == G_XS32 || G::kId == G_KISS || G::kId == G_MWC1616)) {
         if (!launched && b.resident && a.rot) {
-            hipLaunchKernelGGL((k_generate_rot<G, DT, WG, U>), dim3((unsigned)blocks), dim3(WG), 0, stream, b);
+            if constexpr (G::kId == G_KISS && DT == RNG_DT_U32) {
+                if (by_mad) {
+                    hipLaunchKernelGGL((k_generate_rot<GenKISSMad, DT, WG, U>), dim3((unsigned)blocks), dim3(WG), 0,
+                                       stream, b);
+                    launched = true;
+                }
+            }
+            if (!launched)
+                hipLaunchKernelGGL((k_generate_rot<G, DT, WG, U>), dim3((unsigned)blocks), dim3(WG), 0, stream, b);
             launched = true;
+        }
+        if constexpr (G::kId == G_KISS && DT == RNG_DT_F32) {
+            if (!launched && by_mad) {
+                hipLaunchKernelGGL((k_generate<GenKISSMad, DT, WG, U, K, kMode>), dim3((unsigned)blocks), dim3(WG), 0,
+                                   stream, b);
+                launched = true;
+            }
         }
     }
     if (!launched)
