@@ -431,8 +431,14 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
     // the plain order).
     // rows of 4 or 8 KiB on workgroups of up to 256 lanes: runs of 4 or 2
     // adjacent rows per lane, 16 KiB each (when the launch is resident; else
-    // the orders below)
-    if (staged && a.P == 1 && a.vec4 && shape.wg <= 256) a.seg = run_rows(S, N);
+    // the orders below), from more runs of 64 lanes on than CUs: with fewer, one
+    // wave per CU steps alone (49152 x 1024 u32, us, runs / rotated rows: MWC1616
+    // 72.6 / 43.5, KISS 109 / 47, MWC32 50 / 33, XS256 128 / 39; at 65536 x 1024 74
+    // / 52, 110 / 55, 59 / 42, 129 / 44, but MWC1616 80128 x 1024 75 / 86).
+    if (staged && a.P == 1 && a.vec4 && shape.wg <= 256) {
+        a.seg = run_rows(S, N);
+        if (a.seg && S / (64 * a.seg) <= 256) a.seg = 0;
+    }
     if (g == RNG_XS256 && staged && a.P == 1 && a.vec4 && S % 64 == 0 && xs256_chunked_rows(N) && shape.wg >= 512) {
         a.C = N / kXs256RowChunks;
         a.P = kXs256RowChunks;
