@@ -386,10 +386,44 @@ static bool general_rows(int g, uint64_t S, uint64_t N, bool vec4, const void *o
     return S >= 64 && S * N < ((uint64_t)1 << 26) && (N < 8192 || S >= kSeqWaves / 2);
 }
 
-// Shared by rng_generate and the split path: one generate launch over
-// S streams whose states live at stride ld.
+// The kernels that take a call, and its chunks.  The row and sequence kernels have
+// launch shapes of their own; row kernels only if `rows` (the caller asked for no
+// shape, or for one of up to 256 lanes).
+enum class Route { kGeneral, kFew, kRows, kSequences };
+
+struct Chunks {
+    uint64_t C;
+    uint32_t P, lgp;  // kRows: 2^lgp chunks
+};
+
+static Route choose_route(int g, uint64_t S, uint64_t N, const void *out, bool staged, bool rows, Chunks *k)
+{
+    const bool vec4 = N % 4 == 0 && ((uintptr_t)out & 15) == 0;
+    const bool general = !staged || (N <= kRowMax && general_rows(g, S, N, vec4, out));
+    if (!general && seq_streams(g, S, N, out)) return Route::kSequences;
+    rows = rows && !general && N <= kRowMax;
+    uint32_t c;
+    if (rows && row_chunks(g, S, N, &k->lgp, &c)) {
+        k->C = c;
+        return Route::kRows;
+    }
+    if (staged && S < 64) {
+        lane_chunks(g, S, N, &k->C, &k->P);
+        if (k->P > 1) return Route::kFew;
+    }
+    choose_chunks(g, S, N, kGenTile, &k->C, &k->P, kGenLanes);
+    if (rows && k->P == 1 && N >= kRowMin && (!vec4 || S % 64 != 0 || N % kGenTile != 0)) {
+        k->C = N;
+        k->lgp = 0;
+        return Route::kRows;
+    }
+    return Route::kGeneral;
+}
+
+// Shared by rng_generate, rng_generate_ex and the tuner: S streams whose states
+// live at stride ld.  asked: the caller chose the launch shape.
 int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint64_t N, void *d_out,
-                  Shape shape, bool staged, hipStream_t st)
+                  Shape shape, bool asked, bool staged, hipStream_t st)
 {
     if (S == 0 || N == 0) return RNG_OK;
     DevTables tab;
@@ -404,21 +438,19 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
     a.vec4 = (N % 4 == 0) && (((uintptr_t)d_out & 15) == 0);
     a.nt = 0;  // plain stores: the streaming hint measured slower for these writes
     a.tab = tab;
-    const bool general = !staged || (N <= kRowMax && general_rows(g, S, N, a.vec4, d_out));
-    if (!general && seq_streams(g, S, N, d_out)) {
+    Chunks k;
+    switch (choose_route(g, S, N, d_out, staged, shape.wg <= 256 || !asked, &k)) {
+    case Route::kSequences:
         if (int e = check_launch(launch_seq(g, dt, d_state, ld, S, N, d_out, nullptr, tab, st), "rng_generate")) return e;
         return check_launch(dispatch_skip(g, d_state, ld, S, N, tab, st), "rng_generate: state");
+    case Route::kRows:
+        return check_launch(launch_rows(g, dt, d_state, ld, S, N, k.lgp, (uint32_t)k.C, d_out, tab, st), "rng_generate");
+    case Route::kFew:
+        return check_launch(generate_few(g, dt, d_state, ld, S, N, k.C, k.P, d_out, tab, st), "rng_generate");
+    case Route::kGeneral: break;
     }
-    uint32_t lgp, c;
-    if (!general && shape.wg <= 256 && N <= kRowMax && row_chunks(g, S, N, &lgp, &c))
-        return check_launch(launch_rows(g, dt, d_state, ld, S, N, lgp, c, d_out, tab, st), "rng_generate");
-    if (staged && S < 64) {
-        uint64_t c;
-        uint32_t P;
-        lane_chunks(g, S, N, &c, &P);
-        if (P > 1) return check_launch(generate_few(g, dt, d_state, ld, S, N, c, P, d_out, tab, st), "rng_generate");
-    }
-    choose_chunks(g, S, N, kGenTile, &a.C, &a.P, kGenLanes);
+    a.C = k.C;
+    a.P = k.P;
     // XS256 rows of an odd number of 4 KiB (no rotated order: a row would need
     // a 256 x 256 jump inside the write stream): four chunks per stream, each
     // jumped once at its start, before any store (one table product per
@@ -448,9 +480,6 @@ int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uin
         a.rot = 1;
         rot_constants(g, N, a);
     }
-    if (!general && a.P == 1 && shape.wg <= 256 && N >= kRowMin && N <= kRowMax &&
-        (!a.vec4 || S % 64 != 0 || N % kGenTile != 0))
-        return check_launch(launch_rows(g, dt, d_state, ld, S, N, 0, (uint32_t)N, d_out, tab, st), "rng_generate");
     rc = dispatch_generate(g, dt, a, (int)shape.wg, (int)shape.unroll, staged, st);
     if (rc != kStatesNotWritten) return check_launch(rc, "rng_generate");
     // chunks of one stream in several workgroups: the states advance after
@@ -609,27 +638,32 @@ int rng_seed(int g, uint64_t seed, uint64_t first_stream, uint64_t n_streams, ui
                         "rng_seed");
 }
 
-int rng_generate_ex(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, int t, void *d_out,
-                    uint32_t wg, uint32_t unroll, void *stream)
+static int generate_checked(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, int t, void *d_out, Shape shape,
+                            bool asked, void *stream)
 {
     if (check_gen(g)) return RNG_EINVAL;
     if (t != RNG_U32 && t != RNG_F32) return fail(RNG_EINVAL, "unknown dtype %d", t);
-    if (!valid_shape(wg, unroll)) return fail(RNG_EINVAL, "launch shape wg=%u unroll=%u", wg, unroll);
+    if (!valid_shape(shape.wg, shape.unroll))
+        return fail(RNG_EINVAL, "launch shape wg=%u unroll=%u", shape.wg, shape.unroll);
     if (n_streams == 0 || n == 0) return RNG_OK;
     if (!d_state || !d_out) return fail(RNG_EINVAL, "NULL state or output");
     if (((uintptr_t)d_state & 3) || ((uintptr_t)d_out & 3))
         return fail(RNG_EINVAL, "state and output must be 4-byte aligned");
     if (int rc = check_sizes(n_streams, n, gen_words(g))) return rc;
-    return generate_impl(g, t, d_state, n_streams, n_streams, n, d_out, Shape{wg, unroll}, true,
-                         (hipStream_t)stream);
+    return generate_impl(g, t, d_state, n_streams, n_streams, n, d_out, shape, asked, true, (hipStream_t)stream);
+}
+
+int rng_generate_ex(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, int t, void *d_out,
+                    uint32_t wg, uint32_t unroll, void *stream)
+{
+    return generate_checked(g, d_state, n_streams, n, t, d_out, Shape{wg, unroll}, true, stream);
 }
 
 int rng_generate(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, int t, void *d_out, void *stream)
 {
     if (check_gen(g)) return RNG_EINVAL;
     if (t != RNG_U32 && t != RNG_F32) return fail(RNG_EINVAL, "unknown dtype %d", t);
-    Shape s = row_shape(g, t, n_streams, n);
-    return rng_generate_ex(g, d_state, n_streams, n, t, d_out, s.wg, s.unroll, stream);
+    return generate_checked(g, d_state, n_streams, n, t, d_out, row_shape(g, t, n_streams, n), false, stream);
 }
 
 int rng_skip(int g, uint32_t *d_state, uint64_t n_streams, uint64_t k, void *stream)

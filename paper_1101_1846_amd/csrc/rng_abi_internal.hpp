@@ -30,7 +30,7 @@ void choose_chunks(int g, uint64_t S, uint64_t N, uint64_t align, uint64_t *C, u
 // Chunks for one lane per chunk (fewer streams than a wave has lanes).
 void lane_chunks(int g, uint64_t S, uint64_t N, uint64_t *C, uint32_t *P);
 int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint64_t N, void *d_out,
-                  Shape shape, bool staged, hipStream_t st);
+                  Shape shape, bool asked, bool staged, hipStream_t st);
 int dispatch_generate(int g, int dt, const GenArgs &a, int wg, int unroll, bool staged, hipStream_t st);
 int dispatch_skip(int g, uint32_t *st, uint64_t ld, uint64_t S, uint64_t k, const DevTables &tab, hipStream_t s);
 int dispatch_state_copy(int g, const uint32_t *src, uint64_t ss, uint64_t si, uint32_t *dst, uint64_t ds,

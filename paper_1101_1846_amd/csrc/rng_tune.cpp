@@ -83,12 +83,12 @@ int rng_autotune(int g, int t, uint64_t n_streams, uint64_t n, uint32_t *d_state
         for (uint32_t un : uns) {
             // one warm-up launch, then reps timed launches
             rc = generate_impl(g, t, d_state_scratch, n_streams, n_streams, n, d_out_scratch, Shape{wg, un},
-                               true, st);
+                               true, true, st);
             if (rc) break;
             (void)hipEventRecord(e0, st);
             for (uint32_t r = 0; r < reps && !rc; ++r)
                 rc = generate_impl(g, t, d_state_scratch, n_streams, n_streams, n, d_out_scratch,
-                                   Shape{wg, un}, true, st);
+                                   Shape{wg, un}, true, true, st);
             (void)hipEventRecord(e1, st);
             if (rc) break;
             if ((e = hipEventSynchronize(e1)) != hipSuccess) {
