@@ -329,6 +329,14 @@ static void rot_constants(int g, uint64_t N, GenArgs &a)
     std::memcpy(a.rot_lcg, hit->lcg, sizeof(hit->lcg));
 }
 
+// Fewer rows than a wave has lanes whose chunks (row_chunks) do not begin on whole
+// lines from the stream's start on.
+static bool split_lines(int g, uint64_t S, uint64_t N)
+{
+    uint32_t lgp, c;
+    return S < 64 && N <= kRowMax && !(row_chunks(g, S, N, &lgp, &c) && c % 32 == 0);
+}
+
 // Streams that run as long sequences, windows of consecutive numbers across a
 // wave (seq.hip, seq_xs256.hip), instead of rows or chunks of a row per lane: up
 // to one stream per wave of the device, from the lengths on at which a stream's
@@ -338,52 +346,92 @@ static void rot_constants(int g, uint64_t N, GenArgs &a)
 // start by a chain of table products per lane, from shorter rows on (64 x 512
 // 18.3 / 12.6, 1000 x 1000 42 / 20), with four streams per wave (4096 x 4096
 // 151 / 67, 4096 x 10^4 188 / 95; but 4096 x 65536 231 / 227, 2 10^4 x 10^4 421
-// either way), and with more where rows that long start inside 128-byte lines
-// (10^4 x 25001 525 / 358).
-static bool seq_streams(int g, uint64_t S, uint64_t N, const void *out)
+// either way, and 4096 x 3072 at 16 bytes into a line 70 against 56 for the four
+// chunks of a workgroup), and with more where rows that long start inside 128-byte
+// lines (10^4 x 25001 525 / 358).
+static bool seq_streams(int g, uint64_t S, uint64_t N, bool vec4, const void *out)
 {
-    // the cheap generators' windows outrun their chunks later (XS32 1000 x 8192
-    // 14.7 / 16.4, 1000 x 16384 19.5 / 19.0)
-    if ((g == RNG_XS32 || g == RNG_MWC32) && S > kSeqWaves / 2 && N < 16384) return false;
-    if (g != RNG_XS256) return S <= kSeqWaves && N >= 8192;
-    if (S <= kSeqWaves) return N >= 512;
-    if (S <= 4 * kSeqWaves && N >= 2048 && N < 16384) return true;
-    return N >= 16384 && S <= ((uint64_t)1 << 24) && (N % 32 != 0 || ((uintptr_t)out & 127));
+    switch (g) {
+    case RNG_XS256:
+        if (S <= kSeqWaves) return N >= 512;
+        if (S <= 4 * kSeqWaves && N >= 2048 && N < 16384) return !(vec4 && S % 64 == 0 && xs256_chunked_rows(N));
+        return N >= 16384 && S <= ((uint64_t)1 << 24) && (N % 32 != 0 || ((uintptr_t)out & 127));
+    // the cheap generators: a stream of the few whose chunks would break lines
+    // early (MWC32 10 x 2500, us, general / chunks / windows 7.7 / 10.5 / 7.1, 33 x
+    // 6000 8.8 / 13.8 / 7.3, but 1 x 4096 7.1 / 4.2 / 7.7; XS32 10 x 6000 13.8 / 17.3
+    // / 9.0), many streams later, as windows outrun their chunks later (XS32 1000 x
+    // 8192 14.7 / 16.4, 1000 x 16384 19.5 / 19.0, and the four windows of 500 x 16384
+    // 15.5 / 20.6; MWC32 300 x 6000 15 / 7.8)
+    case RNG_MWC32:
+        if (S <= kSeqWaves / 2) return N >= 6000 || (N >= 340 && split_lines(g, S, N));
+        return S <= kSeqWaves && N >= 16384;
+    case RNG_XS32:
+        if (S <= kSeqWaves / 4) return N >= 8192 || (N >= 4096 && split_lines(g, S, N));
+        if (S <= kSeqWaves / 2) return N >= 8192 && (N < 12000 || N >= 20000);
+        return S <= kSeqWaves && N >= 16384;
+    }
+    return S <= kSeqWaves && N >= 8192;
 }
 
 // Rows that k_generate takes although they are no whole tiles: short ones, whose
 // heads and last tiles, which do not overlap their stores, cost more line by line
-// (rows.hip) than the partial lines do while these stay in the caches.
-//   whole lines: XS256 x 96 (us, k_generate / k_rows: 7.1 / 7.8 for 1000 rows), and
-//     short rows that fill the lanes (XS32 65536 x 96 -10 %, 8192 x 512 7.5 / 8.6);
+// (rows.hip) than the partial lines do while these stay in the caches.  From 17000
+// timed calls of 1 to 3 10^5 streams x 64 to 10^6 numbers at 0, 4 and 16 bytes into
+// a line; against the better kernel it is within 5 % on four of five, against the
+// general one alone never far behind (us or time, general / line by line):
+//   fewer rows than lanes: up to 128 numbers (XS32 33 x 100 5.1 / 7.6, KISS 10 x 75
+//     8.6 / 13.3, MWC1616 10 x 128 5.2 / 7.3, XS256 10 x 128 at 4 bytes 9.7 / 11.3),
+//     MWC32 whose chunks would break lines up to 340 (3 x 168 6.9 / 9.4);
+//   whole lines: XS256 below 128, XS32 and MWC32 x 96, a tile and a half (XS32 100 x
+//     96 5.6 / 6.0), and short rows that fill the lanes (XS32 65536 x 96 -10 %,
+//     8192 x 512 7.5 / 8.6);
 //   whole tiles: rows of two to four long chunks, which k_generate keeps 64 streams
-//     apart (MWC32 24576 x 8192 144 / 156, XS32 20032 x 8192 -26 %, KISS 28032 x 8192
-//     -23 %, but XS32 16384 x 2048 +11 %, 16384 x 16384 +17 %);
+//     apart (MWC32 24576 x 8192 144 / 156, 25000 x 1024 18.0 / 20.3, XS32 20032 x 8192
+//     -26 %, KISS 28032 x 8192 -23 %, but XS32 8192 x 1024 15.2 / 11.2, 16384 x 2048
+//     +11 %, 16384 x 16384 +17 %);
 //   rows that begin inside 16 bytes: below 128 numbers (XS256 1000 x 75 10.9 / 13.4),
 //     as k_generate then stores word by word (XS32 1000 x 203 twice as long);
 //   else by how many numbers a lane's start and a number's steps are worth: XS256
 //     1000 x 340 16.3 / 21.2, 13810 x 776 -7 %, but x 3000 +22 %; KISS 1000 x 168 -17 %,
-//     x 300 +5 %, 40000 x 776 -6 %; MWC1616 1000 x 300 -17 %, x 460 +25 %, 13810 x 776
-//     -6 %; XS32 8192 x 340 8.1 / 14.6, 2000 x 11000 -18 %, but 152 x 11000 +43 %;
-//     MWC32 13810 x 2500 -15 %, 40000 x 1300 -7 %, but 2000 x 50000 +22 %.
+//     x 300 +5 %, 8192 x 1000 24.7 / 18.8, x 1300 19.6 / 25.2, 40000 x 776 -6 %; MWC1616
+//     1000 x 300 -17 %, x 460 +25 %, 13810 x 776 -6 %; XS32 8192 x 340 8.1 / 14.6, 2000 x
+//     11000 -18 %, but 152 x 11000 +43 %, 300 x 16384 12.0 / 14.3; MWC32 13810 x 2500
+//     -15 %, 40000 x 1300 -7 %, but 2000 x 50000 +22 %.
 // KISS's rows gain from every lane (1000 x 75 14.2 / 12.1).  More rows than lanes
-// never lose (MWC32 10^5 x 75 +54 %).
+// lose only as whole tiles off a line's start (100000 x 512 at 16 bytes: XS32 39.1 /
+// 42.2, XS256 46.6 / 54.2) and for XS256 as short rows beyond 2^18 (300000 x 200 62.7
+// / 73.2, but 200000 x 168 44.5 / 39.8); MWC32 10^5 x 75 +54 %.  XS256 rows of an odd
+// number of 4 KiB, which k_generate takes with 512 lanes, where the last pass of the
+// row kernel's waves is short (100000 x 3072 255 / 280, but 64000 x 1024 130 / 44,
+// 300007 x 3072 804 / 759).
 static bool general_rows(int g, uint64_t S, uint64_t N, bool vec4, const void *out)
 {
-    if (S > 65536) return false;
-    const bool cheap = g == RNG_XS32 || g == RNG_MWC32;
-    if (N % 32 == 0 && !((uintptr_t)out & 127)) {
+    const bool cheap = g == RNG_XS32 || g == RNG_MWC32, lines = N % 32 == 0 && !((uintptr_t)out & 127);
+    if (S > 65536) {
+        if (!vec4 || g == RNG_KISS) return false;
+        if (lines) return g == RNG_XS256 && xs256_chunked_rows(N) && 20 * S < 17 * ((S + 65535) & ~(uint64_t)65535);
+        if (g == RNG_XS256 && S > ((uint64_t)1 << 18)) return N < 256;
+        return N % kGenTile == 0 && N >= 512;
+    }
+    if (S < 64) {
+        if (!lines && (N < 128 || (N == 128 && (vec4 || g == RNG_XS256)))) return true;
+        if (g == RNG_MWC32 && vec4 && N < 340) return split_lines(g, S, N);
+    }
+    if (lines) {
         if (g == RNG_XS256) return N < 128;
-        if (N % kGenTile == 0 && N >= (g == RNG_KISS ? 4096 : 3072) && N < 12288 && S >= (cheap ? 8192 : 12289)) return true;
+        if (cheap && N == 96) return true;
+        if (N % kGenTile == 0 && N >= (cheap ? 1024 : g == RNG_KISS ? 4096 : 3072) && N < 12288 && S > (cheap ? 8192 : 12288))
+            return true;
         return g != RNG_KISS && N <= 512 && (S > 32768 || (cheap && S * N >= (uint64_t)1 << 22));
     }
     if (!vec4) return N < 128 && g != RNG_KISS;
     switch (g) {
     case RNG_XS256: return N < 512 || (S > kSeqWaves && N < 1536);
-    case RNG_KISS: return N < (S > 16384 ? 1536 : 192);
+    case RNG_KISS: return N < 192 || (N < 1700 && (S > 16384 || (S >= 8192 && N >= 1100)));
     case RNG_MWC1616: return S >= 64 && N < (S > 8192 ? 1536 : 400);
     }
-    return S >= 64 && S * N < ((uint64_t)1 << 26) && (N < 8192 || S >= kSeqWaves / 2);
+    if (S * N >= (uint64_t)1 << 26) return false;
+    return S >= 64 && (N < 8192 || S >= kSeqWaves / 2 || (g == RNG_XS32 && S >= kSeqWaves / 4 && N >= 12000 && N < 60000));
 }
 
 // The kernels that take a call, and its chunks.  The row and sequence kernels have
@@ -400,7 +448,7 @@ static Route choose_route(int g, uint64_t S, uint64_t N, const void *out, bool s
 {
     const bool vec4 = N % 4 == 0 && ((uintptr_t)out & 15) == 0;
     const bool general = !staged || (N <= kRowMax && general_rows(g, S, N, vec4, out));
-    if (!general && seq_streams(g, S, N, out)) return Route::kSequences;
+    if (!general && seq_streams(g, S, N, vec4, out)) return Route::kSequences;
     rows = rows && !general && N <= kRowMax;
     uint32_t c;
     if (rows && row_chunks(g, S, N, &k->lgp, &c)) {
