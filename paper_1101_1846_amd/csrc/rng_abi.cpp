@@ -468,6 +468,13 @@ static Route choose_route(int g, uint64_t S, uint64_t N, const void *out, bool s
     return Route::kGeneral;
 }
 
+// Whether rng_generate's shape changes anything for this call.
+bool shape_matters(int g, uint64_t S, uint64_t N, const void *out)
+{
+    Chunks k;
+    return choose_route(g, S, N, out, true, true, &k) == Route::kGeneral;
+}
+
 // Shared by rng_generate, rng_generate_ex and the tuner: S streams whose states
 // live at stride ld.  asked: the caller chose the launch shape.
 int generate_impl(int g, int dt, uint32_t *d_state, uint64_t ld, uint64_t S, uint64_t N, void *d_out,

@@ -24,6 +24,7 @@ uint32_t run_rows(uint64_t S, uint64_t N);
 Shape tuned_shape(int g, int dt, bool runs);
 Shape row_shape(int g, int dt, uint64_t S, uint64_t n);
 void set_tuned_shape(int g, int dt, bool runs, Shape s);
+bool shape_matters(int g, uint64_t S, uint64_t N, const void *out);
 // Chunks per stream: the largest power of two p with S p <= target_lanes and
 // chunks of at least the generator's minimum length.
 void choose_chunks(int g, uint64_t S, uint64_t N, uint64_t align, uint64_t *C, uint32_t *P, uint64_t target_lanes);
