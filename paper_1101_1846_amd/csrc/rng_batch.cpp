@@ -447,9 +447,12 @@ int rng_batch_autotune(rng_batch_t *h, uint32_t reps, uint32_t *best_wg, uint32_
 {
     if (!h || !best_wg || !best_unroll || !best_chunk) return fail(RNG_EINVAL, "NULL argument");
     if (reps == 0) return fail(RNG_EINVAL, "reps is 0");
+    uint64_t n, total = 0;
     {
         std::lock_guard<std::mutex> lk(h->mu);
         if (h->last.empty()) return fail(RNG_EINVAL, "no planned batch to tune on");
+        n = h->last.size();
+        for (const rng_request_t &r : h->last) total += r.length;
     }
     // every built shape: workgroups of 64..1024 lanes x unroll 1..16 (the
     // paper chose its block size by occupancy and unrolled its main loop)
@@ -459,7 +462,10 @@ int rng_batch_autotune(rng_batch_t *h, uint32_t reps, uint32_t *best_wg, uint32_
         shapes[i][0] = wgs[i / 5];
         shapes[i][1] = unrolls[i % 5];
     }
-    static const uint32_t chunks[] = {512, 1024, 2048, 4096};
+    // Longest first, and none that plans the same rows as one before it: between
+    // those, timing noise would store a limit for later, larger batches.
+    static const uint32_t chunks[] = {4096, 2048, 1024, 512};
+    uint32_t planned_bits = ~0u;
     hipStream_t st = (hipStream_t)stream;
     hipEvent_t e0, e1;
     hipError_t e;
@@ -472,6 +478,9 @@ int rng_batch_autotune(rng_batch_t *h, uint32_t reps, uint32_t *best_wg, uint32_
     uint32_t bw = h->wg, bu = h->unroll, bc = (uint32_t)h->C;
     int rc = RNG_OK;
     for (uint32_t c : chunks) {
+        const uint32_t bits = row_bits(n, total, (uint32_t)__builtin_ctz(c));
+        if (bits == planned_bits) continue;
+        planned_bits = bits;
         for (auto &sh : shapes) {
             if ((rc = rng_batch_set_shape(h, sh[0], sh[1], c))) break;
             if ((rc = rng_batch_launch(h, stream))) break;  // warm-up (and graph capture)
