@@ -184,7 +184,7 @@ int rng_batch_create(uint32_t max_requests, uint64_t max_samples, rng_batch_t **
     if (hipGetDeviceProperties(&prop, h->device) == hipSuccess) h->num_cu = prop.multiProcessorCount;
     hipError_t e = hipSuccess;
     int rc = RNG_OK;
-    if ((e = hipMalloc((void **)&h->d_counter, 256)) != hipSuccess ||
+    if ((e = hipMalloc((void **)&h->d_counter, kBatchCounterWords << (kBatchLgCounters + 2))) != hipSuccess ||
         (e = hipEventCreateWithFlags(&h->copied, hipEventDisableTiming)) != hipSuccess ||
         (e = hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking)) != hipSuccess)
         rc = hip_fail(e, "rng_batch_create");
@@ -322,7 +322,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         h->copy_pending = false;
     }
     h->planned = false;  // until this plan is complete: a failure below leaves nothing to launch
-    const uint32_t cap = row_bits(n, total_samples, (uint32_t)__builtin_ctzll(longest_row(h)));
+    const uint32_t longest = (uint32_t)__builtin_ctzll(longest_row(h)), cap = row_bits(n, total_samples, longest);
     auto tile_bits = [cap](uint64_t length) {
         uint32_t lg = kBatchLgMin;
         while (lg < cap && ((uint64_t)64 << lg) < length) ++lg;
@@ -362,6 +362,8 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         base += Q[i].ntiles;
     }
     H.n_tiles = base;
+    // (every counter needs a wave: a grid that leaves tiles over has one per CU at least)
+    H.lg_counters = total_samples < (uint64_t)base * 8192 && h->num_cu >= 1 << kBatchLgCounters ? kBatchLgCounters : 0;
     H.plan_bytes = (uint32_t)align16(H.off_reqs + sizeof(BatchReq) * (uint64_t)n);
     h->planned = true;
     return RNG_OK;

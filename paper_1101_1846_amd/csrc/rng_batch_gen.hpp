@@ -119,9 +119,10 @@ __device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchReq &q
 }
 
 // Persistent generation.  Wave w of the grid's W waves takes tile w first;
-// the tiles from W on are pulled from an atomic counter (reset by the root
+// the tiles from W on are pulled from atomic counters (reset by the root
 // kernel), so a batch with fewer tiles than waves issues no atomics and the
-// waves without a tile leave at once.
+// waves without a tile leave at once.  Of 2^c counters, number i hands out tiles
+// W + i, W + i + 2^c, ... to the waves w = i mod 2^c.
 template <int WG, int U>
 __global__ __launch_bounds__(WG) void k_batch_gen(BatchArgs a)
 {
@@ -148,9 +149,10 @@ __global__ __launch_bounds__(WG) void k_batch_gen(BatchArgs a)
         case G_MWC1616: batch_tile<GenMWC1616, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
         }
         if (nwaves >= n_tiles) break;  // every tile was handed out statically
+        const uint32_t lgc = uniform_read(&a.hdr->lg_counters), mine = (blockIdx.x * NW + wv) & ((1u << lgc) - 1);
         uint32_t next = 0;
-        if (lane == 0) next = atomicAdd(a.counter, 1u);
-        t = nwaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
+        if (lane == 0) next = atomicAdd(a.counter + mine * kBatchCounterWords, 1u);
+        t = nwaves + mine + ((uint32_t)__builtin_amdgcn_readfirstlane((int)next) << lgc);
     }
 }
 

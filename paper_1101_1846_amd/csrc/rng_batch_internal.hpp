@@ -18,6 +18,13 @@ constexpr int kBatchMaxGroups = 10;  // 5 generators x 2 dtypes
 constexpr int kBatchTile = 64;       // LDS tile depth of the batch kernel
 constexpr int kBatchLgMin = 5, kBatchLgMax = 12;  // rows of 32 to 4096 samples
 
+// Tiles beyond the waves of the grid are pulled from 2^lg_counters counters, a
+// 128-byte line each, of which wave w uses number w mod 2^lg_counters.  Atomics on
+// one address follow each other in about 13 ns: tiles of fewer than 8192 samples
+// end sooner than that over 2048 waves (10^4 requests of 16 samples: 155 us from one
+// counter, 52 from 32).  Longer ones share one, which balances them best.
+constexpr uint32_t kBatchLgCounters = 5, kBatchCounterWords = 32;
+
 struct BatchReq {
     uint32_t *state;     // word 0 of the stream's state
     uint64_t stride;     // word stride of that state
@@ -47,7 +54,8 @@ struct BatchHeader {
     uint32_t n_tiles;
     uint32_t off_reqs;
     uint32_t plan_bytes;
-    uint32_t pad[3];
+    uint32_t lg_counters;
+    uint32_t pad[2];
     BatchGroup groups[kBatchMaxGroups];
 };
 
@@ -68,7 +76,7 @@ struct BatchArgs {
     const BatchHeader *hdr;  // the packed plan
     uint32_t *tile_req;      // [n_tiles] request of every tile
     uint32_t *ws;            // [n][8] start states of the requests
-    uint32_t *counter;       // [0] tile counter of the persistent kernel
+    uint32_t *counter;       // tile counters of the persistent kernel
     DevTables tab;
 };
 

@@ -29,7 +29,7 @@ __device__ __forceinline__ void with_gen(uint32_t g, F &&f)
 // writes the state while others may not have read it yet), writes the request
 // of each of its tiles, and moves the state of an empty request, or the copy of
 // one that crosses position 2^64, by `offset`.
-// Also clears the generation kernel's tile counter.
+// Also clears the generation kernel's tile counters.
 constexpr int kRootWG = 256;
 
 __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline pin)
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
     if (pin.bytes && blockIdx.x == 0)  // the plan for the generation kernel
         for (uint32_t i = threadIdx.x; i * 16 < pin.bytes; i += kRootWG) ((uint4 *)a.hdr)[i] = pin.q[i];
     const BatchReq *reqs = plan_at<const BatchReq>(hp, hp->off_reqs);
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.counter[0] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 1u << kBatchLgCounters) a.counter[threadIdx.x * kBatchCounterWords] = 0;
     const int lane = threadIdx.x & 63;
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = hp->n;
     for (uint32_t r = blockIdx.x * (kRootWG / 64) + wv; r < n; r += gridDim.x * (kRootWG / 64)) {
