@@ -30,6 +30,7 @@ struct rng_batch {
     uint64_t C = 1024;
     bool chunk_auto = false;  // C chosen per plan (RNG_BATCH_CHUNK_AUTO)
     uint32_t wg = 256, unroll = 8;
+    bool wg_asked = false;  // wg is the caller's (or the tuner's) choice
     uint64_t map_cap = 0;  // tiles the map holds
     char *d_plan = nullptr, *h_plan = nullptr;  // packed plan (BatchHeader first), device and pinned staging
     uint32_t *d_ws = nullptr, *d_counter = nullptr, *d_map = nullptr;
@@ -236,6 +237,7 @@ int rng_batch_set_shape(rng_batch_t *h, uint32_t wg, uint32_t unroll, uint32_t c
     }
     h->wg = w;
     h->unroll = u;
+    if (wg) h->wg_asked = true;
     return RNG_OK;
 }
 
@@ -323,14 +325,17 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     }
     h->planned = false;  // until this plan is complete: a failure below leaves nothing to launch
     const uint32_t longest = (uint32_t)__builtin_ctzll(longest_row(h)), cap = row_bits(n, total_samples, longest);
-    auto tile_bits = [cap](uint64_t length) {
+    // A request that one lane steps through sooner than the lanes' starts take stays
+    // one row (16 XS256 requests of 64 samples: 14.5 us as two rows, 10.7 as one).
+    auto tile_bits = [cap, longest](const rng_request_t &r) {
         uint32_t lg = kBatchLgMin;
-        while (lg < cap && ((uint64_t)64 << lg) < length) ++lg;
+        const bool one = r.offset == 0 && r.length <= (r.gen == RNG_XS256 ? 64u : 32u);
+        while (lg < (one ? longest : cap) && ((uint64_t)(one ? 1 : 64) << lg) < r.length) ++lg;
         return lg;
     };
     auto tiles_of = [](uint64_t length, uint32_t lg) { return (length + ((uint64_t)64 << lg) - 1) >> (lg + 6); };
     uint64_t tiles = 0;
-    for (uint32_t i = 0; i < n; ++i) tiles += tiles_of(reqs[i].length, tile_bits(reqs[i].length));
+    for (uint32_t i = 0; i < n; ++i) tiles += tiles_of(reqs[i].length, tile_bits(reqs[i]));
     if (tiles > h->map_cap)
         return fail(RNG_ENOMEM, "batch needs %llu tiles > %llu", (unsigned long long)tiles, (unsigned long long)h->map_cap);
     // requests by (generator, dtype), in table order within each
@@ -352,7 +357,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     }
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
-        const uint32_t k = key(i), lg = tile_bits(r.length);
+        const uint32_t k = key(i), lg = tile_bits(r);
         Q[begin[k]++] = BatchReq{r.d_state, r.state_stride, r.offset, r.length, (uint32_t *)r.d_out,
                                  0, (uint32_t)tiles_of(r.length, lg), group[k], lg};
     }
@@ -408,8 +413,17 @@ int rng_batch_launch(rng_batch_t *h, void *stream)
         const BatchArgs a = make_args(h, tab);
         int rc = launch_batch_root(a, pin, H.n, st);
         if (!rc && H.n_tiles) {
-            const unsigned need = (unsigned)std::min<uint64_t>(gen_grid, (H.n_tiles + h->wg / 64 - 1) / (h->wg / 64));
-            rc = launch_batch_gen(a, (int)h->wg, (int)h->unroll, need, st);
+            // Up to a tile per CU goes out as workgroups of one wave, a CU each, if it
+            // is long: four waves that share one slow each other down (16 XS256 requests
+            // of 64 samples 15.3 us in workgroups of 256 lanes, 10.7 of 64, 100 of them
+            // 22.4 and 16.8; no difference from 300 on; but 16 MWC32 requests of 1000
+            // 7.7 and 8.5, and one XS256 request of two tiles 13.1 and 14.9).
+            bool slow = false;
+            for (uint32_t i = 0; i < H.ngroups; ++i) slow |= H.groups[i].gen == G_XS256 || H.groups[i].gen == G_KISS;
+            const bool alone = !h->wg_asked && slow && H.n_tiles > h->wg / 64 && H.n_tiles <= (uint32_t)h->num_cu;
+            const uint32_t wg = alone ? 64 : h->wg;
+            const unsigned need = (unsigned)std::min<uint64_t>(gen_grid, (H.n_tiles + wg / 64 - 1) / (wg / 64));
+            rc = launch_batch_gen(a, (int)wg, (int)h->unroll, need, st);
         }
         return check_launch(rc, "rng_batch_launch");
     }

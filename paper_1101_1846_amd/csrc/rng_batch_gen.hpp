@@ -111,7 +111,8 @@ __device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchReq &q
     const uint32_t left = (uint32_t)min(rest, (uint64_t)64 << q.lgc);
     G g;
     load_uniform(g, a.ws + (uint64_t)8 * r, 1, 0);
-    wave_starts(g, (batch_far(q) ? 0 : q.offset) + first, q.lgc, tile, lane, a.tab);
+    const uint64_t k = (batch_far(q) ? 0 : q.offset) + first;
+    if (k || left > 1u << q.lgc) wave_starts(g, k, q.lgc, tile, lane, a.tab);  // else one row, from the state itself
     gu32 *out = global_ptr(q.out) + first;
     if (dtype == RNG_DT_F32) batch_rows<G, RNG_DT_F32, U, K>(g, out, left, q.lgc, tile, lane);
     else batch_rows<G, RNG_DT_U32, U, K>(g, out, left, q.lgc, tile, lane);
