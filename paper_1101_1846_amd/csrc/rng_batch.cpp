@@ -334,33 +334,49 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         return lg;
     };
     auto tiles_of = [](uint64_t length, uint32_t lg) { return (length + ((uint64_t)64 << lg) - 1) >> (lg + 6); };
+    // requests that share a tile: short enough for the rounds of tiles that this saves
+    uint32_t shorts = 0;
+    for (uint32_t i = 0; i < n; ++i) shorts += reqs[i].length - 1 < kBatchPackMax;
+    const uint64_t pack = shorts < kBatchPackMin ? 0 : std::min<uint64_t>(kBatchPackMax, shorts / 12);
+    auto packed = [pack](const rng_request_t &r) {  // no empty one
+        return r.length - 1 < (r.gen == RNG_XS256 || r.gen == RNG_KISS ? pack : std::min<uint64_t>(pack, 192));
+    };
     uint64_t tiles = 0;
     for (uint32_t i = 0; i < n; ++i) tiles += tiles_of(reqs[i].length, tile_bits(reqs[i]));
     if (tiles > h->map_cap)
         return fail(RNG_ENOMEM, "batch needs %llu tiles > %llu", (unsigned long long)tiles, (unsigned long long)h->map_cap);
-    // requests by (generator, dtype), in table order within each
+    // requests by (generator, dtype), those that share tiles first, in table order
+    // within each
     BatchHeader &H = h->hdr();
     std::memset(&H, 0, sizeof(H));
     H.n = n;
     H.off_reqs = (uint32_t)align16(sizeof(BatchHeader));
     BatchReq *Q = plan_at<BatchReq>(&H, H.off_reqs);
-    uint32_t count[16] = {0}, group[16] = {0}, begin[16] = {0};  // by key = 2 generator + dtype
-    auto key = [&](uint32_t i) { return (uint32_t)reqs[i].gen * 2 + (uint32_t)reqs[i].dtype; };
-    for (uint32_t i = 0; i < n; ++i) ++count[key(i)];
+    // by key = 4 generator + 2 dtype + (a tile of its own)
+    uint32_t count[32] = {0}, group[32] = {0}, begin[32] = {0};
+    auto key = [&](const rng_request_t &r) { return (uint32_t)r.gen * 4 + (uint32_t)r.dtype * 2 + !packed(r); };
+    for (uint32_t i = 0; i < n; ++i) ++count[key(reqs[i])];
     uint32_t at = 0;
-    for (uint32_t k = 0; k < 16; ++k) {
+    for (uint32_t k = 0; k < 32; ++k) {
         begin[k] = at;
         at += count[k];
-        if (!count[k]) continue;
-        group[k] = H.ngroups;
-        H.groups[H.ngroups++] = BatchGroup{k / 2, k % 2};
+        if (!count[k & ~1u] && !count[k | 1u]) continue;
+        if (k % 2 == 0) H.groups[H.ngroups++] = BatchGroup{k / 4, k / 2 % 2};
+        group[k] = H.ngroups - 1;
     }
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
-        const uint32_t k = key(i), lg = tile_bits(r);
+        const uint32_t k = key(r);
+        const uint32_t lg = packed(r) ? kBatchPacked : tile_bits(r);
         Q[begin[k]++] = BatchReq{r.d_state, r.state_stride, r.offset, r.length, (uint32_t *)r.d_out,
-                                 0, (uint32_t)tiles_of(r.length, lg), group[k], lg};
+                                 0, packed(r) ? 0 : (uint32_t)tiles_of(r.length, lg), group[k], lg};
     }
+    for (uint32_t k = 0; k < 32; k += 2)  // begin[k] is their end now
+        for (uint32_t i = 0; i < count[k]; i += 64) {
+            BatchReq &first = Q[begin[k] - count[k] + i];
+            first.ntiles = 1;
+            first.lgc = kBatchPacked + std::min(count[k] - i, 64u) - 1;
+        }
     uint32_t base = 0;
     for (uint32_t i = 0; i < n; ++i) {
         Q[i].tile_base = base;

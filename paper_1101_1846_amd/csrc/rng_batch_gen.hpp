@@ -36,6 +36,29 @@ __device__ __forceinline__ uint32_t bits_of(uint32_t u)
     else return u;
 }
 
+// cnt numbers of the lane's own into its row of the LDS tile.  Lanes with a whole
+// block left take the unrolled path together; a lane whose numbers end inside it
+// stops exactly there.
+template <class G, int DT, int U>
+__device__ __forceinline__ void batch_numbers(G &g, uint32_t *row, uint32_t cnt)
+{
+    uint32_t k = 0;
+#pragma unroll 1
+    for (; k + U <= cnt; k += U) {
+        uint32_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = bits_of<DT>(g.next());
+        if constexpr (U % 4 == 0) {
+#pragma unroll
+            for (int u = 0; u < U; u += 4) *(uint4 *)&row[k + u] = make_uint4(v[u], v[u + 1], v[u + 2], v[u + 3]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) row[k + u] = v[u];
+        }
+    }
+    for (; k < cnt; ++k) row[k] = bits_of<DT>(g.next());
+}
+
 // The rows of one tile, lane l's states in g: c = 2^lgc samples of lane l from
 // l c on, up to `left` (the samples from the tile's start to the request's end,
 // at most 64 c).  K samples at a time go through the LDS tile and are stored
@@ -50,24 +73,7 @@ __device__ __forceinline__ void batch_rows(G &g, gu32 *out, uint32_t left, uint3
     const bool aligned = ((uintptr_t)out & 15) == 0;
     uint32_t *row = tile + lane * LD;
     for (uint32_t k0 = 0; k0 < longest; k0 += K) {
-        // Lanes with a whole block left take the unrolled path together; the
-        // lane whose row ends inside it stops exactly at the request's end.
-        const uint32_t cnt = len > k0 ? min(len - k0, (uint32_t)K) : 0;
-        uint32_t k = 0;
-#pragma unroll 1
-        for (; k + U <= cnt; k += U) {
-            uint32_t v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = bits_of<DT>(g.next());
-            if constexpr (U % 4 == 0) {
-#pragma unroll
-                for (int u = 0; u < U; u += 4) *(uint4 *)&row[k + u] = make_uint4(v[u], v[u + 1], v[u + 2], v[u + 3]);
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) row[k + u] = v[u];
-            }
-        }
-        for (; k < cnt; ++k) row[k] = bits_of<DT>(g.next());
+        batch_numbers<G, DT, U>(g, row, len > k0 ? min(len - k0, (uint32_t)K) : 0);
         RNGX_COMPILER_FENCE();
         if (aligned && k0 + K <= c && left == 64u << lgc) {  // uniform: every quad is whole
             const int r0 = lane / QPR, q = lane % QPR;
@@ -111,12 +117,55 @@ __device__ __forceinline__ void batch_tile(const BatchArgs &a, const BatchReq &q
     const uint32_t left = (uint32_t)min(rest, (uint64_t)64 << q.lgc);
     G g;
     load_uniform(g, a.ws + (uint64_t)8 * r, 1, 0);
-    const uint64_t k = (batch_far(q) ? 0 : q.offset) + first;
+    const uint64_t k = (batch_moved(q) ? 0 : q.offset) + first;
     if (k || left > 1u << q.lgc) wave_starts(g, k, q.lgc, tile, lane, a.tab);  // else one row, from the state itself
     gu32 *out = global_ptr(q.out) + first;
     if (dtype == RNG_DT_F32) batch_rows<G, RNG_DT_F32, U, K>(g, out, left, q.lgc, tile, lane);
     else batch_rows<G, RNG_DT_U32, U, K>(g, out, left, q.lgc, tile, lane);
     if (i + 1 == q.ntiles && (uint32_t)lane == (left - 1) >> q.lgc) g.store(q.state, q.stride, 0);
+}
+
+// A packed tile: lane l steps request r + l, `count` requests of one group, from its
+// own state to its end; the rows, which begin anywhere, go out one by one.
+template <class G, int DT, int U, int K>
+__device__ __forceinline__ void batch_pack_rows(G &g, const BatchReq &mine, uint32_t count, uint32_t *tile, int lane)
+{
+    constexpr int LD = K + 4;
+    const uint32_t len = (uint32_t)lane < count ? (uint32_t)mine.length : 0;
+    const uint64_t out = (uint64_t)mine.out;
+    for (uint32_t k0 = 0; __ballot(len > k0); k0 += K) {
+        batch_numbers<G, DT, U>(g, tile + lane * LD, len > k0 ? min(len - k0, (uint32_t)K) : 0);
+        RNGX_COMPILER_FENCE();
+        for (uint32_t i = 0; i < count; ++i) {
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, (int)i);
+            const uint64_t to = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(out >> 32), (int)i) << 32 |
+                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)out, (int)i);
+            const uint32_t at = k0 + (uint32_t)lane;
+            if (lane < K && at < n) global_ptr((uint32_t *)to)[at] = tile[i * LD + lane];
+        }
+        RNGX_COMPILER_FENCE();
+    }
+}
+
+template <class G, int U, int K>
+__device__ __forceinline__ void batch_pack(const BatchArgs &a, const BatchReq *reqs, uint32_t r, uint32_t count,
+                                           uint32_t dtype, uint32_t *tile, int lane)
+{
+    const uint32_t m = r + min((uint32_t)lane, count - 1);
+    const BatchReq mine = reqs[m];
+    G g;
+    g.load(a.ws + (uint64_t)8 * m, 1, 0);
+    if (dtype == RNG_DT_F32) batch_pack_rows<G, RNG_DT_F32, U, K>(g, mine, count, tile, lane);
+    else batch_pack_rows<G, RNG_DT_U32, U, K>(g, mine, count, tile, lane);
+    if ((uint32_t)lane < count) g.store(mine.state, mine.stride, 0);
+}
+
+template <class G, int U, int K>
+__device__ __forceinline__ void batch_any(const BatchArgs &a, const BatchReq *reqs, const BatchReq &q, uint32_t r, uint32_t i,
+                                          uint32_t dtype, uint32_t *tile, int lane)
+{
+    if (q.lgc >= kBatchPacked) batch_pack<G, U, K>(a, reqs, r, q.lgc - kBatchPacked + 1, dtype, tile, lane);
+    else batch_tile<G, U, K>(a, q, r, i, dtype, tile, lane);
 }
 
 // Persistent generation.  Wave w of the grid's W waves takes tile w first;
@@ -143,11 +192,11 @@ __global__ __launch_bounds__(WG) void k_batch_gen(BatchArgs a)
         const BatchGroup gr = uniform_read(a.hdr->groups + q.group);
         const uint32_t i = t - q.tile_base;
         switch (gr.gen) {
-        case G_MWC32: batch_tile<GenMWC32, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
-        case G_XS256: batch_tile<GenXS256, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
-        case G_XS32: batch_tile<GenXS32, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
-        case G_KISS: batch_tile<GenKISS, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
-        case G_MWC1616: batch_tile<GenMWC1616, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+        case G_MWC32: batch_any<GenMWC32, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
+        case G_XS256: batch_any<GenXS256, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
+        case G_XS32: batch_any<GenXS32, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
+        case G_KISS: batch_any<GenKISS, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
+        case G_MWC1616: batch_any<GenMWC1616, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
         }
         if (nwaves >= n_tiles) break;  // every tile was handed out statically
         const uint32_t lgc = uniform_read(&a.hdr->lg_counters), mine = (blockIdx.x * NW + wv) & ((1u << lgc) - 1);

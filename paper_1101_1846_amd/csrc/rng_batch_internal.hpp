@@ -6,7 +6,8 @@
 // shorter.  The wave moves its lanes from the request's start state to their
 // rows by itself (wave_starts.hpp), so no chunk states pass through memory.
 // Requests are grouped by (generator, dtype) and their tiles numbered
-// consecutively.
+// consecutively.  Of many short requests, up to 64 of a group share a tile instead,
+// one per lane.
 #pragma once
 #include <stdint.h>
 
@@ -25,6 +26,14 @@ constexpr int kBatchLgMin = 5, kBatchLgMax = 12;  // rows of 32 to 4096 samples
 // counter, 52 from 32).  Longer ones share one, which balances them best.
 constexpr uint32_t kBatchLgCounters = 5, kBatchCounterWords = 32;
 
+// kBatchPacked + c - 1 in lgc: the first of c requests that share one tile (the
+// others have none), a request per lane.  From kBatchPackMin requests of at most
+// kBatchPackMax samples on, about as many as the device holds waves: a tile of its
+// own costs each some 9 us of a wave, 8 more for XS256, a step in common 45 to 90 ns
+// (10^4 requests, us, own tiles / shared: XS256 x 100 107 / 52, x 256 105 / 67, KISS x
+// 64 82 / 46, MWC32 x 100 58 / 50, x 256 58 / 61).
+constexpr uint32_t kBatchPacked = 64, kBatchPackMin = 2048, kBatchPackMax = 256;
+
 struct BatchReq {
     uint32_t *state;     // word 0 of the stream's state
     uint64_t stride;     // word stride of that state
@@ -34,13 +43,17 @@ struct BatchReq {
     uint32_t tile_base;  // its first tile
     uint32_t ntiles;     // ceil(length / 64 2^lgc)
     uint32_t group;
-    uint32_t lgc;        // log2 of the row length
+    uint32_t lgc;        // log2 of the row length, or kBatchPacked and more
 };
 
-// A slice that ends beyond position 2^64 of its stream: a tile's position, the
-// offset and the samples before the tile, would not fit 64 bits, so the start
-// state is moved by the offset first and the tiles count from there.
-__device__ __forceinline__ bool batch_far(const BatchReq &q) { return q.offset + q.length < q.offset; }
+// Requests whose start state the root kernel moves by the offset, so that the
+// tiles count from there: a slice that ends beyond position 2^64 of its stream (a
+// tile's position, the offset and the samples before the tile, would not fit 64
+// bits), and one that shares its tile.
+__device__ __forceinline__ bool batch_moved(const BatchReq &q)
+{
+    return q.offset + q.length < q.offset || (q.lgc >= kBatchPacked && q.offset);
+}
 
 struct BatchGroup {
     uint32_t gen, dtype;

@@ -28,7 +28,7 @@ __device__ __forceinline__ void with_gen(uint32_t g, F &&f)
 // One wave per request: copies its start state (the wave that ends a request
 // writes the state while others may not have read it yet), writes the request
 // of each of its tiles, and moves the state of an empty request, or the copy of
-// one that crosses position 2^64, by `offset`.
+// one that batch_moved names, by `offset`.
 // Also clears the generation kernel's tile counters.
 constexpr int kRootWG = 256;
 
@@ -45,14 +45,14 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
     for (uint32_t r = blockIdx.x * (kRootWG / 64) + wv; r < n; r += gridDim.x * (kRootWG / 64)) {
         const BatchReq q = reqs[r];
         with_gen(hp->groups[q.group].gen, [&]<class G>() {
-            const bool far = batch_far(q);
-            if (far || (q.length == 0 && q.offset)) {
+            const bool moved = batch_moved(q);
+            if (moved || (q.length == 0 && q.offset)) {
                 G g;
                 g.load(q.state, q.stride, 0);
                 const uint64_t k = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(q.offset >> 32)) << 32 |
                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)q.offset);
                 wave_starts(g, k, kBatchLgMin, s_lds[wv], lane, a.tab);
-                if (lane == 0) g.store(far ? a.ws + (uint64_t)8 * r : q.state, far ? 1 : q.stride, 0);
+                if (lane == 0) g.store(moved ? a.ws + (uint64_t)8 * r : q.state, moved ? 1 : q.stride, 0);
             } else if (lane < G::W) {
                 a.ws[(uint64_t)8 * r + lane] = q.state[(uint64_t)lane * q.stride];
             }
