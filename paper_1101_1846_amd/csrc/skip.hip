@@ -15,9 +15,12 @@
 // nonzero hexadecimal digit of k).  With a chain of table products, one per
 // digit, in its place, the launch took 37 us for 2^20 states and a k of four
 // digits, now 34 (its look-ups take the rest), and 33 for 2^16 states and a k of
-// ten digits, now 16.  Below kXs256TableMin states (10^4: 17 us against 22) each
-// takes its own products, one per nonzero digit, by the lane or, for few,
-// by a whole wave.
+// ten digits, now 16.  A k of one digit (a table in memory) or two (one product per
+// column) needs no such sum: 65536 states 14.7 and 14.8 us with it, 6.9 and 12.5
+// without.  Below kXs256TableMin states each takes its own products, one per
+// nonzero digit, by the lane or, for few, by a whole wave; below kXs256ChainMax
+// too if there are at most two (10^4 states, us, products / sums: 7.1 / 14.5 and 11.7
+// / 14.6, but 16.4 / 14.4 for three).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -43,7 +46,7 @@ constexpr int skip_wg()
 {
     return G::kId == G_XS256 ? kSkipXs256WG : kSkipWG;
 }
-constexpr uint64_t kXs256TableMin = (uint64_t)1 << 13;
+constexpr uint64_t kXs256TableMin = (uint64_t)1 << 13, kXs256ChainMax = (uint64_t)1 << 16;
 
 struct SkipArgs {
     uint32_t *st;           // [W][ld]
@@ -52,6 +55,8 @@ struct SkipArgs {
     uint32_t lcg_a, lcg_c;  // k steps of the LCG
     uint32_t xs32[32];      // columns of M^k, xorshift32
     uint64_t poly[4];       // x^k mod the characteristic polynomial of the XS256 step
+    uint32_t digits;        // nonzero hexadecimal digits of k
+    uint32_t t4w[2];        // the tables of the first two
     DevTables tab;
 };
 
@@ -109,49 +114,84 @@ __global__ __launch_bounds__(skip_wg<G>()) void k_skip_by(SkipArgs a)
         // Column c of M^k is the XOR of M^i e_c over the set bits i of x^k mod
         // the characteristic polynomial: threads c, 256 + c, ... take 64 of the
         // 256 steps each, from the columns of M^64, M^128 and M^192 (entries of
-        // single bits in those tables).
+        // single bits in those tables).  For k of two hexadecimal digits it is the
+        // second one's map of column c of the first one's, a quarter of its 64
+        // nibbles per thread; a single digit's table is the one in memory.
         const uint32_t c = tid & 255, seg = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 8);
-        GenXS256 g;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) g.v[i] = (uint32_t)(c / 32 == (uint32_t)i) << (c % 32);
-        if (seg) {
-            const uint4 *T = a.tab.xs256_t4w + ((size_t)15 + 4 * seg - 1) * 2048 + (c >> 2) * 32 + (1u << (c & 3));
+        auto column = [&](uint32_t table, uint32_t (&v)[8]) {
+            const uint4 *T = a.tab.xs256_t4w + (size_t)table * 2048 + (c >> 2) * 32 + (1u << (c & 3));
             const uint4 lo = T[0], hi = T[16];
-            g.v[0] = lo.x;
-            g.v[1] = lo.y;
-            g.v[2] = lo.z;
-            g.v[3] = lo.w;
-            g.v[4] = hi.x;
-            g.v[5] = hi.y;
-            g.v[6] = hi.z;
-            g.v[7] = hi.w;
-        }
+            v[0] = lo.x;
+            v[1] = lo.y;
+            v[2] = lo.z;
+            v[3] = lo.w;
+            v[4] = hi.x;
+            v[5] = hi.y;
+            v[6] = hi.z;
+            v[7] = hi.w;
+        };
         uint32_t col[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        uint64_t bits = a.poly[seg];  // uniform
-#pragma unroll 1
-        for (int i = 0; i < 64; i += 8, bits >>= 8)
+        if (a.digits == 1) {
+            const uint4 *T = a.tab.xs256_t4w + (size_t)a.t4w[0] * 2048;
+            const uint4 q0 = T[tid], q1 = T[kSkipXs256WG + tid];
+            s_t4[tid] = q0;
+            s_t4[kSkipXs256WG + tid] = q1;
+        } else if (a.digits == 2) {
+            uint32_t v[8];
+            column(a.t4w[0], v);
+            const uint4 *T = a.tab.xs256_t4w + (size_t)a.t4w[1] * 2048 + seg * 512;
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                if ((bits >> b) & 1)
+            for (int h = 0; h < 2; ++h) {
+                uint32_t w = v[h];
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) col[k] ^= g.v[k];
-                g.next();
+                for (int i = 1; i < 4; ++i) w = seg == (uint32_t)i ? v[2 * i + h] : w;
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const uint32_t n = (w >> (4 * p)) & 15u;
+                    const uint4 lo = T[(8 * h + p) * 32 + n], hi = T[(8 * h + p) * 32 + 16 + n];
+                    col[0] ^= lo.x;
+                    col[1] ^= lo.y;
+                    col[2] ^= lo.z;
+                    col[3] ^= lo.w;
+                    col[4] ^= hi.x;
+                    col[5] ^= hi.y;
+                    col[6] ^= hi.z;
+                    col[7] ^= hi.w;
+                }
             }
-        uint32_t *part = (uint32_t *)s_t4;  // [4][8][256]
+        } else {
+            GenXS256 g;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) part[(seg * 8 + i) * 256 + c] = col[i];
-        __syncthreads();
-        for (uint32_t e = tid; e < 2048; e += WG)  // word e / 256 of column e % 256
-            s_col[(e & 255) * 8 + (e >> 8)] = xor3(part[e], part[2048 + e], part[4096 + e]) ^ part[6144 + e];
-        __syncthreads();
-        // quad q = (2p + h) * 16 + v: words 4h .. 4h+3 of the XOR of columns 4p + j over the set bits j of v
-        for (uint32_t q = tid; q < 2048; q += WG) {
-            const uint32_t p = q >> 5, h = (q >> 4) & 1, v = q & 15;
-            uint32_t r[4] = {0, 0, 0, 0};
-            for (int j = 0; j < 4; ++j)
-                if ((v >> j) & 1)
-                    for (int w = 0; w < 4; ++w) r[w] ^= s_col[(4 * p + j) * 8 + 4 * h + w];
-            s_t4[q] = make_uint4(r[0], r[1], r[2], r[3]);
+            for (int i = 0; i < 8; ++i) g.v[i] = (uint32_t)(c / 32 == (uint32_t)i) << (c % 32);
+            if (seg) column(15 + 4 * seg - 1, g.v);
+            uint64_t bits = a.poly[seg];  // uniform
+#pragma unroll 1
+            for (int i = 0; i < 64; i += 8, bits >>= 8)
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    if ((bits >> b) & 1)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) col[k] ^= g.v[k];
+                    g.next();
+                }
+        }
+        if (a.digits != 1) {
+            uint32_t *part = (uint32_t *)s_t4;  // [4][8][256]
+#pragma unroll
+            for (int i = 0; i < 8; ++i) part[(seg * 8 + i) * 256 + c] = col[i];
+            __syncthreads();
+            for (uint32_t e = tid; e < 2048; e += WG)  // word e / 256 of column e % 256
+                s_col[(e & 255) * 8 + (e >> 8)] = xor3(part[e], part[2048 + e], part[4096 + e]) ^ part[6144 + e];
+            __syncthreads();
+            // quad q = (2p + h) * 16 + v: words 4h .. 4h+3 of the XOR of columns 4p + j over the set bits j of v
+            for (uint32_t q = tid; q < 2048; q += WG) {
+                const uint32_t p = q >> 5, h = (q >> 4) & 1, v = q & 15;
+                uint32_t r[4] = {0, 0, 0, 0};
+                for (int j = 0; j < 4; ++j)
+                    if ((v >> j) & 1)
+                        for (int w = 0; w < 4; ++w) r[w] ^= s_col[(4 * p + j) * 8 + 4 * h + w];
+                s_t4[q] = make_uint4(r[0], r[1], r[2], r[3]);
+            }
         }
     }
     if constexpr (kMwc16 || kXs32 || kXs256) __syncthreads();
@@ -253,14 +293,13 @@ int launch_skip_by(const SkipArgs &a, hipStream_t stream)
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
     }
-    if (G::kId == G_XS256 && a.S < kXs256TableMin) {  // see the file comment
+    if (G::kId == G_XS256 && (a.S < kXs256TableMin || (a.S < kXs256ChainMax && a.digits <= 2))) {  // see the file comment
         hipLaunchKernelGGL(k_skip_each<G>, dim3((unsigned)((a.S + kSkipWG - 1) / kSkipWG)), dim3(kSkipWG), 0, stream,
                            a);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     // workgroups that build LDS tables stride over the states: one per CU
-    // for XS256 (one staged table per nonzero hexadecimal digit of k), two
-    // for MWC16
+    // for XS256, two for MWC16
     constexpr int WG = skip_wg<G>();
     const uint64_t cap = G::kId == G_XS256 ? 256 : (G::kId == G_MWC1616 || G::kId == G_KISS) ? 512 : 4096;
     const uint64_t need = (a.S + WG - 1) / WG;
@@ -281,7 +320,14 @@ int dispatch_skip(int g, uint32_t *st, uint64_t ld, uint64_t S, uint64_t k, cons
     a.k = k;
     a.tab = tab;
     if (g == RNG_MWC32) a.mwc32_f = mwc32_fold_const(k);
-    if (g == RNG_XS256 && S >= kXs256TableMin) xs256_jump_poly(k, (uint32_t *)a.poly);
+    if (g == RNG_XS256 && S > kSkipWaveMax) {
+        for (uint32_t j = 0; j < 16; ++j)
+            if (const uint32_t d = (uint32_t)(k >> (4 * j)) & 15u) {
+                if (a.digits < 2) a.t4w[a.digits] = j * 15 + d - 1;
+                ++a.digits;
+            }
+        if (S >= kXs256TableMin && a.digits > 2) xs256_jump_poly(k, (uint32_t *)a.poly);
+    }
     if ((g == RNG_XS32 || g == RNG_KISS) && S > kSkipWaveMax) xs32_lcg_jump(k, a.xs32, &a.lcg_a, &a.lcg_c);
     switch (g) {
     case RNG_MWC32: return launch_skip_by<GenMWC32>(a, s);
