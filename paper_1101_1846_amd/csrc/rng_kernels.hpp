@@ -667,8 +667,14 @@ __global__ __launch_bounds__(WG) void k_fused_pi_windows(FusedArgs a)
             G g;
             load_uniform(g, a.state, a.ld, s);
             wave_starts(g, t << (a.lgc + 6), a.lgc, s_lds[wv], lane, a.tab);
-            const uint64_t at = (t << (a.lgc + 6)) + ((uint64_t)lane << a.lgc);
-            if (at < a.N) mine += count_pairs<G, U>(g, min(a.N - at, (uint64_t)1 << a.lgc));
+            // Where 8 lanes or fewer would do, those past the end step too, for nothing:
+            // the four waves of a workgroup run at less than half the rate then (8 XS256
+            // streams of 512 numbers 19 us, of 600 15).
+            const uint64_t w0 = t << (a.lgc + 6), at = w0 + ((uint64_t)lane << a.lgc), C = (uint64_t)1 << a.lgc;
+            if (at < a.N || a.N - w0 <= 8 * C) {
+                const uint64_t cnt = count_pairs<G, U>(g, at < a.N ? min(a.N - at, C) : C);
+                mine += at < a.N ? cnt : 0;
+            }
         }
     }
     add_counts<WG>(mine, a.count);

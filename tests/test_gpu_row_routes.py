@@ -75,3 +75,23 @@ def test_xs256_pi_chunks(oracle, S, n):
     assert int(cnt.item()) == oracle.fused_pi(o, ref_st, n, threads=16)
     oracle.skip(o, end := oracle.seed(o, 8, S), n)
     assert np.array_equal(st.cpu().numpy().view(np.uint32), end)
+
+
+# few numbers per stream: a lane each up to these lengths, a window with idle lanes above
+@pytest.mark.parametrize("name,S,n", [("XS256", 1, 339), ("XS256", 1, 341), ("XS256", 300, 387), ("XS256", 300, 389),
+                                      ("XS256", 8192, 1650), ("XS256", 8192, 1651), ("KISS", 63, 319), ("KISS", 63, 321),
+                                      ("MWC32", 8, 255), ("XS32", 63, 257), ("MWC1616", 5, 513), ("KISS", 7, 512)])
+def test_pi_short(oracle, name, S, n):
+    import torch
+    import paper_1101_1846_amd as R
+    R.rng_init()
+    g, o = R.GENERATORS[name], oracle.GENERATORS[name]
+    st = torch.empty((R.rng_state_words(g), S), dtype=torch.int32, device="cuda")
+    cnt = torch.full((1,), 9, dtype=torch.int64, device="cuda")
+    R.rng_seed(g, 8, 0, S, st)
+    R.rng_fused_pi(g, st, S, n, cnt)
+    torch.cuda.synchronize()
+    ref_st = oracle.seed(o, 8, S)
+    assert int(cnt.item()) == 9 + oracle.fused_pi(o, ref_st, n, threads=8)
+    oracle.skip(o, end := oracle.seed(o, 8, S), n)
+    assert np.array_equal(st.cpu().numpy().view(np.uint32), end)
