@@ -49,6 +49,7 @@ struct rng_batch {
     unsigned gen_full = 0;                // generation workgroups resident at once for that shape
     int num_cu = 256;
     std::vector<rng_request_t> last;  // last planned table, re-planned on a chunk change
+    std::vector<uint16_t> codes;      // a plan's group and row bits per request, while it is made
     BatchHeader &hdr() { return *(BatchHeader *)h_plan; }
 };
 
@@ -303,6 +304,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
 {
     if (n > h->max_requests) return fail(RNG_ENOMEM, "%u requests > capacity %u", n, h->max_requests);
     uint64_t total_samples = 0;
+    uint32_t shorts = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
         if (check_gen(r.gen)) return fail(RNG_EINVAL, "request %u: unknown generator %d", i, r.gen);
@@ -312,6 +314,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         if (r.length && (!r.d_out || ((uintptr_t)r.d_out & 3))) return fail(RNG_EINVAL, "request %u: bad output", i);
         if (__builtin_add_overflow(total_samples, r.length, &total_samples))
             return fail(RNG_ERANGE, "total length overflows");
+        shorts += r.length - 1 < kBatchPackMax;
     }
     if (total_samples > h->max_samples)
         return fail(RNG_ENOMEM, "batch of %llu samples > capacity %llu", (unsigned long long)total_samples,
@@ -325,24 +328,35 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     }
     h->planned = false;  // until this plan is complete: a failure below leaves nothing to launch
     const uint32_t longest = (uint32_t)__builtin_ctzll(longest_row(h)), cap = row_bits(n, total_samples, longest);
+    // requests that share a tile: short enough for the rounds of tiles that this saves
+    const uint64_t pack = shorts < kBatchPackMin ? 0 : std::min<uint64_t>(kBatchPackMax, shorts / 12);
+    const uint64_t packs[6] = {0, std::min<uint64_t>(pack, 192), pack, std::min<uint64_t>(pack, 192), pack,
+                               std::min<uint64_t>(pack, 192)};  // XS256 and KISS: more per number
     // A request that one lane steps through sooner than the lanes' starts take stays
-    // one row (16 XS256 requests of 64 samples: 14.5 us as two rows, 10.7 as one).
+    // one row (16 requests, us, more rows / one: XS256 of 64 samples 14.3 / 9.5, of 100
+    // 14.7 / 12.2, KISS of 64 11.6 / 9.3).
+    static const uint64_t kOneRow[6] = {0, 32, 128, 32, 64, 32};
     auto tile_bits = [cap, longest](const rng_request_t &r) {
-        uint32_t lg = kBatchLgMin;
-        const bool one = r.offset == 0 && r.length <= (r.gen == RNG_XS256 ? 64u : 32u);
-        while (lg < (one ? longest : cap) && ((uint64_t)(one ? 1 : 64) << lg) < r.length) ++lg;
-        return lg;
+        const bool one = r.offset == 0 && r.length <= kOneRow[r.gen];
+        const uint32_t bits = r.length > 1 ? 64 - (uint32_t)__builtin_clzll(r.length - 1) : 0;  // 2^bits >= length
+        const uint32_t lg = std::max<uint32_t>(kBatchLgMin, one ? bits : bits < 6 ? 0 : bits - 6);
+        return std::min(lg, one ? longest : cap);
     };
     auto tiles_of = [](uint64_t length, uint32_t lg) { return (length + ((uint64_t)64 << lg) - 1) >> (lg + 6); };
-    // requests that share a tile: short enough for the rounds of tiles that this saves
-    uint32_t shorts = 0;
-    for (uint32_t i = 0; i < n; ++i) shorts += reqs[i].length - 1 < kBatchPackMax;
-    const uint64_t pack = shorts < kBatchPackMin ? 0 : std::min<uint64_t>(kBatchPackMax, shorts / 12);
-    auto packed = [pack](const rng_request_t &r) {  // no empty one
-        return r.length - 1 < (r.gen == RNG_XS256 || r.gen == RNG_KISS ? pack : std::min<uint64_t>(pack, 192));
-    };
+    // per request: key = 4 generator + 2 dtype + (a tile of its own), and its row bits
     uint64_t tiles = 0;
-    for (uint32_t i = 0; i < n; ++i) tiles += tiles_of(reqs[i].length, tile_bits(reqs[i]));
+    uint32_t count[32] = {0}, group[32] = {0}, begin[32] = {0};
+    h->codes.resize(n);
+    for (uint32_t i = 0; i < n; ++i) {
+        const rng_request_t &r = reqs[i];
+        const bool packed = r.length - 1 < packs[r.gen];  // no empty one
+        const uint32_t key = (uint32_t)r.gen * 4 + (uint32_t)r.dtype * 2 + !packed;
+        const uint32_t lg = packed ? kBatchPacked : tile_bits(r);
+        h->codes[i] = (uint16_t)(key << 8 | lg);
+        ++count[key];
+        tiles += packed ? 0 : tiles_of(r.length, lg);
+    }
+    for (uint32_t k = 0; k < 32; k += 2) tiles += (count[k] + 63) / 64;
     if (tiles > h->map_cap)
         return fail(RNG_ENOMEM, "batch needs %llu tiles > %llu", (unsigned long long)tiles, (unsigned long long)h->map_cap);
     // requests by (generator, dtype), those that share tiles first, in table order
@@ -352,10 +366,6 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     H.n = n;
     H.off_reqs = (uint32_t)align16(sizeof(BatchHeader));
     BatchReq *Q = plan_at<BatchReq>(&H, H.off_reqs);
-    // by key = 4 generator + 2 dtype + (a tile of its own)
-    uint32_t count[32] = {0}, group[32] = {0}, begin[32] = {0};
-    auto key = [&](const rng_request_t &r) { return (uint32_t)r.gen * 4 + (uint32_t)r.dtype * 2 + !packed(r); };
-    for (uint32_t i = 0; i < n; ++i) ++count[key(reqs[i])];
     uint32_t at = 0;
     for (uint32_t k = 0; k < 32; ++k) {
         begin[k] = at;
@@ -366,10 +376,9 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     }
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
-        const uint32_t k = key(r);
-        const uint32_t lg = packed(r) ? kBatchPacked : tile_bits(r);
+        const uint32_t k = h->codes[i] >> 8, lg = h->codes[i] & 255;
         Q[begin[k]++] = BatchReq{r.d_state, r.state_stride, r.offset, r.length, (uint32_t *)r.d_out,
-                                 0, packed(r) ? 0 : (uint32_t)tiles_of(r.length, lg), group[k], lg};
+                                 0, lg == kBatchPacked ? 0 : (uint32_t)tiles_of(r.length, lg), group[k], lg};
     }
     for (uint32_t k = 0; k < 32; k += 2)  // begin[k] is their end now
         for (uint32_t i = 0; i < count[k]; i += 64) {

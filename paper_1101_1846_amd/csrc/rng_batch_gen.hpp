@@ -69,7 +69,11 @@ __device__ __forceinline__ void batch_rows(G &g, gu32 *out, uint32_t left, uint3
     static_assert(K % U == 0 && K % 4 == 0, "tile depth");
     constexpr int LD = K + 4, QPR = K / 4, RPI = 64 / QPR;
     const uint32_t c = 1u << lgc, at = (uint32_t)lane << lgc;
-    const uint32_t len = left > at ? min(left - at, c) : 0, longest = min(left, c);
+    // With 8 rows or fewer the other lanes step too, for nothing (their numbers stay in
+    // LDS): a wave with so few lanes at work runs at less than half the rate beside
+    // others (16 XS256 requests of 64 samples 9.9 us, so 8.6).
+    const uint32_t longest = min(left, c), idle = left <= 8 * c ? longest : 0;
+    const uint32_t len = left > at ? min(left - at, c) : idle;
     const bool aligned = ((uintptr_t)out & 15) == 0;
     uint32_t *row = tile + lane * LD;
     for (uint32_t k0 = 0; k0 < longest; k0 += K) {
