@@ -107,9 +107,14 @@ int rng_generate(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, int t
                  void *d_out, void *stream);
 
 /* Same, with an explicit launch shape: wg in {64,128,256,512,1024} lanes per
- * workgroup and unroll in {1,2,4,8,16} samples per generation-loop step.
+ * workgroup and unroll in {1,2,4,8,16} samples per generation-loop step, for the
+ * calls that the whole-tile kernel takes.  Long sequences of few streams run as
+ * windows in a shape of their own whatever is asked for, and so do chunks of
+ * streams and rows that are no whole tiles (n a multiple of 128, n_streams of 64,
+ * d_out 16-byte aligned) unless wg is above 256, which keeps them on that kernel.
  * rng_generate uses the autotuned shape when one is loaded, else a default;
- * rows of 4 or 8 KiB over whole groups of runs have a shape of their own
+ * it decides about whole tiles only.
+ * Rows of 4 or 8 KiB over whole groups of runs have a shape of their own
  * (below), and for other XS256 rows of an odd number of 4 KiB
  * (n = 1024 (2i + 1)) it takes at least 512 lanes, which generate each row
  * as four jumped chunks so that concurrent writes spread over four column
@@ -126,11 +131,13 @@ int rng_generate_ex(int g, uint32_t *d_state, uint64_t n_streams, uint64_t n, in
  *
  * Shapes are kept per row class.  Rows of 4 or 8 KiB (n = 1024 or 2048)
  * over a stream count that is a multiple of 256 or 128 are written as 16 KiB
- * runs of 4 or 2 adjacent rows per lane (on workgroups of up to 256 lanes),
- * and have a shape of their own (default 64 lanes, unroll 16); every other
- * problem uses the shape that rng_set_shape / rng_get_shape address (default
- * 256 lanes, unroll 8).  rng_autotune keeps its pick for the class of the
- * problem it timed; rng_set_row_shape sets, and rng_row_shape reads, the
+ * runs of 4 or 2 adjacent rows per lane (on workgroups of up to 256 lanes, from
+ * 257 runs of 64 lanes on), and have a shape of their own (default 64 lanes,
+ * unroll 16); every other problem uses the shape that rng_set_shape /
+ * rng_get_shape address (default 256 lanes, unroll 8).  rng_autotune keeps its
+ * pick for the class of the problem it timed; a call whose kernels have a shape
+ * of their own is timed once, changes no stored shape and reports the one in
+ * force.  rng_set_row_shape sets, and rng_row_shape reads, the
  * shape rng_generate will use for n_streams x n (for XS256 rows of an odd
  * number of 4 KiB outside the run class, at least 512 lanes). */
 int rng_set_shape(int g, int t, uint32_t wg, uint32_t unroll);
@@ -180,7 +187,8 @@ int rng_skip(int g, uint32_t *d_state, uint64_t n_streams, uint64_t k, void *str
  * cut into blocks of consecutive samples that suit the device; n_threads only
  * sizes the workspace.  d_workspace of at least
  * rng_split_workspace_bytes(g, n_threads) bytes, 256-byte aligned, caller
- * owned, holds a copy of the start state when the final one overlaps it. */
+ * owned, holds a copy of the start state when the final one or the output
+ * overlaps it.  A final state inside the output is written last. */
 int rng_split_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes);
 int rng_generate_split(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                        int t, void *d_out, uint32_t *d_final_state, void *d_workspace,
@@ -188,8 +196,8 @@ int rng_generate_split(int g, const uint32_t *d_state_one, uint64_t total, uint6
 
 /* For callers that cannot allocate (code under HIP graph capture, serving
  * loops, harnesses that forbid hipMalloc): rng_generate_split without a
- * workspace argument.  A start state that the final one overlaps is copied to
- * a small device array that the library holds on every device it runs on until
+ * workspace argument.  A start state that the final one or the output overlaps is
+ * copied to a small device array that the library holds on every device it runs on until
  * the process ends; the call itself makes no hipMalloc, hipFree or other
  * allocating call.  rng_init() must have run on the current device (it builds
  * the tables and looks up the array's address), else RNG_EINVAL.  Splits whose
@@ -212,7 +220,7 @@ int rng_generate_split_noalloc(int g, const uint32_t *d_state_one, uint64_t tota
  * d_final_state ([words], device; may alias d_state_one).  d_workspace of at
  * least rng_leapfrog_workspace_bytes(g, T) bytes, T = min(n_threads, total),
  * 256-byte aligned, caller owned, holds a copy of the start state when the
- * final one overlaps it.  Errors as rng_generate_split. */
+ * final one or the output overlaps it.  Errors as rng_generate_split. */
 int rng_leapfrog_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes);
 int rng_generate_leapfrog(int g, const uint32_t *d_state_one, uint64_t total, uint64_t n_threads,
                           int t, void *d_out, uint32_t *d_final_state, void *d_workspace,
@@ -267,10 +275,11 @@ int rng_xs256_placement(int placement, uint32_t *d_state, uint64_t n_streams, ui
 /* in one persistent generation launch (after the root launch, issued       */
 /* directly or replayed as a captured HIP graph).  Each request is a slice  */
 /* [offset, offset + length) of one stream's serial sequence; the stream's  */
-/* state is advanced by offset + length.  Requests are cut into chunks of C */
-/* samples, 64 of them to a tile; the persistent kernel's waves pull tiles  */
-/* from an atomic counter, jump the request's state to the tile and start   */
-/* their lanes from it.                                                     */
+/* state is advanced by offset + length, which may exceed 2^64.  Requests   */
+/* are cut into chunks of C samples, 64 of them to a tile (of thousands of  */
+/* short ones, up to 64 share a tile); the persistent kernel's waves pull   */
+/* tiles from atomic counters, jump the request's state to the tile and     */
+/* start their lanes from it.                                               */
 /* ---------------------------------------------------------------------- */
 typedef struct {
     int32_t gen;            /* rng_gen_t */
@@ -315,7 +324,8 @@ int rng_batch_set_graph(rng_batch_t *h, int use_graph);
  * 1024} and unroll (samples per generation step) in {1, 2, 4, 8, 16}, every
  * pair built (others RNG_EINVAL; 1024-lane workgroups stage 32-sample LDS
  * tiles, the others 64); and chunk length C (a multiple of 64).  0 keeps the
- * current value.  A lane produces consecutive samples of one request, at most
+ * current value; until a wg is given, plans of few tiles may go out as
+ * workgroups of 64 lanes.  A lane produces consecutive samples of one request, at most
  * the power of two below C or 4096; a plan takes fewer where the batch is too
  * small to fill the device with rows that long.  chunk = RNG_BATCH_CHUNK_AUTO
  * allows 4096.  A changed C applies to the last planned table at once (it is
@@ -326,8 +336,9 @@ int rng_batch_set_shape(rng_batch_t *h, uint32_t wg, uint32_t unroll, uint32_t c
 int rng_batch_get_shape(rng_batch_t *h, uint32_t *wg, uint32_t *unroll, uint32_t *chunk);
 /* Time the planned batch under every persistent-kernel shape (the 25 pairs
  * wg x unroll) and chunk length in {512, 1024, 2048, 4096}, reps launches
- * each after one warm-up launch, and keep the fastest.  Every trial launch runs the batch, so the request states
- * advance and the outputs are overwritten. */
+ * each after one warm-up launch, and keep the fastest.  Chunk lengths that plan
+ * the same rows are timed once, as the longest of them.  Every trial launch runs
+ * the batch, so the request states advance and the outputs are overwritten. */
 int rng_batch_autotune(rng_batch_t *h, uint32_t reps, uint32_t *best_wg, uint32_t *best_unroll,
                        uint32_t *best_chunk, float *best_us, void *stream);
 int rng_batch_destroy(rng_batch_t *h);

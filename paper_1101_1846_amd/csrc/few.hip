@@ -6,10 +6,11 @@
 // the wave's LDS tile, and the tile goes out row by row through per-row
 // destination pointers, consecutive lanes on consecutive 16-byte quads.  No
 // chunk writes the state back (the others read it at unordered times): the
-// host advances the states by N with a skip launch afterwards.  Only rows too
-// short for windows of consecutive numbers (seq.hip) come here, with launch
-// shapes of more than 256 lanes (rows.hip takes the others), so never XS256,
-// whose chunks are longer.
+// host advances the states by N with a skip launch afterwards.  Only short rows
+// come here, those that rows.hip would take longer for (general_rows: up to 128
+// numbers, MWC32 up to 340), and with a shape of more than 256 lanes that the caller
+// asked for all that are too short for windows (seq.hip); never XS256, whose chunks
+// are longer.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -9,23 +9,6 @@
 #include "rng.h"
 #include "rng_abi_internal.hpp"
 
-namespace rngx {
-
-namespace {
-
-// Parts of the workspace size that callers rely on (only the start state's
-// copy is used).
-constexpr uint64_t kConstBytes = 256;
-constexpr uint64_t kColBytes = 256 * 8 * 4;
-constexpr uint64_t kTableBytes = 2048 * 16;
-constexpr uint64_t kByteTableBytes = 4 * 256 * 4;
-
-uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
-
-}  // namespace
-
-}  // namespace rngx
-
 using namespace rngx;
 
 extern "C" {
@@ -35,9 +18,10 @@ int rng_leapfrog_workspace_bytes(int g, uint64_t n_threads, uint64_t *bytes)
     if (check_gen(g)) return RNG_EINVAL;
     if (!bytes) return fail(RNG_EINVAL, "bytes is NULL");
     if (n_threads > ((uint64_t)1 << 36)) return fail(RNG_ERANGE, "n_threads above 2^36");
-    const bool bytes_t = g == RNG_XS32 || g == RNG_KISS;
-    *bytes = align256(n_threads * gen_words(g) * 4) + kConstBytes + (g == RNG_XS256 ? kColBytes + kTableBytes : 0) +
-             (bytes_t ? kByteTableBytes : 0);
+    // One copy of a state is used of it.  The size, a state per thread and the
+    // tables of a leap by n_threads steps, is the one that callers have been given.
+    const uint64_t states = (n_threads * gen_words(g) * 4 + 255) & ~(uint64_t)255;
+    *bytes = states + 256 + (g == RNG_XS256 ? 40960 : g == RNG_XS32 || g == RNG_KISS ? 4096 : 0);
     return RNG_OK;
 }
 

@@ -220,9 +220,9 @@ void lane_chunks(int g, uint64_t S, uint64_t N, uint64_t *C, uint32_t *P)
     *P = (uint32_t)((N + c - 1) / c);
 }
 
-// Lanes that chunked bulk generation by k_generate aims for (shapes of more than
-// 256 lanes, general_rows, XS256 above the sequences' stream counts): the waves the device holds at
-// once with 128-deep LDS tiles (4 per CU, 256 CUs) times 64.  Measured
+// Lanes that chunked bulk generation by k_generate aims for (general_rows, shapes of
+// more than 256 lanes asked for, XS256 above the sequences' stream counts): the waves
+// the device holds at once with 128-deep LDS tiles (4 per CU, 256 CUs) times 64.  Measured
 // against 2^17 and 2^15 over 64..65536 streams: 2^16 is 15-40 % faster than
 // 2^17 for MWC32 and KISS and equal for XS256; 2^15 slows XS256 and KISS.
 constexpr uint64_t kGenLanes = (uint64_t)1 << 16;

@@ -52,8 +52,8 @@ int launch_seq(int g, int dt, const uint32_t *state, uint64_t ld, uint64_t S, ui
                uint32_t *final_state, const DevTables &tab, hipStream_t st);
 int launch_seq_xs256(int dt, const uint32_t *state, uint64_t ld, uint64_t S, uint64_t N, void *out,
                      uint32_t *final_state, const DevTables &tab, hipStream_t st);
-// One sequence of `total` numbers through launch_seq; a final state that
-// overlaps the start state goes by a copy of it in ws (one state).
+// One sequence of `total` numbers through launch_seq; start and final states may lie
+// anywhere: those that overlap each other or the output go through ws (one state).
 int seq_run(int g, const uint32_t *state_one, uint64_t total, int t, void *out, uint32_t *final_state, uint32_t *ws,
             const DevTables &tab, hipStream_t st);
 
@@ -70,8 +70,8 @@ int device_tables_if_ready(DevTables *out);
 // Looks up, once per device, the address of the allocation-free entry
 // point's scratch array on the current device (called by rng_init).
 int scratch_init_current_device();
-// Sequence splitting: argument checks, the workspace a split needs, and the
-// launches themselves (thread states in ws, [W][T] words).
+// Sequence splitting: argument checks, the workspace that a caller has to bring (a
+// state per thread; one is used), and the launches themselves (seq_run).
 int split_args_check(uint64_t total, uint64_t n_threads, const void *d_out, const uint32_t *d_state_one,
                      const uint32_t *d_final_state);
 int split_scratch_bytes(int g, uint64_t total, uint64_t n_threads, uint64_t *bytes);

@@ -350,7 +350,9 @@ __device__ __forceinline__ T uniform_read(const T *p)
 
 // Stream s's state for a whole wave (s uniform) through the scalar cache: with
 // vector loads every wave of a launch that starts from one state asks the same
-// L2 channel for each word, 18000 clocks for 1024 waves and 8 words.
+// L2 channel for each word, 18000 clocks for 1024 waves and 8 words.  No other wave
+// of the launch may write these words, and this one only what it works out from
+// them (k_skip_wave's states in place): the scalar cache sees no store.
 template <class G>
 __device__ __forceinline__ void load_uniform(G &g, const uint32_t *st, uint64_t ld, uint64_t s)
 {
