@@ -168,7 +168,7 @@ template <class G, int U, int K>
 __device__ __forceinline__ void batch_any(const BatchArgs &a, const BatchReq *reqs, const BatchReq &q, uint32_t r, uint32_t i,
                                           uint32_t dtype, uint32_t *tile, int lane)
 {
-    if (q.lgc >= kBatchPacked) batch_pack<G, U, K>(a, reqs, r, q.lgc - kBatchPacked + 1, dtype, tile, lane);
+    if (__builtin_expect(q.lgc >= kBatchPacked, 0)) batch_pack<G, U, K>(a, reqs, r, q.lgc - kBatchPacked + 1, dtype, tile, lane);
     else batch_tile<G, U, K>(a, q, r, i, dtype, tile, lane);
 }
 
