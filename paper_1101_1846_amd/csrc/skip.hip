@@ -16,11 +16,11 @@
 // digit, in its place, the launch took 37 us for 2^20 states and a k of four
 // digits, now 34 (its look-ups take the rest), and 33 for 2^16 states and a k of
 // ten digits, now 16.  A k of one digit (a table in memory) or two (one product per
-// column) needs no such sum: 65536 states 14.7 and 14.8 us with it, 6.9 and 12.5
-// without.  Below kXs256TableMin states each takes its own products, one per
-// nonzero digit, by the lane or, for few, by a whole wave; below kXs256ChainMax
-// too if there are at most two (10^4 states, us, products / sums: 7.1 / 14.5 and 11.7
-// / 14.6, but 16.4 / 14.4 for three).
+// column) needs no such sum: 65536 states 14.7 and 14.8 us with it, 6.5 and 12.2
+// without, 2^20 29.9 and 29.6, 21.9 and 26.9.  Below kXs256TableMin states each
+// takes its own products, one per nonzero digit, by the lane or, for few, by a
+// whole wave; below kXs256ChainMax too if there are at most two (10^4 states, us,
+// products / sums: 7.1 / 14.5 and 11.7 / 14.6, but 16.4 / 14.4 for three).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -38,8 +38,9 @@ constexpr int kSkipWG = 256;
 // built, and 16 waves per CU share the LDS reads when they apply it.  (Splitting
 // a product's nibbles over the four lanes of a quad reads four table rows at
 // once, whose entries share LDS banks; products on the matrix cores, as parities
-// of FP4 sums, take longer over packing the bits than the look-ups: 25 against
-// 16 us per 2^20 states.)
+// of FP4 sums, take longer over packing the bits than the look-ups alone: 25
+// against 16 us per 2^20 states; with the states' 64 MB and the launch a k of one
+// digit, which builds nothing, takes 22.)
 constexpr int kSkipXs256WG = 1024;
 template <class G>
 constexpr int skip_wg()
@@ -76,7 +77,8 @@ __device__ __forceinline__ uint32_t lds_t392_index(const uint16_t *t, uint32_t a
     return lo;
 }
 
-template <class G>
+// kFew: XS256 and a k of one or two nonzero hexadecimal digits.
+template <class G, bool kFew = false>
 __global__ __launch_bounds__(skip_wg<G>()) void k_skip_by(SkipArgs a)
 {
     constexpr int WG = skip_wg<G>();
@@ -131,32 +133,34 @@ __global__ __launch_bounds__(skip_wg<G>()) void k_skip_by(SkipArgs a)
             v[7] = hi.w;
         };
         uint32_t col[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (a.digits == 1) {
-            const uint4 *T = a.tab.xs256_t4w + (size_t)a.t4w[0] * 2048;
-            const uint4 q0 = T[tid], q1 = T[kSkipXs256WG + tid];
-            s_t4[tid] = q0;
-            s_t4[kSkipXs256WG + tid] = q1;
-        } else if (a.digits == 2) {
-            uint32_t v[8];
-            column(a.t4w[0], v);
-            const uint4 *T = a.tab.xs256_t4w + (size_t)a.t4w[1] * 2048 + seg * 512;
+        if constexpr (kFew) {
+            if (a.digits == 1) {
+                const uint4 *T = a.tab.xs256_t4w + (size_t)a.t4w[0] * 2048;
+                const uint4 q0 = T[tid], q1 = T[kSkipXs256WG + tid];
+                s_t4[tid] = q0;
+                s_t4[kSkipXs256WG + tid] = q1;
+            } else {
+                uint32_t v[8];
+                column(a.t4w[0], v);
+                const uint4 *T = a.tab.xs256_t4w + (size_t)a.t4w[1] * 2048 + seg * 512;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t w = v[h];
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t w = v[h];
 #pragma unroll
-                for (int i = 1; i < 4; ++i) w = seg == (uint32_t)i ? v[2 * i + h] : w;
+                    for (int i = 1; i < 4; ++i) w = seg == (uint32_t)i ? v[2 * i + h] : w;
 #pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const uint32_t n = (w >> (4 * p)) & 15u;
-                    const uint4 lo = T[(8 * h + p) * 32 + n], hi = T[(8 * h + p) * 32 + 16 + n];
-                    col[0] ^= lo.x;
-                    col[1] ^= lo.y;
-                    col[2] ^= lo.z;
-                    col[3] ^= lo.w;
-                    col[4] ^= hi.x;
-                    col[5] ^= hi.y;
-                    col[6] ^= hi.z;
-                    col[7] ^= hi.w;
+                    for (int p = 0; p < 8; ++p) {
+                        const uint32_t n = (w >> (4 * p)) & 15u;
+                        const uint4 lo = T[(8 * h + p) * 32 + n], hi = T[(8 * h + p) * 32 + 16 + n];
+                        col[0] ^= lo.x;
+                        col[1] ^= lo.y;
+                        col[2] ^= lo.z;
+                        col[3] ^= lo.w;
+                        col[4] ^= hi.x;
+                        col[5] ^= hi.y;
+                        col[6] ^= hi.z;
+                        col[7] ^= hi.w;
+                    }
                 }
             }
         } else {
@@ -175,7 +179,7 @@ __global__ __launch_bounds__(skip_wg<G>()) void k_skip_by(SkipArgs a)
                     g.next();
                 }
         }
-        if (a.digits != 1) {
+        if (!kFew || a.digits != 1) {
             uint32_t *part = (uint32_t *)s_t4;  // [4][8][256]
 #pragma unroll
             for (int i = 0; i < 8; ++i) part[(seg * 8 + i) * 256 + c] = col[i];
@@ -304,6 +308,12 @@ int launch_skip_by(const SkipArgs &a, hipStream_t stream)
     const uint64_t cap = G::kId == G_XS256 ? 256 : (G::kId == G_MWC1616 || G::kId == G_KISS) ? 512 : 4096;
     const uint64_t need = (a.S + WG - 1) / WG;
     const unsigned blocks = (unsigned)(need < cap ? need : cap);
+    if constexpr (G::kId == G_XS256) {
+        if (a.digits <= 2) {
+            hipLaunchKernelGGL((k_skip_by<G, true>), dim3(blocks), dim3(WG), 0, stream, a);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        }
+    }
     hipLaunchKernelGGL(k_skip_by<G>, dim3(blocks), dim3(WG), 0, stream, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
