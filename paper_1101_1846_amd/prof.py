@@ -17,6 +17,7 @@ SQ_INSTS_VALU run of ``bench.py --profile fused`` and prints the record that
 and of its calibration loop).
 """
 import json
+import re
 import sqlite3
 import sys
 from collections import defaultdict
@@ -33,7 +34,7 @@ def _rows(db, sql):
 
 
 def short(name, width=96):
-    name = name.replace("rngx::", "").replace("(GenArgs)", "")
+    name = name.replace("rngx::", "").replace("(anonymous namespace)::", "").replace("(GenArgs)", "")
     return name if len(name) <= width else name[: width - 3] + "..."
 
 
@@ -149,12 +150,17 @@ def step_table(db, bench_line):
     dom = line["roofline"]["kernel"]
     for key, sh in line["launch_shapes"].items():
         g, d = key.split("_")
-        pat = "k_generate<Gen%s, %d, %d, %d, 128, 2>" % (g, 1 if d == "f32" else 0, sh["wg"], sh["unroll"])
-        durs = [dur / 1000.0 for n, st, dur in rows if pat in n and st < t_fill][-steps:]
+        # a generator can have more than one form of its step (GenKISS, GenKISSMad): the last one launched
+        pat = re.compile(r"k_generate<Gen%s\w*, %d, %d, %d, 128, 2>" % (g, 1 if d == "f32" else 0, sh["wg"],
+                                                                        sh["unroll"]))
+        found = [(m.group(), dur / 1000.0) for m, dur in ((pat.search(n), dur) for n, st, dur in rows if st < t_fill)
+                 if m]
+        kernel = found[-1][0]
+        durs = [dur for n, dur in found if n == kernel][-steps:]
         ev = "%.2f" % (line["per_kernel"][key]["ms"] * 1e3)
         if "<%s>" % key in dom:
             ev += " (timed steps: %.2f)" % (line["roofline"]["avg_launch_ms"] * 1e3)
-        out.append("| %s | %d | %.2f | %.2f | %.2f | %s |" % (pat, len(durs), sum(durs) / len(durs), min(durs),
+        out.append("| %s | %d | %.2f | %.2f | %.2f | %s |" % (kernel, len(durs), sum(durs) / len(durs), min(durs),
                                                             max(durs), ev))
     return "\n".join(out)
 
