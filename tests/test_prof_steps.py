@@ -4,10 +4,9 @@ step the call took."""
 import json
 import sqlite3
 
-from paper_1101_1846_amd import prof
-
 
 def test_step_table_takes_every_form_of_a_step(tmp_path):
+    from paper_1101_1846_amd import prof  # not at collection: torch loads its HIP runtime first
     db, line = str(tmp_path / "run.db"), str(tmp_path / "line.json")
     con = sqlite3.connect(db)
     con.execute("create table kernels (name text, start integer, duration integer)")
