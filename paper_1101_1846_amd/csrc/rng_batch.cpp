@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "rng.h"
@@ -49,7 +50,7 @@ struct rng_batch {
     unsigned gen_full = 0;                // generation workgroups resident at once for that shape
     int num_cu = 256;
     std::vector<rng_request_t> last;  // last planned table, re-planned on a chunk change
-    std::vector<uint16_t> codes;      // a plan's group and row bits per request, while it is made
+    std::vector<uint16_t> codes;      // [max_requests] group and row bits, while a plan is made
     BatchHeader &hdr() { return *(BatchHeader *)h_plan; }
 };
 
@@ -191,6 +192,13 @@ int rng_batch_create(uint32_t max_requests, uint64_t max_samples, rng_batch_t **
         (e = hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking)) != hipSuccess)
         rc = hip_fail(e, "rng_batch_create");
     if (!rc) rc = alloc_ws(h);
+    if (!rc) {
+        try {
+            h->codes.resize(max_requests);
+        } catch (const std::bad_alloc &) {
+            rc = fail(RNG_ENOMEM, "no host memory for %u requests", max_requests);
+        }
+    }
     if (rc) {
         free_batch(h);
         return rc;
@@ -346,7 +354,6 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     // per request: key = 4 generator + 2 dtype + (a tile of its own), and its row bits
     uint64_t tiles = 0;
     uint32_t count[32] = {0}, group[32] = {0}, begin[32] = {0};
-    h->codes.resize(n);
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
         const bool packed = r.length - 1 < packs[r.gen];  // no empty one
