@@ -308,11 +308,42 @@ int rngx::batch_set_distinct(rng_batch_t *h, const rng_request_t *reqs, uint32_t
 
 extern "C" {
 
+// Lengths from which on each generator's requests keep a tile of their own, from the
+// counts of those up to kBatchPackMax by generator and length: the shared tiles take
+// as long as their longest request, a step in common each, the others the sum of their
+// starts, both at once, so the limits lie where the two meet.  Times in 0.1 ns, measured
+// on 2500 to 100000 requests of 16 to 4000 samples; a step takes longer the more shared
+// tiles there are.
+constexpr uint32_t kPackBin = 64, kPackBins = kBatchPackMax / kPackBin;
+static void packed_lengths(const uint32_t (&count)[6][kPackBins], uint64_t (&packs)[6])
+{
+    static const uint64_t kOwnTile[6] = {0, 17, 62, 27, 38, 24}, kStep[6] = {1, 540, 740, 630, 700, 550};
+    uint64_t upto[6][kPackBins + 1], shorts = 0, packed = 0;  // upto[g][b]: requests in the first b bins
+    for (uint32_t g = 1; g < 6; ++g) {
+        packs[g] = upto[g][0] = 0;
+        for (uint32_t b = 0; b < kPackBins; ++b) upto[g][b + 1] = upto[g][b] + count[g][b];
+        shorts += upto[g][kPackBins];
+    }
+    if (shorts < kBatchPackMin) return;
+    for (uint64_t x = kPackBin * 540;; x += kPackBin * 540) {
+        uint64_t own = 0, in = 0, least = kPackBins;
+        for (uint32_t g = 1; g < 6; ++g) {
+            const uint64_t bins = std::min<uint64_t>(x * 131072 / (kPackBin * kStep[g] * (131072 + packed)), kPackBins);
+            packs[g] = bins * kPackBin;
+            in += upto[g][bins];
+            own += (upto[g][kPackBins] - upto[g][bins]) * kOwnTile[g];
+            least = std::min(least, bins);
+        }
+        packed = in;
+        if (own <= x || least == kPackBins) return;
+    }
+}
+
 static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
 {
     if (n > h->max_requests) return fail(RNG_ENOMEM, "%u requests > capacity %u", n, h->max_requests);
     uint64_t total_samples = 0;
-    uint32_t shorts = 0;
+    uint32_t short_of[6][kPackBins] = {{0}};
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
         if (check_gen(r.gen)) return fail(RNG_EINVAL, "request %u: unknown generator %d", i, r.gen);
@@ -322,7 +353,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         if (r.length && (!r.d_out || ((uintptr_t)r.d_out & 3))) return fail(RNG_EINVAL, "request %u: bad output", i);
         if (__builtin_add_overflow(total_samples, r.length, &total_samples))
             return fail(RNG_ERANGE, "total length overflows");
-        shorts += r.length - 1 < kBatchPackMax;
+        if (r.length - 1 < kBatchPackMax) ++short_of[r.gen][(r.length - 1) / kPackBin];
     }
     if (total_samples > h->max_samples)
         return fail(RNG_ENOMEM, "batch of %llu samples > capacity %llu", (unsigned long long)total_samples,
@@ -336,10 +367,8 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     }
     h->planned = false;  // until this plan is complete: a failure below leaves nothing to launch
     const uint32_t longest = (uint32_t)__builtin_ctzll(longest_row(h)), cap = row_bits(n, total_samples, longest);
-    // requests that share a tile: short enough for the rounds of tiles that this saves
-    const uint64_t pack = shorts < kBatchPackMin ? 0 : std::min<uint64_t>(kBatchPackMax, shorts / 12);
-    const uint64_t packs[6] = {0, std::min<uint64_t>(pack, 192), pack, std::min<uint64_t>(pack, 192), pack,
-                               std::min<uint64_t>(pack, 192)};  // XS256 and KISS: more per number
+    uint64_t packs[6];
+    packed_lengths(short_of, packs);
     // A request that one lane steps through sooner than the lanes' starts take stays
     // one row (16 requests, us, more rows / one: XS256 of 64 samples 14.3 / 9.5, of 100
     // 14.7 / 12.2, KISS of 64 11.6 / 9.3).
@@ -351,23 +380,23 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         return std::min(lg, one ? longest : cap);
     };
     auto tiles_of = [](uint64_t length, uint32_t lg) { return (length + ((uint64_t)64 << lg) - 1) >> (lg + 6); };
-    // per request: key = 4 generator + 2 dtype + (a tile of its own), and its row bits
+    // per request: key = 16 (a tile of its own) + 2 generator + dtype, and its row bits
     uint64_t tiles = 0;
     uint32_t count[32] = {0}, group[32] = {0}, begin[32] = {0};
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
         const bool packed = r.length - 1 < packs[r.gen];  // no empty one
-        const uint32_t key = (uint32_t)r.gen * 4 + (uint32_t)r.dtype * 2 + !packed;
+        const uint32_t key = (packed ? 0 : 16) + (uint32_t)r.gen * 2 + (uint32_t)r.dtype;
         const uint32_t lg = packed ? kBatchPacked : tile_bits(r);
         h->codes[i] = (uint16_t)(key << 8 | lg);
         ++count[key];
         tiles += packed ? 0 : tiles_of(r.length, lg);
     }
-    for (uint32_t k = 0; k < 32; k += 2) tiles += (count[k] + 63) / 64;
+    for (uint32_t k = 0; k < 16; ++k) tiles += (count[k] + 63) / 64;
     if (tiles > h->map_cap)
         return fail(RNG_ENOMEM, "batch needs %llu tiles > %llu", (unsigned long long)tiles, (unsigned long long)h->map_cap);
-    // requests by (generator, dtype), those that share tiles first, in table order
-    // within each
+    // requests by (generator, dtype), in table order within each; all that share tiles
+    // come first, as these take longest
     BatchHeader &H = h->hdr();
     std::memset(&H, 0, sizeof(H));
     H.n = n;
@@ -377,17 +406,19 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     for (uint32_t k = 0; k < 32; ++k) {
         begin[k] = at;
         at += count[k];
-        if (!count[k & ~1u] && !count[k | 1u]) continue;
-        if (k % 2 == 0) H.groups[H.ngroups++] = BatchGroup{k / 4, k / 2 % 2};
-        group[k] = H.ngroups - 1;
     }
+    for (uint32_t k = 0; k < 16; ++k)
+        if (count[k] || count[16 + k]) {
+            group[k] = group[16 + k] = H.ngroups;
+            H.groups[H.ngroups++] = BatchGroup{k / 2, k % 2};
+        }
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
         const uint32_t k = h->codes[i] >> 8, lg = h->codes[i] & 255;
         Q[begin[k]++] = BatchReq{r.d_state, r.state_stride, r.offset, r.length, (uint32_t *)r.d_out,
                                  0, lg == kBatchPacked ? 0 : (uint32_t)tiles_of(r.length, lg), group[k], lg};
     }
-    for (uint32_t k = 0; k < 32; k += 2)  // begin[k] is their end now
+    for (uint32_t k = 0; k < 16; ++k)  // begin[k] is their end now
         for (uint32_t i = 0; i < count[k]; i += 64) {
             BatchReq &first = Q[begin[k] - count[k] + i];
             first.ntiles = 1;
@@ -449,8 +480,9 @@ int rng_batch_launch(rng_batch_t *h, void *stream)
             // is long: four waves that share one slow each other down (16 XS256 requests
             // of 64 samples 15.3 us in workgroups of 256 lanes, 10.7 of 64, 100 of them
             // 22.4 and 16.8; no difference from 300 on; but 16 MWC32 requests of 1000
-            // 7.7 and 8.5, and one XS256 request of two tiles 13.1 and 14.9).
-            bool slow = false;
+            // 7.7 and 8.5, and one XS256 request of two tiles 13.1 and 14.9).  So many
+            // requests in so few tiles share them, which is long too.
+            bool slow = H.n >= kBatchPackMin;
             for (uint32_t i = 0; i < H.ngroups; ++i) slow |= H.groups[i].gen == G_XS256 || H.groups[i].gen == G_KISS;
             const bool alone = !h->wg_asked && slow && H.n_tiles > h->wg / 64 && H.n_tiles <= (uint32_t)h->num_cu;
             const uint32_t wg = alone ? 64 : h->wg;

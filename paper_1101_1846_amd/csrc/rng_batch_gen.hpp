@@ -135,17 +135,26 @@ template <class G, int DT, int U, int K>
 __device__ __forceinline__ void batch_pack_rows(G &g, const BatchReq &mine, uint32_t count, uint32_t *tile, int lane)
 {
     constexpr int LD = K + 4;
+    constexpr uint32_t R = 8;  // divides the tile's 64 rows
     const uint32_t len = (uint32_t)lane < count ? (uint32_t)mine.length : 0;
     const uint64_t out = (uint64_t)mine.out;
     for (uint32_t k0 = 0; __ballot(len > k0); k0 += K) {
         batch_numbers<G, DT, U>(g, tile + lane * LD, len > k0 ? min(len - k0, (uint32_t)K) : 0);
         RNGX_COMPILER_FENCE();
-        for (uint32_t i = 0; i < count; ++i) {
-            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, (int)i);
-            const uint64_t to = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(out >> 32), (int)i) << 32 |
-                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)out, (int)i);
-            const uint32_t at = k0 + (uint32_t)lane;
-            if (lane < K && at < n) global_ptr((uint32_t *)to)[at] = tile[i * LD + lane];
+        const uint32_t at = k0 + (uint32_t)lane;
+        // R rows at once, so that their LDS reads overlap (10^4 XS256 requests of 256
+        // samples 31 us, so 25); rows past `count` have no length
+        for (uint32_t i = 0; i < count; i += R) {
+            uint32_t v[R];
+#pragma unroll
+            for (uint32_t j = 0; j < R; ++j) v[j] = tile[(i + j) * LD + min(lane, K - 1)];
+#pragma unroll
+            for (uint32_t j = 0; j < R; ++j) {
+                const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, (int)(i + j));
+                const uint64_t to = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(out >> 32), (int)(i + j)) << 32 |
+                                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)out, (int)(i + j));
+                if (lane < K && at < n) global_ptr((uint32_t *)to)[at] = v[j];
+            }
         }
         RNGX_COMPILER_FENCE();
     }

@@ -29,10 +29,11 @@ constexpr uint32_t kBatchLgCounters = 5, kBatchCounterWords = 32;
 // kBatchPacked + c - 1 in lgc: the first of c requests that share one tile (the
 // others have none), a request per lane.  From kBatchPackMin requests of at most
 // kBatchPackMax samples on, about as many as the device holds waves: a tile of its
-// own costs each some 9 us of a wave, 8 more for XS256, a step in common 45 to 90 ns
-// (10^4 requests, us, own tiles / shared: XS256 x 100 107 / 52, x 256 105 / 67, KISS x
-// 64 82 / 46, MWC32 x 100 58 / 50, x 256 58 / 61).
-constexpr uint32_t kBatchPacked = 64, kBatchPackMin = 2048, kBatchPackMax = 256;
+// own costs each some 9 us of a wave, 8 more for XS256, a step in common 54 to 74 ns
+// (10^4 requests, us of the launch, own tiles / shared: XS256 x 100 74 / 13, x 320 77
+// / 30, x 700 80 / 62, KISS x 320 49 / 29, XS32 x 256 35 / 21, MWC32 x 256 23.5 / 18.9,
+// x 320 23.5 / 23.5; 30000: XS256 x 1000 211 / 90).
+constexpr uint32_t kBatchPacked = 64, kBatchPackMin = 2048, kBatchPackMax = 4096;
 
 struct BatchReq {
     uint32_t *state;     // word 0 of the stream's state

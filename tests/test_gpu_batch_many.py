@@ -1,6 +1,7 @@
 """Batches of thousands of short requests (more tiles than the grid has waves, pulled
-from several counters; from 2048 requests on those that are short enough share tiles) against the serial CPU oracle, bit for bit, launched twice from
-one plan, directly and as a graph.  Whole numbers: no tolerance."""
+from several counters; from 2048 requests on those that are short enough share tiles)
+against the serial CPU oracle, bit for bit, launched twice from one plan, directly and
+as a graph.  Whole numbers: no tolerance."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,8 @@ GENS = ["MWC32", "XS256", "XS32", "KISS", "MWC1616"]
 
 
 @pytest.mark.parametrize("n,longest,chunk,wg,graph", [(2049, 64, 0, 0, 0), (2300, 64, 0, 0, 0), (4500, 300, 0, 0, 0), (4500, 300, 64, 64, 0),
-                                                       (3000, 2000, 0, 1024, 0), (5000, 130, 0, 0, 1), (2700, 250, 512, 512, 0)])
+                                                       (3000, 2000, 0, 1024, 0), (5000, 130, 0, 0, 1), (2700, 250, 512, 512, 0),
+                                                       (9000, 700, 0, 0, 0), (9000, 1000, 0, 256, 1)])
 def test_many_short_requests(oracle, n, longest, chunk, wg, graph):
     import torch
     import paper_1101_1846_amd as R
