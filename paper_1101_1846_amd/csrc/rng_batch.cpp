@@ -320,7 +320,7 @@ static void packed_lengths(const uint32_t (&count)[6][kPackBins], uint64_t (&pac
     static const uint64_t kOwnTile[6] = {0, 17, 62, 27, 38, 24}, kStep[6] = {1, 540, 740, 630, 700, 550};
     uint64_t upto[6][kPackBins + 1], shorts = 0, packed = 0;  // upto[g][b]: requests in the first b bins
     for (uint32_t g = 1; g < 6; ++g) {
-        packs[g] = upto[g][0] = 0;
+        upto[g][0] = 0;
         for (uint32_t b = 0; b < kPackBins; ++b) upto[g][b + 1] = upto[g][b] + count[g][b];
         shorts += upto[g][kPackBins];
     }
@@ -343,7 +343,9 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
 {
     if (n > h->max_requests) return fail(RNG_ENOMEM, "%u requests > capacity %u", n, h->max_requests);
     uint64_t total_samples = 0;
-    uint32_t short_of[6][kPackBins] = {{0}};
+    uint32_t short_of[6][kPackBins];
+    const bool many = n >= kBatchPackMin;
+    if (many) std::memset(short_of, 0, sizeof(short_of));
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
         if (check_gen(r.gen)) return fail(RNG_EINVAL, "request %u: unknown generator %d", i, r.gen);
@@ -353,7 +355,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         if (r.length && (!r.d_out || ((uintptr_t)r.d_out & 3))) return fail(RNG_EINVAL, "request %u: bad output", i);
         if (__builtin_add_overflow(total_samples, r.length, &total_samples))
             return fail(RNG_ERANGE, "total length overflows");
-        if (r.length - 1 < kBatchPackMax) ++short_of[r.gen][(r.length - 1) / kPackBin];
+        if (many && r.length - 1 < kBatchPackMax) ++short_of[r.gen][(r.length - 1) / kPackBin];
     }
     if (total_samples > h->max_samples)
         return fail(RNG_ENOMEM, "batch of %llu samples > capacity %llu", (unsigned long long)total_samples,
@@ -367,8 +369,8 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     }
     h->planned = false;  // until this plan is complete: a failure below leaves nothing to launch
     const uint32_t longest = (uint32_t)__builtin_ctzll(longest_row(h)), cap = row_bits(n, total_samples, longest);
-    uint64_t packs[6];
-    packed_lengths(short_of, packs);
+    uint64_t packs[6] = {0};
+    if (many) packed_lengths(short_of, packs);
     // A request that one lane steps through sooner than the lanes' starts take stays
     // one row (16 requests, us, more rows / one: XS256 of 64 samples 14.3 / 9.5, of 100
     // 14.7 / 12.2, KISS of 64 11.6 / 9.3).
