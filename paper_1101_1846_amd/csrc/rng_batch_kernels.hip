@@ -25,13 +25,35 @@ __device__ __forceinline__ void with_gen(uint32_t g, F &&f)
     }
 }
 
-// One wave per request: copies its start state (the wave that ends a request
-// writes the state while others may not have read it yet), writes the request
-// of each of its tiles, and moves the state of an empty request, or the copy of
-// one that batch_moved names, by `offset`.
-// Also clears the generation kernel's tile counters.
 constexpr int kRootWG = 256;
 
+// Moves the state of an empty request, or the copy of one that batch_moved names, by
+// its offset.  The whole wave; q uniform.
+template <class G>
+__device__ __forceinline__ void root_move(const BatchArgs &a, const BatchReq &q, uint32_t r, uint32_t *lds, int lane)
+{
+    const bool moved = batch_moved(q);
+    G g;
+    g.load(q.state, q.stride, 0);
+    const uint64_t k = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(q.offset >> 32)) << 32 |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)q.offset);
+    wave_starts(g, k, kBatchLgMin, lds, lane, a.tab);
+    if (lane == 0) g.store(moved ? a.ws + (uint64_t)8 * r : q.state, moved ? 1 : q.stride, 0);
+}
+
+__device__ __forceinline__ bool root_moves(const BatchReq &q)
+{
+    return batch_moved(q) || (q.length == 0 && q.offset);
+}
+
+// Copies the start state of each request (the wave that ends a request writes the
+// state while others may not have read it yet), writes the request of each of its
+// tiles, and moves the states of root_moves.  Also clears the generation kernel's tile
+// counters.
+// One wave per request; kMany: eight requests per wave, a lane for each word, as a
+// request is mostly the latency of its reads (us, one / eight per wave: 5000 requests
+// 5.4 / 4.4, 10^4 6.8 / 4.6, 10^5 33 / 9).
+template <bool kMany>
 __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline pin)
 {
     __shared__ __attribute__((aligned(16))) uint32_t s_lds[kRootWG / 64][kWaveStartLds];
@@ -42,31 +64,49 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
     if (blockIdx.x == 0 && threadIdx.x < 1u << kBatchLgCounters) a.counter[threadIdx.x * kBatchCounterWords] = 0;
     const int lane = threadIdx.x & 63;
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = hp->n;
-    for (uint32_t r = blockIdx.x * (kRootWG / 64) + wv; r < n; r += gridDim.x * (kRootWG / 64)) {
-        const BatchReq q = reqs[r];
-        with_gen(hp->groups[q.group].gen, [&]<class G>() {
-            const bool moved = batch_moved(q);
-            if (moved || (q.length == 0 && q.offset)) {
-                G g;
-                g.load(q.state, q.stride, 0);
-                const uint64_t k = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(q.offset >> 32)) << 32 |
-                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)q.offset);
-                wave_starts(g, k, kBatchLgMin, s_lds[wv], lane, a.tab);
-                if (lane == 0) g.store(moved ? a.ws + (uint64_t)8 * r : q.state, moved ? 1 : q.stride, 0);
-            } else if (lane < G::W) {
-                a.ws[(uint64_t)8 * r + lane] = q.state[(uint64_t)lane * q.stride];
+    const uint32_t wave = blockIdx.x * (kRootWG / 64) + wv, waves = gridDim.x * (kRootWG / 64);
+    if constexpr (kMany) {
+        constexpr uint32_t kWords = GenMWC32::W << 4 * G_MWC32 | GenXS256::W << 4 * G_XS256 | GenXS32::W << 4 * G_XS32 |
+                                    GenKISS::W << 4 * G_KISS | GenMWC1616::W << 4 * G_MWC1616;
+        const uint32_t word = (uint32_t)lane & 7;
+        for (uint64_t r0 = (uint64_t)wave * 8; r0 < n; r0 += (uint64_t)waves * 8) {
+            const uint32_t r = (uint32_t)r0 + ((uint32_t)lane >> 3);
+            const bool here = r < n;
+            const BatchReq q = reqs[here ? r : n - 1];
+            const uint32_t words = kWords >> 4 * hp->groups[q.group].gen & 15;
+            const bool moves = here && root_moves(q);
+            if (here && !moves && word < words) a.ws[(uint64_t)8 * r + word] = q.state[(uint64_t)word * q.stride];
+            if (here && q.ntiles <= 64)
+                for (uint32_t i = word; i < q.ntiles; i += 8) a.tile_req[q.tile_base + i] = r;
+            for (uint64_t left = __ballot(word == 0 && here && (moves || q.ntiles > 64)); left; left &= left - 1) {
+                const uint32_t t = (uint32_t)r0 + ((uint32_t)__builtin_ctzll(left) >> 3);
+                const BatchReq u = reqs[t];
+                if (root_moves(u))
+                    with_gen(hp->groups[u.group].gen, [&]<class G>() { root_move<G>(a, u, t, s_lds[wv], lane); });
+                if (u.ntiles > 64)
+                    for (uint32_t i = lane; i < u.ntiles; i += 64) a.tile_req[u.tile_base + i] = t;
             }
-        });
-        for (uint32_t i = lane; i < q.ntiles; i += 64) a.tile_req[q.tile_base + i] = r;
+        }
+    } else {
+        for (uint32_t r = wave; r < n; r += waves) {
+            const BatchReq q = reqs[r];
+            with_gen(hp->groups[q.group].gen, [&]<class G>() {
+                if (root_moves(q)) root_move<G>(a, q, r, s_lds[wv], lane);
+                else if (lane < G::W) a.ws[(uint64_t)8 * r + lane] = q.state[(uint64_t)lane * q.stride];
+            });
+            for (uint32_t i = lane; i < q.ntiles; i += 64) a.tile_req[q.tile_base + i] = r;
+        }
     }
 }
 
 // ------------------------------------------------------------------ launchers
 int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t requests, hipStream_t s)
 {
-    const uint64_t blocks = ((uint64_t)requests + kRootWG / 64 - 1) / (kRootWG / 64);
+    const bool many = requests > 4096;  // more than one per wave
+    const uint64_t per = (many ? 8 : 1) * (kRootWG / 64), blocks = ((uint64_t)requests + per - 1) / per;
     const unsigned grid = (unsigned)(blocks < 1024 ? blocks : 1024);
-    hipLaunchKernelGGL(k_batch_root, dim3(grid ? grid : 1), dim3(kRootWG), 0, s, a, pin);
+    if (many) hipLaunchKernelGGL(k_batch_root<true>, dim3(grid), dim3(kRootWG), 0, s, a, pin);
+    else hipLaunchKernelGGL(k_batch_root<false>, dim3(grid ? grid : 1), dim3(kRootWG), 0, s, a, pin);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
