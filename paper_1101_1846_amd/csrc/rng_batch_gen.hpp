@@ -173,14 +173,6 @@ __device__ __forceinline__ void batch_pack(const BatchArgs &a, const BatchReq *r
     if ((uint32_t)lane < count) g.store(mine.state, mine.stride, 0);
 }
 
-template <class G, int U, int K>
-__device__ __forceinline__ void batch_any(const BatchArgs &a, const BatchReq *reqs, const BatchReq &q, uint32_t r, uint32_t i,
-                                          uint32_t dtype, uint32_t *tile, int lane)
-{
-    if (__builtin_expect(q.lgc >= kBatchPacked, 0)) batch_pack<G, U, K>(a, reqs, r, q.lgc - kBatchPacked + 1, dtype, tile, lane);
-    else batch_tile<G, U, K>(a, q, r, i, dtype, tile, lane);
-}
-
 // Persistent generation.  Wave w of the grid's W waves takes tile w first;
 // the tiles from W on are pulled from atomic counters (reset by the root
 // kernel), so a batch with fewer tiles than waves issues no atomics and the
@@ -204,12 +196,23 @@ __global__ __launch_bounds__(WG) void k_batch_gen(BatchArgs a)
         const BatchReq q = uniform_read(reqs + r);
         const BatchGroup gr = uniform_read(a.hdr->groups + q.group);
         const uint32_t i = t - q.tile_base;
-        switch (gr.gen) {
-        case G_MWC32: batch_any<GenMWC32, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
-        case G_XS256: batch_any<GenXS256, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
-        case G_XS32: batch_any<GenXS32, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
-        case G_KISS: batch_any<GenKISS, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
-        case G_MWC1616: batch_any<GenMWC1616, U, K>(a, reqs, q, r, i, gr.dtype, tile, lane); break;
+        if (__builtin_expect(q.lgc >= kBatchPacked, 0)) {  // its code behind the others' (small plans gain 0.3 us)
+            const uint32_t count = q.lgc - kBatchPacked + 1;
+            switch (gr.gen) {
+            case G_MWC32: batch_pack<GenMWC32, U, K>(a, reqs, r, count, gr.dtype, tile, lane); break;
+            case G_XS256: batch_pack<GenXS256, U, K>(a, reqs, r, count, gr.dtype, tile, lane); break;
+            case G_XS32: batch_pack<GenXS32, U, K>(a, reqs, r, count, gr.dtype, tile, lane); break;
+            case G_KISS: batch_pack<GenKISS, U, K>(a, reqs, r, count, gr.dtype, tile, lane); break;
+            case G_MWC1616: batch_pack<GenMWC1616, U, K>(a, reqs, r, count, gr.dtype, tile, lane); break;
+            }
+        } else {
+            switch (gr.gen) {
+            case G_MWC32: batch_tile<GenMWC32, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+            case G_XS256: batch_tile<GenXS256, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+            case G_XS32: batch_tile<GenXS32, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+            case G_KISS: batch_tile<GenKISS, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+            case G_MWC1616: batch_tile<GenMWC1616, U, K>(a, q, r, i, gr.dtype, tile, lane); break;
+            }
         }
         if (nwaves >= n_tiles) break;  // every tile was handed out statically
         const uint32_t lgc = uniform_read(&a.hdr->lg_counters), mine = (blockIdx.x * NW + wv) & ((1u << lgc) - 1);
