@@ -16,7 +16,7 @@
 #include "rng_batch_internal.hpp"
 
 namespace rngx {
-int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t requests, hipStream_t s);
+int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t requests, uint32_t moves, hipStream_t s);
 int launch_batch_gen(const BatchArgs &a, int wg, int unroll, unsigned grid, hipStream_t s);
 int batch_gen_occupancy(int wg, int unroll, int *blocks_per_cu);
 }  // namespace rngx
@@ -49,6 +49,7 @@ struct rng_batch {
     uint32_t occ_wg = 0, occ_unroll = 0;  // shape of the cached occupancy
     unsigned gen_full = 0;                // generation workgroups resident at once for that shape
     int num_cu = 256;
+    uint32_t moves = 0;               // requests of the plan whose state the root kernel moves
     std::vector<rng_request_t> last;  // last planned table, re-planned on a chunk change
     std::vector<uint16_t> codes;      // [max_requests] group and row bits, while a plan is made
     BatchHeader &hdr() { return *(BatchHeader *)h_plan; }
@@ -384,6 +385,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
     auto tiles_of = [](uint64_t length, uint32_t lg) { return (length + ((uint64_t)64 << lg) - 1) >> (lg + 6); };
     // per request: key = 16 (a tile of its own) + 2 generator + dtype, and its row bits
     uint64_t tiles = 0;
+    uint32_t moves = 0;
     uint32_t count[32] = {0}, group[32] = {0}, begin[32] = {0};
     for (uint32_t i = 0; i < n; ++i) {
         const rng_request_t &r = reqs[i];
@@ -391,6 +393,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         const uint32_t key = (packed ? 0 : 16) + (uint32_t)r.gen * 2 + (uint32_t)r.dtype;
         const uint32_t lg = packed ? kBatchPacked : tile_bits(r);
         h->codes[i] = (uint16_t)(key << 8 | lg);
+        moves += r.offset && (packed || r.length == 0);
         ++count[key];
         tiles += packed ? 0 : tiles_of(r.length, lg);
     }
@@ -432,6 +435,7 @@ static int plan(rng_batch_t *h, const rng_request_t *reqs, uint32_t n)
         base += Q[i].ntiles;
     }
     H.n_tiles = base;
+    h->moves = moves;
     // (every counter needs a wave: a grid that leaves tiles over has one per CU at least)
     H.lg_counters = total_samples < (uint64_t)base * 8192 && h->num_cu >= 1 << kBatchLgCounters ? kBatchLgCounters : 0;
     H.plan_bytes = (uint32_t)align16(H.off_reqs + sizeof(BatchReq) * (uint64_t)n);
@@ -476,7 +480,7 @@ int rng_batch_launch(rng_batch_t *h, void *stream)
     const unsigned gen_grid = h->gen_full;
     if (!h->use_graph) {
         const BatchArgs a = make_args(h, tab);
-        int rc = launch_batch_root(a, pin, H.n, st);
+        int rc = launch_batch_root(a, pin, H.n, h->moves, st);
         if (!rc && H.n_tiles) {
             // Up to a tile per CU goes out as workgroups of one wave, a CU each, if it
             // is long: four waves that share one slow each other down (16 XS256 requests
@@ -505,7 +509,7 @@ int rng_batch_launch(rng_batch_t *h, void *stream)
         if ((e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal)) != hipSuccess)
             return hip_fail(e, "hipStreamBeginCapture");
         pin.bytes = 0;  // the graph's root kernel reads the uploaded plan
-        int rc = launch_batch_root(a, pin, h->max_requests, cs);
+        int rc = launch_batch_root(a, pin, h->max_requests, 0, cs);
         if (!rc) rc = launch_batch_gen(a, (int)h->wg, (int)h->unroll, gen_grid, cs);
         e = hipStreamEndCapture(cs, &g.graph);
         if (rc) {

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "rng_batch_internal.hpp"
 #include "rng_device.hpp"
 #include "rng_internal.hpp"
@@ -50,11 +52,11 @@ __device__ __forceinline__ bool root_moves(const BatchReq &q)
 // state while others may not have read it yet), writes the request of each of its
 // tiles, and moves the states of root_moves.  Also clears the generation kernel's tile
 // counters.
-// One wave per request; kMany: eight requests per wave, a lane for each word, as a
-// request is mostly the latency of its reads (us, one / eight per wave: 5000 requests
-// 5.4 / 4.4, 10^4 6.8 / 4.6, 10^5 33 / 9).
+// One wave per request; kMany: `each` <= 8 requests per wave at once, a lane for each
+// word, as a request is mostly the latency of its reads (us, one by one / at once: 5000
+// requests 5.4 / 4.4, 10^4 6.8 / 4.6, 10^5 33 / 9).
 template <bool kMany>
-__global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline pin)
+__global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline pin, uint32_t each)
 {
     __shared__ __attribute__((aligned(16))) uint32_t s_lds[kRootWG / 64][kWaveStartLds];
     const BatchHeader *hp = pin.bytes ? (const BatchHeader *)pin.q : a.hdr;
@@ -69,9 +71,9 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
         constexpr uint32_t kWords = GenMWC32::W << 4 * G_MWC32 | GenXS256::W << 4 * G_XS256 | GenXS32::W << 4 * G_XS32 |
                                     GenKISS::W << 4 * G_KISS | GenMWC1616::W << 4 * G_MWC1616;
         const uint32_t word = (uint32_t)lane & 7;
-        for (uint64_t r0 = (uint64_t)wave * 8; r0 < n; r0 += (uint64_t)waves * 8) {
-            const uint32_t r = (uint32_t)r0 + ((uint32_t)lane >> 3);
-            const bool here = r < n;
+        for (uint64_t r0 = (uint64_t)wave * each; r0 < n; r0 += (uint64_t)waves * each) {
+            const uint32_t sub = (uint32_t)lane >> 3, r = (uint32_t)r0 + sub;
+            const bool here = sub < each && r < n;
             const BatchReq q = reqs[here ? r : n - 1];
             const uint32_t words = kWords >> 4 * hp->groups[q.group].gen & 15;
             const bool moves = here && root_moves(q);
@@ -100,13 +102,15 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
 }
 
 // ------------------------------------------------------------------ launchers
-int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t requests, hipStream_t s)
+int launch_batch_root(const BatchArgs &a, const PlanInline &pin, uint32_t requests, uint32_t moves, hipStream_t s)
 {
-    const bool many = requests > 4096;  // more than one per wave
-    const uint64_t per = (many ? 8 : 1) * (kRootWG / 64), blocks = ((uint64_t)requests + per - 1) / per;
-    const unsigned grid = (unsigned)(blocks < 1024 ? blocks : 1024);
-    if (many) hipLaunchKernelGGL(k_batch_root<true>, dim3(grid), dim3(kRootWG), 0, s, a, pin);
-    else hipLaunchKernelGGL(k_batch_root<false>, dim3(grid ? grid : 1), dim3(kRootWG), 0, s, a, pin);
+    // No more requests per wave than the 4096 waves at once need, as states move one by
+    // one, and one where most move (10^4 XS256 requests with an offset 112 us, so 102).
+    const uint64_t each = moves > requests / 2 ? 1 : std::max<uint64_t>(std::min<uint64_t>(((uint64_t)requests + 4095) / 4096, 8), 1);
+    const uint64_t per = each * (kRootWG / 64);
+    const unsigned grid = (unsigned)std::min<uint64_t>(((uint64_t)requests + per - 1) / per, 1024);
+    if (each > 1) hipLaunchKernelGGL(k_batch_root<true>, dim3(grid), dim3(kRootWG), 0, s, a, pin, (uint32_t)each);
+    else hipLaunchKernelGGL(k_batch_root<false>, dim3(grid ? grid : 1), dim3(kRootWG), 0, s, a, pin, 1u);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -14,13 +14,29 @@ GENS = ["MWC32", "XS256", "XS32", "KISS", "MWC1616"]
                                                        (3000, 2000, 0, 1024, 0), (5000, 130, 0, 0, 1), (2700, 250, 512, 512, 0),
                                                        (9000, 700, 0, 0, 0), (9000, 1000, 0, 256, 1)])
 def test_many_short_requests(oracle, n, longest, chunk, wg, graph):
-    import torch
-    import paper_1101_1846_amd as R
-    R.rng_init()
     rng = np.random.RandomState(n)
     length = rng.randint(0, longest + 1, n)
     length[:8] = [0, 1, longest, 32, 33, 63, 64, 65]
     offset = np.where(rng.randint(0, 4, n) == 0, rng.randint(1, 1 << 40, n), 0)
+    run(oracle, rng, length, offset, chunk, wg, graph)
+
+
+# above 4096 requests the root kernel takes several per wave, but not where most states
+# move by an offset; requests of more than 64 tiles among them
+@pytest.mark.parametrize("n,moved", [(4097, 3), (4097, 1), (8200, 8), (8200, 1)])
+def test_root_of_many(oracle, n, moved):
+    rng = np.random.RandomState(n + moved)
+    length = rng.randint(0, 40, n)
+    length[[5, n // 2, n - 1]] = 300000, 262144, 270001
+    offset = np.where(np.arange(n) % moved == 0, rng.randint(1, 1 << 62, n), 0)
+    run(oracle, rng, length, offset, 64, 0, 0)
+
+
+def run(oracle, rng, length, offset, chunk, wg, graph):
+    import torch
+    import paper_1101_1846_amd as R
+    R.rng_init()
+    n = len(length)
     gen, dtype, pad = rng.randint(0, 5, n), rng.randint(0, 2, n), rng.randint(0, 5, n)
     pools = []
     for g in GENS:
