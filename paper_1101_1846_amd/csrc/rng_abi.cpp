@@ -400,17 +400,17 @@ static bool seq_streams(int g, uint64_t S, uint64_t N, bool vec4, const void *ou
 // KISS's rows gain from every lane (1000 x 75 14.2 / 12.1).  More rows than lanes
 // lose only as whole tiles off a line's start (100000 x 512 at 16 bytes: XS32 39.1 /
 // 42.2, XS256 46.6 / 54.2) and for XS256 as short rows beyond 2^18 (300000 x 200 62.7
-// / 73.2, but 200000 x 168 44.5 / 39.8); MWC32 10^5 x 75 +54 %.  XS256 rows of an odd
-// number of 4 KiB, which k_generate takes with 512 lanes, where the last pass of the
-// row kernel's waves is short (100000 x 3072 255 / 280, but 64000 x 1024 130 / 44,
-// 300007 x 3072 804 / 759).
+// / 73.2, but 200000 x 168 44.5 / 39.8) or below 64 numbers (250000 x 60 23.8 / 28.1);
+// MWC32 10^5 x 75 +54 %.  XS256 rows of an odd number of 4 KiB, which k_generate takes
+// with 512 lanes, where the last pass of the row kernel's waves is short (100000 x 3072
+// 255 / 280, but 64000 x 1024 130 / 44, 300007 x 3072 804 / 759).
 static bool general_rows(int g, uint64_t S, uint64_t N, bool vec4, const void *out)
 {
     const bool cheap = g == RNG_XS32 || g == RNG_MWC32, lines = N % 32 == 0 && !((uintptr_t)out & 127);
     if (S > 65536) {
         if (!vec4 || g == RNG_KISS) return false;
         if (lines) return g == RNG_XS256 && xs256_chunked_rows(N) && 20 * S < 17 * ((S + 65535) & ~(uint64_t)65535);
-        if (g == RNG_XS256 && S > ((uint64_t)1 << 18)) return N < 256;
+        if (g == RNG_XS256 && (N < 64 || S > ((uint64_t)1 << 18))) return N < 256;
         return N % kGenTile == 0 && N >= 512;
     }
     if (S < 64) {

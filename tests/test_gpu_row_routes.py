@@ -40,7 +40,7 @@ def run(oracle, name, dt, S, N, off):
     ("u32", 200, 96, 0), ("u32", 5000, 416, 0),
     # more than 65536 streams
     ("u32", 65536, 512, 4), ("f32", 65537, 512, 4), ("u32", 66001, 640, 8), ("u32", 66001, 516, 4), ("f32", 262144, 200, 4),
-    ("u32", 262145, 200, 0), ("u32", 262200, 256, 4),
+    ("u32", 262145, 200, 0), ("u32", 262200, 256, 4), ("u32", 66001, 60, 0), ("f32", 70000, 64, 4),
     # windows, chunks and rows of the cheap generators and of KISS
     ("u32", 256, 11999, 4), ("f32", 257, 12000, 4), ("u32", 512, 19999, 1), ("f32", 300, 20000, 0), ("u32", 8191, 1300, 4),
     ("f32", 8192, 1100, 0), ("u32", 8192, 1096, 4), ("f32", 9000, 1700, 4),
