@@ -66,10 +66,10 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
     if (blockIdx.x == 0 && threadIdx.x < 1u << kBatchLgCounters) a.counter[threadIdx.x * kBatchCounterWords] = 0;
     const int lane = threadIdx.x & 63;
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = hp->n;
+    constexpr uint32_t kWords = GenMWC32::W << 4 * G_MWC32 | GenXS256::W << 4 * G_XS256 | GenXS32::W << 4 * G_XS32 |
+                                GenKISS::W << 4 * G_KISS | GenMWC1616::W << 4 * G_MWC1616;
     const uint32_t wave = blockIdx.x * (kRootWG / 64) + wv, waves = gridDim.x * (kRootWG / 64);
     if constexpr (kMany) {
-        constexpr uint32_t kWords = GenMWC32::W << 4 * G_MWC32 | GenXS256::W << 4 * G_XS256 | GenXS32::W << 4 * G_XS32 |
-                                    GenKISS::W << 4 * G_KISS | GenMWC1616::W << 4 * G_MWC1616;
         const uint32_t word = (uint32_t)lane & 7;
         for (uint64_t r0 = (uint64_t)wave * each; r0 < n; r0 += (uint64_t)waves * each) {
             const uint32_t sub = (uint32_t)lane >> 3, r = (uint32_t)r0 + sub;
@@ -92,11 +92,12 @@ __global__ __launch_bounds__(kRootWG) void k_batch_root(BatchArgs a, PlanInline 
     } else {
         for (uint32_t r = wave; r < n; r += waves) {
             const BatchReq q = reqs[r];
-            with_gen(hp->groups[q.group].gen, [&]<class G>() {
-                if (root_moves(q)) root_move<G>(a, q, r, s_lds[wv], lane);
-                else if (lane < G::W) a.ws[(uint64_t)8 * r + lane] = q.state[(uint64_t)lane * q.stride];
-            });
+            const uint32_t gen = hp->groups[q.group].gen;
+            uint32_t state = 0;  // on its way while the tiles are written
+            if ((uint32_t)lane < (kWords >> 4 * gen & 15)) state = q.state[(uint64_t)lane * q.stride];
             for (uint32_t i = lane; i < q.ntiles; i += 64) a.tile_req[q.tile_base + i] = r;
+            if (root_moves(q)) with_gen(gen, [&]<class G>() { root_move<G>(a, q, r, s_lds[wv], lane); });
+            else if ((uint32_t)lane < (kWords >> 4 * gen & 15)) a.ws[(uint64_t)8 * r + lane] = state;
         }
     }
 }
